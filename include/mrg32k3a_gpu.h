@@ -561,11 +561,13 @@ mrg_status mrg_state_check(const uint32_t state6[6]);
  *   "tile_bytes" bytes per stream per LDS tile of the lane-per-stream
  *                stream-major fill, 128 or 256, or 0 (default: 128 for rows
  *                shorter than 1 KiB, else 256);
- *   "strategy"   stream-major fill: 0 = automatic (default: one wave per
- *                stream when a stream has at least 64 x 128 bytes of output,
- *                except rows under 16 KiB that are not whole chunks on
- *                128-byte lines when at least 2^17 streams are filled; else
- *                one lane per stream), 1 = always lane per stream,
+ *   "strategy"   stream-major fill: 0 = automatic (default: several lanes
+ *                per stream for rows of 64 x 128 bytes and more, of 384 bytes
+ *                and a byte per 16 streams and more while the streams are at
+ *                most two waves of lanes per compute unit; except rows under
+ *                16 KiB that are not whole chunks on 128-byte lines when a
+ *                wave of streams fills every SIMD; else one lane per
+ *                stream), 1 = always lane per stream,
  *                2 = always wave per stream;
  *   "coop_wgs_per_cu" wave-per-stream fill: one-wave workgroups per compute
  *                unit, each looping over stream groups (0 = one workgroup
@@ -576,7 +578,9 @@ mrg_status mrg_state_check(const uint32_t state6[6]);
  *                range per XCD;
  *   "coop_lanes" wave-per-stream fill: lanes per stream, 64, 32, 16 or 8
  *                (64/coop_lanes streams share a wave), or 0 (the default:
- *                16 for rows under 64 KiB, else 64).
+ *                64 for rows of 64 KiB and more, else as many as give two
+ *                waves per SIMD, at least 16, or 8 for many short rows off
+ *                their lines).
  * Unknown keys or values: MRG_EINVAL.  Takes effect for later launches. */
 mrg_status mrg_config_set(const char *key, int64_t value);
 mrg_status mrg_config_get(const char *key, int64_t *value);

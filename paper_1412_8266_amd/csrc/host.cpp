@@ -319,6 +319,38 @@ mrg_status new_streamset(uint64_t n_streams, uint64_t first_stream, mrg_streamse
     return MRG_OK;
 }
 
+// Shortest row (bytes) that the automatic stream-major fill gives to several
+// lanes per stream.  A lane draws its stream in series, 60 ns a uint32 and
+// 90 ns a binary64 when its wave has the SIMD to itself, so a launch of few
+// streams takes that time its row length whatever it writes (64 x 1000
+// uint32: 58 us; 9 us with 64 lanes per stream, the time of the call itself).
+// Several lanes cost a jump per lane instead, which grows with the streams:
+// the line lies at about one byte per 16 streams (uint32, lane against
+// several: 4096 x 100 10.7 against 9.4 us, 16384 x 200 17.2 against 14.0,
+// 32768 x 200 18.7 against 25, x 500 35.7 against 34.3), and from half a wave
+// per SIMD on at a whole chunk of 64 lines (49152 x 1000: 64 against 69).
+uint64_t coop_min_bytes(uint64_t count, int cus)
+{
+    if (count > (uint64_t)cus * 128) return 64 * 128;
+    return count / 16 > 384 ? count / 16 : 384;
+}
+
+// Lanes per stream of the automatic stream-major fill: as many as bring the
+// launch to two waves per SIMD (64 for up to 2048 streams on 256 CUs, 32 for
+// 4096, 16 for 8192; 1024 x 10000 uint32 with 64 / 32 / 16 lanes: 16.5 / 23.8
+// / 38.0 us, 4096 x 3000 with 32 / 16: 21.4 / 26.6, 8192 x 1000 with 32 / 16
+// / 8: 21.4 / 18.4 / 23.1).  With more streams 64 for rows of 64 KiB and
+// more, 16 for shorter ones (8 when they are cut: rows under 16 KiB off
+// their lines, 32768 x 1000 49 against 53 us, 49152 x 3000 160 against 175).
+int coop_auto_lanes(uint64_t count, uint64_t row_bytes, bool rows_aligned, int cus)
+{
+    if (row_bytes >= 65536) return 64;
+    const uint64_t slots = (uint64_t)cus * 8 * 64;  // lanes of two waves per SIMD
+    if (count * 64 <= slots) return 64;
+    if (count * 32 <= slots) return 32;
+    return !rows_aligned && row_bytes < 16 * 1024 && count * 8 >= slots ? 8 : 16;
+}
+
 // A^e for both components as kernel arguments.
 mrg::JumpMatrices jump_matrices(const uint64_t e[3])
 {
@@ -580,25 +612,23 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
     }
     mrg::FillLaunch fl;
     if (layout == MRG_STREAM_MAJOR) {
-        // wave per stream when a stream fills at least one chunk of 64 lanes x
-        // 128 bytes (or when forced; see below for rows under 16 KiB); lane per
-        // stream for short streams
-        const uint64_t min_chunk = 64 * (128 / es);
-        const bool coop = tune.strategy == 2 || (tune.strategy == 0 && n_per_stream >= min_chunk);
+        // several lanes per stream (or when forced) for rows from coop_min_bytes
+        // on (see below for rows under 16 KiB); lane per stream for the others
+        DevCtx *ctx;
+        if ((st = device_ctx(ss->device, &ctx))) return st;
+        const bool coop = tune.strategy == 2 ||
+                          (tune.strategy == 0 && n_per_stream * es >= coop_min_bytes(count, ctx->cus));
         if (coop) {
-            DevCtx *ctx;
-            if ((st = device_ctx(ss->device, &ctx))) return st;
             // GL lanes per stream, 64/GL streams per wave; each lane takes
             // 64/GL or 2*64/GL pieces of 128 bytes per chunk (a chunk is then
             // 64 or 128 lines), whichever generates fewer values past the end
             // of a row (the longer chunk on a tie).  A row's line-aligned
             // part is n values, or about n - tv/2 when rows start anywhere.
-            // automatic: 16 lanes for rows under 64 KiB, else 64 (measured
-            // faster for rows of 64 KiB and more)
-            const int GL = tune.coop_lanes ? tune.coop_lanes : n_per_stream * es >= 65536 ? 64 : 16;
+            const bool rows_aligned = (uintptr_t)d_out % 128 == 0 && (n_per_stream * es) % 128 == 0;
+            const int GL = tune.coop_lanes ? tune.coop_lanes
+                                           : coop_auto_lanes(count, n_per_stream * es, rows_aligned, ctx->cus);
             const uint64_t tv = 128 / es;
             const uint64_t nh_min = 64 / GL, nh_max = 2 * nh_min;
-            const bool rows_aligned = (uintptr_t)d_out % 128 == 0 && (n_per_stream * es) % 128 == 0;
             const uint64_t body = rows_aligned || n_per_stream <= tv ? n_per_stream : n_per_stream - tv / 2;
             const uint64_t ch_min = (uint64_t)GL * nh_min * tv, ch_max = 2 * ch_min;
             const uint64_t gen_min = (body + ch_min - 1) / ch_min * ch_min;
@@ -624,14 +654,16 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
                        (uint64_t)(64 / GL) * n_per_stream * es < ((uint64_t)1 << 32);
             // automatic choice: a row under 16 KiB that is not whole chunks on
             // lines is one cut chunk for this writer (values drawn past the
-            // row's end, one piece per flush), and with enough streams to fill
-            // the chip one lane each (2048 waves of 64) the lane-per-stream
-            // writer is the faster one (uint32 rows of 3000: 4.0-4.5 against
-            // 3.4 TB/s; of 4000: 4.2-4.4 against 3.6-3.7; from 4500 values
-            // this writer leads, 4.7-4.8 against 4.0-4.5).  With fewer streams
-            // this writer's 16 lanes per stream keep the launch short.
+            // row's end, one piece per flush), and with enough streams for one
+            // wave of them on every SIMD (2^16 on 256 CUs) the lane-per-stream
+            // writer is the faster one (uint32 rows of 3000: 190 us against
+            // 210-235 for 2^16 streams, 4.0-4.5 against 3.4 TB/s for 2^17 and
+            // more; of 4000: 228 against 264-276 us, 4.2-4.4 against 3.6-3.7
+            // TB/s; from 4500 values this writer leads, 4.7-4.8 against
+            // 4.0-4.5).  With fewer streams this writer keeps the launch short
+            // (49152 x 3000: 160 against 177 us).
             if (tune.strategy == 0 && !fl.whole && n_per_stream * es < 16 * 1024 &&
-                count >= ((uint64_t)64 << 11))
+                count >= (uint64_t)ctx->cus * 256)
                 fl = mrg::FillLaunch();
         }
     }

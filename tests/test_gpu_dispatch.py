@@ -1,0 +1,57 @@
+"""GPU: the automatic choice of fill kernels at its edges, against the oracle.
+
+Every shape sits at a line of a dispatch rule (number of streams against the
+chip, row bytes, rows on or off 128-byte lines) with remainders on both sides
+of it.  Outputs and states are integers or exact conversions of them:
+tolerance 0.  Guard words around every output stay untouched, and a second
+fill continues the first.
+"""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 32
+
+
+@pytest.fixture(scope="module")
+def mg():
+    import torch
+    import paper_1412_8266_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+def check(mg, first, count, n, dtype, layout, off, reps=2):
+    import torch
+    print("dispatch", first, count, n, dtype, layout, off, flush=True)
+    base = oracle.seed_from_master(20120719)
+    ss = mg.StreamSet(first + count + 1, seed=[int(x) for x in base])
+    st = oracle.streams(base, first, count)
+    buf = torch.zeros(count * n + off + 2 * GUARD, dtype=mg.torch_dtype(dtype), device="cuda")
+    lo, hi = GUARD + off, GUARD + off + count * n
+    for rep in range(reps):
+        buf.zero_()
+        ss.fill_ptr(n, dtype, layout, buf[lo:hi].data_ptr(), first=first, count=count)
+        h = buf.cpu().numpy()
+        want, st = oracle.fill(st, n, dtype, layout)
+        assert np.array_equal(h[lo:hi].view(np.uint8), want.reshape(-1).view(np.uint8)), rep
+        assert not h[:lo].view(np.uint8).any() and not h[hi:].view(np.uint8).any(), rep
+    assert np.array_equal(ss.get_states(first, count), st)
+    assert np.array_equal(ss.get_states(0, first), oracle.streams(base, 0, first))
+    ss.close()
+
+
+# rows: lanes per stream by the number of streams (64 / 32 / 16 / 8, one) and
+# the shortest row given to several lanes (384 bytes; a byte per 16 streams)
+ROWS = [(1, 95, 0, 0), (1, 96, 0, 0), (5, 97, 1, 3), (2048, 100, 0, 0), (2049, 100, 0, 1),
+        (4096, 190, 2, 0), (4097, 127, 0, 0), (8200, 129, 1, 0), (16384, 256, 0, 0),
+        (16384, 255, 0, 1), (20000, 330, 0, 0), (32768, 257, 2, 0), (32769, 600, 0, 0),
+        (65535, 600, 1, 0), (65536, 2050, 0, 0)]
+
+
+@pytest.mark.parametrize("count,n,dtype,off", ROWS)
+def test_rows(mg, count, n, dtype, off):
+    check(mg, 3, count, n, dtype, 0, off, reps=1 if count * n > 1 << 25 else 2)
