@@ -489,6 +489,43 @@ __device__ __forceinline__ void rows_fill_short(G &g, unsigned char *lds, int la
     __syncthreads();
 }
 
+// st <- A^e st with e the same in the whole wave: the matrices come through
+// scalar loads, the next digit's while the current product runs, where
+// jump_global waits for a vector load before each (2^20 uint32 of one stream
+// in blocks: 14.2 us with jump_global, 12.8 with this).
+__device__ __forceinline__ void jump_uniform(const uint32_t *__restrict__ table, uint64_t e,
+                                             uint32_t *st)
+{
+    typedef const uint32_t __attribute__((address_space(4))) *scalar_t;
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e);
+    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32));
+    uint64_t left = (uint64_t)hi << 32 | lo;
+    if (!left) return;
+    uint32_t m[18];
+    auto next = [&]() {  // the lowest nonzero digit's matrices, and drop it
+        const int w = __builtin_ctzll(left) / 4;
+        const uint32_t d = (uint32_t)(left >> (4 * w)) & 15u;
+        left &= ~((uint64_t)15 << (4 * w));
+        const scalar_t t = (scalar_t)(uintptr_t)(table + (w * 16 + d) * 9);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            m[i] = t[i];
+            m[9 + i] = t[kTableWindows * kTableWindowWords + i];
+        }
+    };
+    next();
+    for (;;) {
+        uint32_t c[18];
+#pragma unroll
+        for (int i = 0; i < 18; ++i) c[i] = m[i];
+        const bool more = left != 0;
+        if (more) next();
+        matvec3<C1>(c, st[0], st[1], st[2]);
+        matvec3<C2>(c + 9, st[3], st[4], st[5]);
+        if (!more) break;
+    }
+}
+
 // One 128-byte piece (128 / ES values) of a member's segment from g into
 // LDS at pl.  With checked draws (GenF) the piece is drawn with the cheaper
 // combination; when some lane's check fails the whole wave draws it again
@@ -811,6 +848,25 @@ __device__ __forceinline__ void wave_fill_whole(uint32_t *w, const uint32_t *m, 
 #pragma unroll
         for (int k = 0; k < 6; ++k) w[k] = __shfl(e[k], tl * GL + GL - 1);
     }
+}
+
+// Several waves of one launch draw from the same stream, each from its own
+// place: all of them read the stream's state, and the state may move on only
+// when the last of them has read it.  Each wave (or lane, with a ticket word
+// per stream) arrives at the stream's ticket once its state words w are in
+// registers; the one for which last_arrival holds is alone left with the
+// stream and writes its end state.  The ticket wraps to 0 at the last of
+// `parts` arrivals, ready for the next launch, so no launch follows the fill
+// to move the states (1.5-4 us and its host call).
+__device__ __forceinline__ uint32_t arrive(uint32_t *ticket, uint32_t parts, uint32_t *w)
+{
+    // the state words are in registers from here on
+    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5])::"memory");
+    return atomicInc(ticket, parts - 1);
+}
+__device__ __forceinline__ bool last_arrival(uint32_t arrived, uint32_t parts)
+{
+    return arrived >= parts - 1;
 }
 
 // Workgroups are dispatched to the 8 XCDs in turn (workgroup b on XCD b % 8).

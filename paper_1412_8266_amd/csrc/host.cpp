@@ -309,7 +309,7 @@ mrg_status new_streamset(uint64_t n_streams, uint64_t first_stream, mrg_streamse
     ss->device = dev;
     ss->n = n_streams;
     ss->first = first_stream;
-    hipError_t e = hipMalloc(&ss->d_planes, 6 * n_streams * sizeof(uint32_t));
+    hipError_t e = hipMalloc(&ss->d_planes, mrg::set_words(n_streams) * sizeof(uint32_t));
     if (e != hipSuccess) {
         delete ss;
         return set_error(MRG_ENOMEM, "hipMalloc(%llu states): %s", (unsigned long long)n_streams,
@@ -351,14 +351,69 @@ int coop_auto_lanes(uint64_t count, uint64_t row_bytes, bool rows_aligned, int c
     return !rows_aligned && row_bytes < 16 * 1024 && count * 8 >= slots ? 8 : 16;
 }
 
-// A^e for both components as kernel arguments.
+// A^e for both components as kernel arguments: the product of the windowed
+// tables' matrices at the nonzero hexadecimal digits of e.
 mrg::JumpMatrices jump_matrices(const uint64_t e[3])
 {
     mrg::JumpMatrices J;
-    const Mat P1 = power(0, e), P2 = power(1, e);
-    std::memcpy(J.m, P1.data(), 36);
-    std::memcpy(J.m + 9, P2.data(), 36);
+    const std::vector<uint32_t> &t = host_tables();
+    for (int c = 0; c < 2; ++c) {
+        Mat R = identity();
+        bool any = false;
+        for (int w = 0; w < mrg::kTableWindows; ++w) {
+            const int d = (int)(e[w / 16] >> (4 * (w % 16))) & 15;
+            if (!d) continue;
+            Mat T;
+            std::memcpy(T.data(), &t[((c * mrg::kTableWindows + w) * 16 + d) * 9], 36);
+            R = any ? mul(R, T, modulus(c)) : T;
+            any = true;
+        }
+        std::memcpy(J.m + 9 * c, R.data(), 36);
+    }
     return J;
+}
+
+// Rows in blocks of a wave each (fill_split_kernel): about 16 blocks per
+// compute unit in all (two rounds of the waves that are resident), each a
+// whole number of 64-lane chunks -- of 64 KiB (256 uint32 per lane and start
+// state) when the blocks are that long, else of 16 or 8 KiB -- and at most 256
+// KiB (one stream of 2^32 uint32 in order: 2 MiB blocks 2 % slower).
+void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t count, uint64_t n,
+                uint64_t es)
+{
+    const uint64_t row = n * es, want = row / 16 * count / (uint64_t)ctx->cus;
+    const uint64_t unit = want >= 65536 ? 65536 : want >= 16384 ? 16384 : 8192;
+    uint64_t bb = want / unit * unit;
+    bb = bb < unit ? unit : bb > 262144 ? 262144 : bb;
+    // fewer blocks than 2^32 per row, and than 2^31 workgroups in all
+    while (row / bb >= ((uint64_t)1 << 31) / count) bb *= 2;
+    fl->kernel = 2;
+    fl->L = (int)(unit / 64 / es);
+    fl->B = bb / es;
+    // a remainder under an eighth of a block goes to the last block
+    fl->nblk = (uint32_t)(n / fl->B + (n % fl->B > fl->B / 8 || n < fl->B));
+    fl->lane_tab = ctx->d_lane_tab + mrg::lane_table(fl->L) * 64 * 18;
+    fl->tabs = ctx->d_lane_tab;
+    fl->table = ctx->d_table;
+    fl->grid = (unsigned)(count * fl->nblk);
+    const uint64_t e[3] = {n, 0, 0};
+    fl->end = jump_matrices(e);
+    // up to 256 arrivals per ticket line (5 us of them in a row) the fill moves
+    // its streams itself, which spares a launch; beyond, a launch follows
+    const uint64_t per_line = mrg::ticket_pitch(set_n) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
+    fl->move = fl->nblk * per_line <= 256;
+}
+
+// The fill of split_rows and, when it does not move its streams, their jump.
+hipError_t run_split(mrg_streamset ss, const mrg::FillLaunch &fl, const mrg::FillTuning &tune,
+                     uint64_t first, uint64_t count, uint64_t n, mrg_dtype dtype, void *d_out,
+                     hipStream_t st)
+{
+    hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n, (int)dtype, 0, d_out, fl,
+                                    tune, st);
+    if (e == hipSuccess && !fl.move)
+        e = mrg::launch_jump_uniform(ss->d_planes, ss->n, first, count, fl.end, st);
+    return e;
 }
 
 }  // namespace
@@ -666,6 +721,22 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
                 count >= (uint64_t)ctx->cus * 256)
                 fl = mrg::FillLaunch();
         }
+        // few streams: a wave per stream leaves the chip idle and takes 2.3 us
+        // per 4096 uint32 of a row whatever the launch writes, so rows are cut
+        // into blocks (256 x 16384 uint32 15.1 -> 11.2 us, 64 x 2^20 590 -> 49).
+        // With two waves or more per CU the rows have to be long enough for the
+        // blocks' jumps (512 x 10000 15.7 -> 16.9, 512 x 40000 35.4 -> 28.4),
+        // and with a wave per SIMD the rows alone fill the chip (1000 x 65536
+        // 50 -> 56).
+        if (tune.strategy == 0 &&
+            ((count <= (uint64_t)ctx->cus && n_per_stream * es >= 16 * 1024) ||
+             (count <= (uint64_t)ctx->cus * 2 && n_per_stream * es >= 64 * 1024))) {
+            fl = mrg::FillLaunch();
+            split_rows(&fl, ctx, ss->n, count, n_per_stream, es);
+            hipError_t e = run_split(ss, fl, tune, first, count, n_per_stream, dtype, d_out,
+                                     (hipStream_t)stream);
+            return e == hipSuccess ? MRG_OK : hip_error(e, "fill kernel launch");
+        }
     }
     hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n_per_stream, (int)dtype,
                                     (int)layout, d_out, fl, tune, (hipStream_t)stream);
@@ -696,65 +767,50 @@ mrg_status mrg_fill_leapfrog(mrg_streamset ss, uint64_t s, uint64_t players,
     DevCtx *ctx;
     if ((st = device_ctx(ss->device, &ctx))) return st;
     const mrg::FillTuning tune = tuning();
-    mrg::PartitionLaunch pl;
-    pl.table = ctx->d_table;
-    const uint64_t slots = (uint64_t)ctx->cus * 16;  // resident one-wave workgroups
+    const uint64_t en[3] = {N, 0, 0};
     // with one player or one card per player both layouts are the stream in order
     if (layout == MRG_INTERLEAVED || players == 1 || per_player == 1) {
-        // the stream's outputs in order: blocks of 16-256 KiB (at least 4096
-        // of them when the output allows), each a whole number of 128-line
-        // chunks, one 64-lane wave per block
-        const uint64_t tv = 128 / es;
-        uint64_t bb = 16384;
-        while (bb < 262144 && N * es / (2 * bb) >= 4096) bb *= 2;
-        pl.kind = 0;
-        pl.B = bb / es;
-        pl.nfull = N / pl.B;
-        pl.rem = N % pl.B;
-        const bool one_chunk = N < 128 * tv;  // short: 64-line chunks
-        pl.L = (int)(one_chunk ? tv : 2 * tv);
-        pl.lane_tab = ctx->d_lane_tab + mrg::lane_table(pl.L) * 64 * 18;
-        pl.tabs = ctx->d_lane_tab;
-        const uint64_t blocks = pl.nfull + (pl.rem ? 1 : 0);
-        pl.grid = (unsigned)(blocks < ((uint64_t)1 << 31) - 1 ? blocks : ((uint64_t)1 << 31) - 1);
-    } else {
-        // each player's cards in a row: items of KB = min(K, 64) card columns
-        // x T players (R = 64 / KB lanes per column, Ts = T / R players
-        // each), T chosen for about 4 items per resident workgroup (at least
-        // 256 players per lane)
-        mrg::LeapArgs &A = pl.leap;
-        pl.kind = 1;
-        A.P = players;
-        A.K = per_player;
-        A.KB = (int)(per_player < 64 ? per_player : 64);
-        A.R = 64 / A.KB;
-        const uint64_t nkb = (per_player + A.KB - 1) / A.KB;
-        const uint64_t target = 4 * slots;
-        uint64_t Ts = (players + A.R - 1) / A.R;
-        if (nkb < target) {
-            const uint64_t segs = (target + nkb - 1) / nkb;
-            Ts = (players + segs * A.R - 1) / (segs * A.R);
-            if (Ts < 256) Ts = 256;
-        }
-        const uint64_t ts_max = (players + A.R - 1) / A.R;
-        if (Ts > ts_max) Ts = ts_max;
-        A.Ts = Ts;
-        A.T = Ts * A.R;
-        A.nseg = (players + A.T - 1) / A.T;
-        A.items = nkb * A.nseg;
-        pl.grid = (unsigned)(A.items < slots ? A.items : slots);
-        // 63 * players and T - Ts as 192-bit exponents
-        const unsigned __int128 e63 = (unsigned __int128)players * 63u;
-        const uint64_t ew[3] = {(uint64_t)e63, (uint64_t)(e63 >> 64), 0};
-        A.J63 = jump_matrices(ew);
-        const uint64_t es_[3] = {A.T - A.Ts, 0, 0};
-        A.Jseg = jump_matrices(es_);
+        // the stream's outputs in order: one row in blocks
+        mrg::FillLaunch fl;
+        split_rows(&fl, ctx, ss->n, 1, N, es);
+        hipError_t e = run_split(ss, fl, tune, s, 1, N, dtype, d_out, (hipStream_t)stream);
+        return e == hipSuccess ? MRG_OK : hip_error(e, "leapfrog kernel launch");
     }
-    hipError_t e = mrg::launch_partition(ss->d_planes, ss->n, s, (int)dtype, pl, d_out,
-                                         tune.engine, (hipStream_t)stream);
+    // each player's cards in a row: items of KB = min(K, 64) card columns
+    // x T players (R = 64 / KB lanes per column, Ts = T / R players
+    // each), T chosen for about 4 items per resident workgroup (at least
+    // 256 players per lane)
+    const uint64_t slots = (uint64_t)ctx->cus * 16;  // resident one-wave workgroups
+    mrg::LeapArgs A;
+    A.P = players;
+    A.K = per_player;
+    A.KB = (int)(per_player < 64 ? per_player : 64);
+    A.R = 64 / A.KB;
+    const uint64_t nkb = (per_player + A.KB - 1) / A.KB;
+    const uint64_t target = 4 * slots;
+    uint64_t Ts = (players + A.R - 1) / A.R;
+    if (nkb < target) {
+        const uint64_t segs = (target + nkb - 1) / nkb;
+        Ts = (players + segs * A.R - 1) / (segs * A.R);
+        if (Ts < 256) Ts = 256;
+    }
+    const uint64_t ts_max = (players + A.R - 1) / A.R;
+    if (Ts > ts_max) Ts = ts_max;
+    A.Ts = Ts;
+    A.T = Ts * A.R;
+    A.nseg = (players + A.T - 1) / A.T;
+    A.items = nkb * A.nseg;
+    // 63 * players and T - Ts as 192-bit exponents
+    const unsigned __int128 e63 = (unsigned __int128)players * 63u;
+    const uint64_t ew[3] = {(uint64_t)e63, (uint64_t)(e63 >> 64), 0};
+    A.J63 = jump_matrices(ew);
+    const uint64_t es_[3] = {A.T - A.Ts, 0, 0};
+    A.Jseg = jump_matrices(es_);
+    hipError_t e = mrg::launch_leap(ss->d_planes, ss->n, s, (int)dtype, A,
+                                    (unsigned)(A.items < slots ? A.items : slots), ctx->d_table,
+                                    d_out, tune.engine, (hipStream_t)stream);
     if (e != hipSuccess) return hip_error(e, "leapfrog kernel launch");
     // the stream moves past the N outputs dealt
-    const uint64_t en[3] = {N, 0, 0};
     e = mrg::launch_jump_uniform(ss->d_planes, ss->n, s, 1, jump_matrices(en), (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "jump kernel launch");
 }

@@ -9,6 +9,17 @@ namespace mrg {
 
 constexpr int kTableWords = 2 * kTableWindows * kTableWindowWords;
 
+// A set's device memory: the six state planes, then one ticket word per stream
+// (arrive() in gen_device.hpp), 0 between launches and set by the kernels that
+// create the streams.  Arrivals at one 128-byte line queue up, 20 ns each over
+// the eight XCDs, so sets of up to 4096 streams give each ticket its own line.
+__host__ __device__ constexpr uint64_t ticket_pitch(uint64_t n) { return n <= 4096 ? 32 : 1; }
+__host__ __device__ constexpr uint64_t ticket_of(uint64_t n, uint64_t i)
+{
+    return 6 * n + i * ticket_pitch(n);
+}
+constexpr uint64_t set_words(uint64_t n) { return 6 * n + n * ticket_pitch(n); }
+
 struct InitSeed { uint32_t w[6]; };
 struct JumpMatrices { uint32_t m[18]; };  // component 1 then component 2
 
@@ -43,7 +54,7 @@ __host__ __device__ constexpr int lane_table(int L) { return L / 16 - 1; }
 
 // How one stream-major fill is launched (chosen on the host).
 struct FillLaunch {
-    int kernel = 0;                     // 0 lane per stream, 1 wave per stream
+    int kernel = 0;                     // 0 lane per stream, 1 wave per stream, 2 rows in blocks
     int L = 0;                          // values per lane per chunk (wave per stream)
     int lanes = 64;                     // lanes per stream (wave per stream)
     const uint32_t *lane_tab = nullptr; // [64][18]: A^(l*L), component 1 then 2 (lane l % lanes)
@@ -52,6 +63,12 @@ struct FillLaunch {
     unsigned grid = 0;                  // workgroups (wave per stream)
     int order = 0;                      // group order (FillTuning::coop_order)
     int whole = 0;                      // rows on 128-byte lines, whole chunks only (fast writer)
+    // rows in blocks: each row cut into nblk blocks of B values from its first
+    // 128-byte line on, a wave each; the streams then move by n (end = A^n)
+    uint64_t B = 0;
+    uint32_t nblk = 0;
+    int move = 0;                       // the last block to read a state moves it (tickets)
+    JumpMatrices end = {};
 };
 
 hipError_t launch_fill(uint32_t *planes, uint64_t plane_stride, uint64_t first, uint64_t count,
@@ -73,23 +90,10 @@ struct LeapArgs {
     JumpMatrices Jseg = {};  // A^(T - Ts): to the next segment (R > 1)
 };
 
-// One stream partitioned (chosen on the host): kind 0 writes its outputs
-// [0, nfull*B + rem) in order, in blocks of B values (64 lanes per block, L
-// values per lane per chunk); kind 1 deals them to players, each player's
-// cards in a row.
-struct PartitionLaunch {
-    int kind = 0;
-    int L = 0;
-    uint64_t nfull = 0, B = 0, rem = 0;  // kind 0
-    LeapArgs leap;                       // kind 1
-    const uint32_t *lane_tab = nullptr;  // kind 0: [64][18] A^(l*L)
-    const uint32_t *tabs = nullptr;      // kind 0: all lane tables
-    const uint32_t *table = nullptr;     // windowed jump tables
-    unsigned grid = 0;
-};
-hipError_t launch_partition(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
-                            int dtype, const PartitionLaunch &pl, void *out, int engine,
-                            hipStream_t st);
+// One stream (plane index sidx) dealt to players, each player's cards in a row.
+hipError_t launch_leap(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
+                       const LeapArgs &A, unsigned grid, const uint32_t *table, void *out,
+                       int engine, hipStream_t st);
 
 // Philox4x32-10 stream sets (philox.hip): states (position, id, key); fills
 // leave the positions to a following launch_philox_jump.

@@ -13,7 +13,8 @@
 //                    stream (sequence splitting inside each stream)
 //   random_init_kernel  random spacing: each stream from its own expanded
 //                    SplitMix64 draw                                     (sec. 2.3)
-//   fill_split_kernel   one stream's outputs in order, split into blocks
+//   fill_split_kernel   rows of few streams (or one stream in order), split
+//                       into blocks of a wave each                     (sec. 2.3)
 //   fill_leap_kernel    leapfrog: one stream dealt to P players, each
 //                    player's cards in a row                            (sec. 2.3)
 #include <hip/hip_runtime.h>
@@ -78,6 +79,7 @@ jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first
         planes[3 * plane_stride + idx] = canon2(b0);
         planes[4 * plane_stride + idx] = canon2(b1);
         planes[5 * plane_stride + idx] = canon2(b2);
+        if (!exps) planes[ticket_of(plane_stride, idx)] = 0u;
     }
 }
 
@@ -115,6 +117,7 @@ random_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     uint32_t w[6];
     expand_seed(splitmix64_mix(master + (g0 + s + 1) * kSplitMixGamma), w);
     store_state(planes, plane_stride, s, w);
+    planes[ticket_of(plane_stride, s)] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -234,34 +237,53 @@ fill_coop_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t 
     }
 }
 
-// Sequence splitting of one stream (sec. 2.3): its outputs [0, N) in order as
-// blocks of B values (the last one rem values when rem > 0), block r starting
-// from A^(r*B) applied to the stream state (stream sidx of the planes) and
-// written by one wave with wave_fill (64 lanes, L values per lane per chunk).
-// Each XCD takes one contiguous range of blocks (measured 4 % faster here than
-// the chunked order of the stream-major fill).  The stream state is not
-// advanced here.
+// Sequence splitting inside each stream (sec. 2.3), for fewer streams than
+// the chip has wave slots (and one stream dealt in order): row s, n values at
+// out + s * n * ES, is cut into nblk blocks, block q > 0 starting B values per
+// block past the row's first 128-byte line, so that blocks meet on lines.  One
+// wave per block jumps the stream's state to it (A^v0, windowed) and writes it
+// with wave_fill (64 lanes, L values per lane per chunk).  With `move` the
+// last wave to read a stream's state moves it by n (J = A^n; arrive()), else
+// the states are left to a launch after this one.  Each XCD takes one
+// contiguous range of blocks (one stream in order: 4 % faster than the
+// chunked order of the stream-major fill).
 template <int DT, int L, class G>
-__global__ void __launch_bounds__(64)
-fill_split_kernel(const uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t sidx,
-                  uint64_t nfull, uint64_t B, uint64_t rem, unsigned char *__restrict__ out,
+__global__ void __launch_bounds__(64, (coop_pieces<DT, L>() == 2 ? 2 : 4))
+fill_split_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
+                  uint64_t count, uint64_t n, uint64_t B, uint32_t nblk,
+                  unsigned char *__restrict__ out, int move, JumpMatrices J,
                   const uint32_t *__restrict__ lane_tab, const uint32_t *__restrict__ tabs,
                   const uint32_t *__restrict__ table)
 {
     constexpr int ES = Elem<DT>::size;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[64 * 144];
+    constexpr int NP = coop_pieces<DT, L>();
+    __shared__ __attribute__((aligned(16))) unsigned char lds[64 * (NP * 128 + 16)];
     const int lane = threadIdx.x;
     uint32_t m[18];
 #pragma unroll
     for (int i = 0; i < 18; ++i) m[i] = lane_tab[lane * 18 + i];
-    uint32_t s0[6];
-    load_state(planes, plane_stride, sidx, s0);
-    const XcdRange R = xcd_range(nfull + (rem ? 1 : 0));
+    const XcdRange R = xcd_range(count * nblk);
     for (uint64_t r = R.first; r < R.end; r += R.step) {
-        uint32_t w[6] = {s0[0], s0[1], s0[2], s0[3], s0[4], s0[5]};
-        jump_global(table, r * B, 0, 0, 0, 16, w);
-        wave_fill<DT, L, G, true, 64>(w, m, lds, lane, out + r * B * ES, B * ES, 1, 0,
-                                      r < nfull ? B : rem, table, tabs, false);
+        const uint64_t s = r / nblk, q = r % nblk;
+        uint32_t w[6];
+        load_state(planes, plane_stride, first + s, w);
+        uint32_t arrived = 0;
+        if (move && lane == 0) arrived = arrive(planes + ticket_of(plane_stride, first + s), nblk, w);
+        unsigned char *row = out + s * n * ES;
+        const uint64_t hv = head_values<ES>(row, n);
+        const uint64_t v0 = q ? hv + q * B : 0;
+        const uint64_t v1 = q + 1 < nblk && hv + (q + 1) * B < n ? hv + (q + 1) * B : n;
+        if (v0 < v1) {  // the last block of a row with a head may be empty
+            uint32_t b[6] = {w[0], w[1], w[2], w[3], w[4], w[5]};
+            jump_uniform(table, v0, b);
+            wave_fill<DT, L, G, true, 64, 0, NP>(b, m, lds, lane, row, 0, 1, v0, v1, table, tabs,
+                                                 false);
+        }
+        if (move && lane == 0 && last_arrival(arrived, nblk)) {
+            matvec3<C1>(J.m, w[0], w[1], w[2]);
+            matvec3<C2>(J.m + 9, w[3], w[4], w[5]);
+            store_state(planes, plane_stride, first + s, w);
+        }
     }
 }
 
@@ -411,6 +433,18 @@ static hipError_t launch_fill_g(uint32_t *planes, uint64_t plane_stride, uint64_
         else if (fl.lanes == 8 && nh == 16) MRG_COOP(8, 16);
         else return hipErrorInvalidValue;
 #undef MRG_COOP
+    } else if (fl.kernel == 2) {
+        constexpr int TV = 128 / Elem<DT>::size;
+        const dim3 grid(fl.grid), block(64);
+#define MRG_SPLIT(L)                                                                            \
+    hipLaunchKernelGGL((fill_split_kernel<DT, L, G>), grid, block, 0, st, planes, plane_stride,  \
+                       first, count, n, fl.B, fl.nblk, o, fl.move, fl.end, fl.lane_tab,       \
+                       fl.tabs, fl.table)
+        if (fl.L == TV) MRG_SPLIT(TV);
+        else if (fl.L == 2 * TV) MRG_SPLIT(2 * TV);
+        else if (fl.L == 8 * TV) MRG_SPLIT(8 * TV);
+        else return hipErrorInvalidValue;
+#undef MRG_SPLIT
     } else if (tile_bytes == 0 && ((uintptr_t)out % 128 || (n * Elem<DT>::size) % 128)) {
         // rows off their lines: one write per shared line (rows_fill_carry)
         hipLaunchKernelGGL((fill_sm_kernel<DT, 0, G>), dim3(grid_of(count, 64)), dim3(64), 0, st,
@@ -456,48 +490,28 @@ hipError_t launch_random_init(uint32_t *planes, uint64_t plane_stride, uint64_t 
     return hipGetLastError();
 }
 
-template <int DT, class G>
-static hipError_t launch_partition_g(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
-                                     const PartitionLaunch &pl, void *out, hipStream_t st)
+template <class G>
+static hipError_t launch_leap_g(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
+                                int dtype, const LeapArgs &A, unsigned grid,
+                                const uint32_t *table, unsigned char *o, hipStream_t st)
 {
-    unsigned char *o = (unsigned char *)out;
-    constexpr int TV = 128 / Elem<DT>::size;
-    if (pl.kind == 0) {
-        if (pl.L == TV)
-            hipLaunchKernelGGL((fill_split_kernel<DT, TV, G>), dim3(pl.grid), dim3(64), 0, st, planes,
-                               plane_stride, sidx, pl.nfull, pl.B, pl.rem, o, pl.lane_tab,
-                               pl.tabs, pl.table);
-        else if (pl.L == 2 * TV)
-            hipLaunchKernelGGL((fill_split_kernel<DT, 2 * TV, G>), dim3(pl.grid), dim3(64), 0, st,
-                               planes, plane_stride, sidx, pl.nfull, pl.B, pl.rem, o, pl.lane_tab,
-                               pl.tabs, pl.table);
-        else
-            return hipErrorInvalidValue;
-    } else {
-        hipLaunchKernelGGL((fill_leap_kernel<DT, G>), dim3(pl.grid), dim3(64), 0, st, planes,
-                           plane_stride, sidx, pl.leap, o, pl.table);
-    }
+    const dim3 g(grid), b(64);
+    if (dtype == 0)
+        hipLaunchKernelGGL((fill_leap_kernel<0, G>), g, b, 0, st, planes, plane_stride, sidx, A, o, table);
+    else if (dtype == 1)
+        hipLaunchKernelGGL((fill_leap_kernel<1, G>), g, b, 0, st, planes, plane_stride, sidx, A, o, table);
+    else
+        hipLaunchKernelGGL((fill_leap_kernel<2, G>), g, b, 0, st, planes, plane_stride, sidx, A, o, table);
     return hipGetLastError();
 }
 
-template <class G>
-static hipError_t launch_partition_d(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
-                                     int dtype, const PartitionLaunch &pl, void *out,
-                                     hipStream_t st)
+hipError_t launch_leap(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
+                       const LeapArgs &A, unsigned grid, const uint32_t *table, void *out,
+                       int engine, hipStream_t st)
 {
-    switch (dtype) {
-    case 0: return launch_partition_g<0, G>(planes, plane_stride, sidx, pl, out, st);
-    case 1: return launch_partition_g<1, G>(planes, plane_stride, sidx, pl, out, st);
-    default: return launch_partition_g<2, G>(planes, plane_stride, sidx, pl, out, st);
-    }
-}
-
-hipError_t launch_partition(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
-                            int dtype, const PartitionLaunch &pl, void *out, int engine,
-                            hipStream_t st)
-{
-    if (engine == 1) return launch_partition_d<GenF>(planes, plane_stride, sidx, dtype, pl, out, st);
-    return launch_partition_d<GenI>(planes, plane_stride, sidx, dtype, pl, out, st);
+    unsigned char *o = (unsigned char *)out;
+    if (engine == 1) return launch_leap_g<GenF>(planes, plane_stride, sidx, dtype, A, grid, table, o, st);
+    return launch_leap_g<GenI>(planes, plane_stride, sidx, dtype, A, grid, table, o, st);
 }
 
 }  // namespace mrg

@@ -57,6 +57,7 @@ philox_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     const uint32_t w[6] = {0u, 0u, (uint32_t)g, (uint32_t)(g >> 32), (uint32_t)key,
                            (uint32_t)(key >> 32)};
     store_state(planes, plane_stride, s, w);
+    planes[ticket_of(plane_stride, s)] = 0u;
 }
 
 __global__ void __launch_bounds__(256)

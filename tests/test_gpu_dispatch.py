@@ -55,3 +55,49 @@ ROWS = [(1, 95, 0, 0), (1, 96, 0, 0), (5, 97, 1, 3), (2048, 100, 0, 0), (2049, 1
 @pytest.mark.parametrize("count,n,dtype,off", ROWS)
 def test_rows(mg, count, n, dtype, off):
     check(mg, 3, count, n, dtype, 0, off, reps=1 if count * n > 1 << 25 else 2)
+
+
+# rows in blocks of a wave each (few streams, rows of 16 or 64 KiB and more):
+# one and several blocks, remainders in the last block and in one of their
+# own, every chunk size, states moved by the last block or by a launch after
+BLOCKS = [(1, 4096, 0, 0), (1, 4097, 0, 31), (3, 8193, 1, 1), (2, 6144, 2, 0), (2, 2049, 2, 15),
+          (1, 1 << 20, 0, 5), (1, (1 << 22) + 3, 0, 0), (1, 1 << 21, 2, 1), (1, 5 << 20, 0, 0), (40, 100001, 1, 2),
+          (256, 4100, 0, 7), (257, 4100, 0, 7), (512, 16400, 0, 9), (513, 16400, 0, 0)]
+
+
+@pytest.mark.parametrize("engine", [1, 0], ids=["f64", "int"])
+@pytest.mark.parametrize("count,n,dtype,off", BLOCKS)
+def test_rows_in_blocks(mg, count, n, dtype, off, engine):
+    old = mg.mrg_config_get("engine")
+    mg.mrg_config_set("engine", engine)
+    try:
+        check(mg, 2, count, n, dtype, 0, off)
+    finally:
+        mg.mrg_config_set("engine", old)
+
+
+def test_captured_fill_advances_each_replay(mg):
+    """A captured fill whose states move inside the fill kernel: every replay,
+    with eager work between, continues the streams."""
+    import torch
+    base = oracle.seed_from_master(5)
+    ss = mg.StreamSet(8, seed=[int(x) for x in base])
+    st = oracle.streams(base, 0, 8)
+    out = torch.empty(8 * 20001, dtype=torch.uint32, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ss.fill(20001, mg.U32, out=out)  # eager first
+        side.synchronize()
+        want, st = oracle.fill(st, 20001, oracle.U32)
+        assert np.array_equal(out.cpu().numpy(), want.reshape(-1))
+        with torch.cuda.graph(g, stream=side):
+            ss.fill(20001, mg.U32, out=out)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        want, st = oracle.fill(st, 20001, oracle.U32)
+        assert np.array_equal(out.cpu().numpy(), want.reshape(-1))
+        torch.ones(1000, device="cuda").sum().item()
+    assert np.array_equal(ss.get_states(), st)
+    ss.close()
