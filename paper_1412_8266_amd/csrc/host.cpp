@@ -404,6 +404,30 @@ void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t
     fl->move = fl->nblk * per_line <= 256;
 }
 
+// Interleaved fill in segments of each stream (fill_il_seg_kernel): as many as
+// bring the launch to two waves of lanes per SIMD (one for binary64, whose
+// stores fill the memory with half the lanes), of at least 64 steps.  A lane
+// draws 42-50 ns a step in series, so few streams take that time their steps
+// whatever they write (64 x 1000 float32 50 -> 9.5 us, 4096 x 16384 795 -> 62,
+// 32768 x 4096 206 -> 116); four waves per SIMD were slower for 1024 to 4096
+// streams (4096 x 4096 26.6 against 23.0 us, eight 33.6), segments of 32
+// steps no faster, and 65536 binary64 streams in two segments slower (x 1000
+// 98.6 -> 105 us).
+void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t count, uint64_t n, uint64_t es)
+{
+    const uint64_t lanes = (uint64_t)ctx->cus * 2048 / es;
+    uint64_t nseg = lanes / count;
+    if (nseg > n / 64) nseg = n / 64;
+    if (nseg < 2) return;
+    fl->B = ((n + nseg - 1) / nseg + 15) / 16 * 16;
+    fl->nblk = (uint32_t)((n + fl->B - 1) / fl->B);
+    if (fl->nblk < 2) return;
+    fl->kernel = 3;
+    fl->table = ctx->d_table;
+    const uint64_t e[3] = {n, 0, 0};
+    fl->end = jump_matrices(e);
+}
+
 // The fill of split_rows and, when it does not move its streams, their jump.
 hipError_t run_split(mrg_streamset ss, const mrg::FillLaunch &fl, const mrg::FillTuning &tune,
                      uint64_t first, uint64_t count, uint64_t n, mrg_dtype dtype, void *d_out,
@@ -666,6 +690,8 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
         return e == hipSuccess ? MRG_OK : hip_error(e, "tinymt fill kernel launch");
     }
     mrg::FillLaunch fl;
+    // one stream: both layouts are its values in a row
+    if (count == 1 && tune.strategy == 0) layout = MRG_STREAM_MAJOR;
     if (layout == MRG_STREAM_MAJOR) {
         // several lanes per stream (or when forced) for rows from coop_min_bytes
         // on (see below for rows under 16 KiB); lane per stream for the others
@@ -737,6 +763,11 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
                                      (hipStream_t)stream);
             return e == hipSuccess ? MRG_OK : hip_error(e, "fill kernel launch");
         }
+    }
+    if (layout == MRG_INTERLEAVED && tune.strategy == 0) {
+        DevCtx *ctx;
+        if ((st = device_ctx(ss->device, &ctx))) return st;
+        split_steps(&fl, ctx, count, n_per_stream, es);
     }
     hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n_per_stream, (int)dtype,
                                     (int)layout, d_out, fl, tune, (hipStream_t)stream);

@@ -54,7 +54,9 @@ __host__ __device__ constexpr int lane_table(int L) { return L / 16 - 1; }
 
 // How one stream-major fill is launched (chosen on the host).
 struct FillLaunch {
-    int kernel = 0;                     // 0 lane per stream, 1 wave per stream, 2 rows in blocks
+    // 0 lane per stream, 1 wave per stream, 2 rows in blocks; 3 interleaved in
+    // segments (nblk segments of B steps per stream)
+    int kernel = 0;
     int L = 0;                          // values per lane per chunk (wave per stream)
     int lanes = 64;                     // lanes per stream (wave per stream)
     const uint32_t *lane_tab = nullptr; // [64][18]: A^(l*L), component 1 then 2 (lane l % lanes)

@@ -8,7 +8,8 @@
 //                    lane, state in registers, LDS transpose to 16-byte
 //                    row-segment stores                                  (sec. 5.2, Listing 1)
 //   fill_il_kernel   bulk generation, interleaved output (lane = stream,
-//                    consecutive lanes write consecutive elements)
+//                    consecutive lanes write consecutive elements);
+//                    fill_il_seg_kernel the same in segments of each stream
 //   fill_coop_kernel bulk generation, stream-major output, GL lanes per
 //                    stream (sequence splitting inside each stream)
 //   random_init_kernel  random spacing: each stream from its own expanded
@@ -186,6 +187,55 @@ fill_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fi
         p += step;
     }
     rng.store(planes, plane_stride, first + s);
+}
+
+// Interleaved fill of fewer streams than fill the chip one lane each: each
+// stream's n steps are cut into nseg segments of S, lane t taking segment
+// t / count of stream t % count (consecutive lanes still write consecutive
+// elements), started by a jump of q * S; a stream's last segment to read its
+// state moves it by n (J = A^n; arrive()).  Without segments a lane draws its
+// whole stream in series, about 42 ns a step: 4096 x 16384 binary64 took
+// 677 us on 64 waves.
+template <int DT, class G>
+__global__ void __launch_bounds__(256)
+fill_il_seg_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
+                   uint32_t count, uint64_t n, uint32_t nseg, uint64_t S,
+                   unsigned char *__restrict__ out, JumpMatrices J,
+                   const uint32_t *__restrict__ table)
+{
+    constexpr int ES = Elem<DT>::size;
+    const uint32_t t = blockIdx.x * 256 + threadIdx.x;  // count * nseg < 2^31
+    const uint32_t q = t / count, s = t % count;
+    if (q >= nseg) return;
+    uint32_t w[6];
+    load_state(planes, plane_stride, first + s, w);
+    const uint32_t arrived = arrive(planes + ticket_of(plane_stride, first + s), nseg, w);
+    uint32_t b[6] = {w[0], w[1], w[2], w[3], w[4], w[5]};
+    const uint32_t q0 = __builtin_amdgcn_readfirstlane(q);
+    if (__all(q == q0)) jump_uniform(table, (uint64_t)q0 * S, b);
+    else jump_global(table, (uint64_t)q * S, 0, 0, 0, 16, b);
+    G g;
+    g.load(b);
+    const uint64_t k0 = (uint64_t)q * S, k1 = k0 + S < n ? k0 + S : n;
+    const uint64_t step = (uint64_t)count * ES;
+    unsigned char *p = out + k0 * step + (uint64_t)s * ES;
+    uint64_t k = k0;
+    for (; k + 4 <= k1; k += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            put1<DT>(p, g);
+            p += step;
+        }
+    }
+    for (; k < k1; ++k) {
+        put1<DT>(p, g);
+        p += step;
+    }
+    if (last_arrival(arrived, nseg)) {
+        matvec3<C1>(J.m, w[0], w[1], w[2]);
+        matvec3<C2>(J.m + 9, w[3], w[4], w[5]);
+        store_state(planes, plane_stride, first + s, w);
+    }
 }
 
 // Wave-per-stream stream-major fill: workgroups (one wave each) stride over
@@ -411,7 +461,11 @@ static hipError_t launch_fill_g(uint32_t *planes, uint64_t plane_stride, uint64_
                                 const FillLaunch &fl, int tile_bytes, hipStream_t st)
 {
     unsigned char *o = (unsigned char *)out;
-    if (layout == 1) {
+    if (layout == 1 && fl.kernel == 3) {
+        hipLaunchKernelGGL((fill_il_seg_kernel<DT, G>), dim3(grid_of(count * fl.nblk, 256)),
+                           dim3(256), 0, st, planes, plane_stride, first, (uint32_t)count, n,
+                           fl.nblk, fl.B, o, fl.end, fl.table);
+    } else if (layout == 1) {
         hipLaunchKernelGGL((fill_il_kernel<DT, G>), dim3(grid_of(count, 256)), dim3(256), 0, st,
                            planes, plane_stride, first, count, n, o);
     } else if (fl.kernel == 1) {

@@ -76,6 +76,24 @@ def test_rows_in_blocks(mg, count, n, dtype, off, engine):
         mg.mrg_config_set("engine", old)
 
 
+# interleaved in segments: lanes of one wave in two segments and in one, a
+# last segment of one step, tickets on lines of their own and packed
+STEPS = [(1, 64, 0, 0), (1, 70001, 1, 3), (3, 1000, 2, 1), (63, 127, 0, 0), (64, 129, 1, 0),
+         (100, 4097, 0, 5), (4095, 300, 2, 0), (4096, 193, 0, 0), (5000, 1000, 1, 1),
+         (32768, 129, 2, 0), (32769, 129, 2, 0), (65536, 145, 0, 0), (65537, 145, 0, 0)]
+
+
+@pytest.mark.parametrize("engine", [1, 0], ids=["f64", "int"])
+@pytest.mark.parametrize("count,n,dtype,off", STEPS)
+def test_steps_in_segments(mg, count, n, dtype, off, engine):
+    old = mg.mrg_config_get("engine")
+    mg.mrg_config_set("engine", engine)
+    try:
+        check(mg, 1, count, n, dtype, 1, off)
+    finally:
+        mg.mrg_config_set("engine", old)
+
+
 def test_captured_fill_advances_each_replay(mg):
     """A captured fill whose states move inside the fill kernel: every replay,
     with eager work between, continues the streams."""
