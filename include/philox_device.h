@@ -36,6 +36,13 @@ constexpr uint32_t kPhiloxM1 = 0xCD9E8D57u;
 constexpr uint32_t kPhiloxW0 = 0x9E3779B9u;  // Weyl key increments: 2^32 (sqrt 5 - 1) / 2,
 constexpr uint32_t kPhiloxW1 = 0xBB67AE85u;  //                       2^32 (sqrt 3 - 1)
 
+// a ^ b ^ c in one instruction (gfx950's three-input bit operation, truth table
+// 0x96), which the compiler does not form by itself.
+__device__ __forceinline__ uint32_t philox_xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // Ten rounds on the counter c under the key (k0, k1): each round multiplies
 // words 0 and 2 by the multipliers, keeps the low halves as the new words 3
 // and 1 and xors the high halves with words 1 and 3 and the round key into
@@ -46,8 +53,8 @@ __device__ __forceinline__ void philox10(uint32_t c[4], uint32_t k0, uint32_t k1
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)kPhiloxM0 * c[0];
         const uint64_t p1 = (uint64_t)kPhiloxM1 * c[2];
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
+        const uint32_t n0 = philox_xor3((uint32_t)(p1 >> 32), c[1], k0);
+        const uint32_t n2 = philox_xor3((uint32_t)(p0 >> 32), c[3], k1);
         c[1] = (uint32_t)p1;
         c[3] = (uint32_t)p0;
         c[0] = n0;

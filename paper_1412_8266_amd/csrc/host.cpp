@@ -675,11 +675,11 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
     if ((st = mrg::check_device_span(d_out, count * n_per_stream * es, ss->device, "output")))
         return st;
     if (ss->gen == mrg::kGenPhilox) {
+        DevCtx *ctx;
+        if ((st = device_ctx(ss->device, &ctx))) return st;
         hipError_t e = mrg::launch_philox_fill(ss->d_planes, ss->n, first, count, n_per_stream,
-                                               (int)dtype, (int)layout, d_out, (hipStream_t)stream);
-        if (e == hipSuccess)
-            e = mrg::launch_philox_jump(ss->d_planes, ss->n, first, count, nullptr, n_per_stream,
-                                        (hipStream_t)stream);
+                                               (int)dtype, (int)layout, ctx->cus, d_out,
+                                               (hipStream_t)stream);
         return e == hipSuccess ? MRG_OK : hip_error(e, "philox fill kernel launch");
     }
     const mrg::FillTuning tune = tuning();

@@ -97,15 +97,14 @@ hipError_t launch_leap(const uint32_t *planes, uint64_t plane_stride, uint64_t s
                        const LeapArgs &A, unsigned grid, const uint32_t *table, void *out,
                        int engine, hipStream_t st);
 
-// Philox4x32-10 stream sets (philox.hip): states (position, id, key); fills
-// leave the positions to a following launch_philox_jump.
+// Philox4x32-10 stream sets (philox.hip): states (position, id, key).
 hipError_t launch_philox_init(uint32_t *planes, uint64_t plane_stride, uint64_t count,
                               uint64_t g0, uint64_t key, hipStream_t st);
 hipError_t launch_philox_jump(uint32_t *planes, uint64_t plane_stride, uint64_t first,
                               uint64_t count, const uint64_t *d_exp, uint64_t e, hipStream_t st);
-hipError_t launch_philox_fill(const uint32_t *planes, uint64_t plane_stride, uint64_t first,
-                              uint64_t count, uint64_t n, int dtype, int layout, void *out,
-                              hipStream_t st);
+hipError_t launch_philox_fill(uint32_t *planes, uint64_t plane_stride, uint64_t first,
+                              uint64_t count, uint64_t n, int dtype, int layout, int cus,
+                              void *out, hipStream_t st);
 
 // TinyMT32 stream sets (tinymt.hip): states (s0, s1, s2, s3, q, 0), one
 // record of tmt::kRecordWords words per parameter set (sets q0, q0 + 1, ...).

@@ -119,3 +119,36 @@ def test_captured_fill_advances_each_replay(mg):
         torch.ones(1000, device="cuda").sum().item()
     assert np.array_equal(ss.get_states(), st)
     ss.close()
+
+
+# Philox: rows in LDS blocks (one block per row, rows that a workgroup cannot
+# hold whole, the longest), runs of a row (one, several, more than the tickets
+# take), segments of a stream; (streams, n, dtype, layout, offset, position)
+PHILOX = [(300, 1, 0, 0, 1, 3), (5000, 2, 1, 0, 0, 1), (1300, 255, 2, 0, 1, 2), (9000, 61, 0, 0, 3, 0),
+          (2, 511, 0, 0, 5, 1), (2, 512, 0, 0, 5, 1), (70, 2001, 1, 0, 2, 0), (3, 1 << 17, 0, 0, 0, 0),
+          (2, 70001, 2, 0, 1, 3), (1, 1 << 21, 1, 0, 7, 2), (5000, 1100, 0, 0, 0, 0),
+          (70000, 4, 0, 0, 0, 4), (3000, 1020, 0, 0, 0, 8), (3000, 508, 2, 0, 0, 2), (20000, 1030, 1, 0, 0, 1),
+          (1, 5001, 0, 1, 0, 1), (33, 4100, 2, 1, 0, 3), (5000, 700, 1, 1, 1, 0), (64, 20000, 0, 1, 0, 1)]
+
+
+@pytest.mark.parametrize("count,n,dtype,layout,off,pos", PHILOX)
+def test_philox(mg, count, n, dtype, layout, off, pos):
+    import torch
+    print("philox", count, n, dtype, layout, off, pos, flush=True)
+    with mg.StreamSet(count + 2, master_seed=17, generator="philox") as ss:
+        ss.jump_uniform(pos)
+        ss.jump_uniform(2**64 - 6, first=1, count=1)  # one row across the wrap
+        st = ss.get_states()
+        buf = torch.zeros(count * n + off + 2 * GUARD, dtype=mg.torch_dtype(dtype), device="cuda")
+        lo, hi = GUARD + off, GUARD + off + count * n
+        for rep in range(3):
+            buf.zero_()
+            if rep == 2:  # another key in one row
+                st[count // 2 + 1, 4:] = 12345, 678
+                ss.set_states(st)
+            ss.fill_ptr(n, dtype, layout, buf[lo:hi].data_ptr(), first=1, count=count)
+            h = buf.cpu().numpy()
+            want, st[1:-1] = oracle.philox_fill(st[1:-1], n, dtype, layout)
+            assert np.array_equal(h[lo:hi].view(np.uint8), want.reshape(-1).view(np.uint8)), rep
+            assert not h[:lo].view(np.uint8).any() and not h[hi:].view(np.uint8).any(), rep
+            assert np.array_equal(ss.get_states(), st)
