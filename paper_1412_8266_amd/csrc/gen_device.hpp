@@ -104,12 +104,20 @@ __device__ __forceinline__ void store16_uniform(const unsigned char *base, uint3
 }
 
 // 16-byte store at soff + voff bytes past the base of descriptor r (soff
-// wave-uniform, voff per lane).
+// wave-uniform, voff per lane).  A store of more than 8 bytes reads its data
+// registers over several cycles, and a vector instruction that overwrites one
+// of them must come two wait states later.  The compiler keeps that distance
+// except for buffer stores with a scalar offset, where it takes the hardware
+// not to need it; on gfx950 it does: with the next store's address formed in
+// the data's first register right after the store, a quarter of a wave now
+// and then stored that address instead of its value (seen in the batch kernel
+// of every dtype).  The wait states here hold the registers that long.
 template <int AUX = 0>
 __device__ __forceinline__ void store16_rsrc(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
                                              uint4 v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, voff, soff, AUX);
+    asm volatile("s_nop 1" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
 }
 
 template <int ES>
