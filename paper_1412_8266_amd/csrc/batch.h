@@ -26,8 +26,11 @@ constexpr int kBatchLaneBytes = 1024;
 // row items are too few and too uneven to fill the chip on their own (a
 // stream of up to 16 KiB per lane), and the wave items that follow them fill
 // the slots their tail leaves idle.
+// kKindMixed: the items of every dtype and form in one launch (batches too
+// small to fill the chip group by group).
 constexpr int kKindWave = 0;
 constexpr int kKindRows = 1;
+constexpr int kKindMixed = 2;
 
 // One request as the kernel sees it.  seg > 0: wave items, one per segment of
 // seg values of one stream (segs per stream), or, when a stream fits one
@@ -113,6 +116,9 @@ struct Grouped {
 };
 
 void group_requests(const std::vector<BatchReq> &in, Grouped *out);
+// All of them as one kKindMixed group: the row requests, then the wave
+// requests, each largest item first.
+void one_group(const std::vector<BatchReq> &in, Grouped *out);
 
 // A batch cut into work items on the host, before any upload: the grouped
 // descriptors, which input request each non-empty one came from, and the
@@ -126,26 +132,32 @@ struct HostPlan {
     std::vector<uint64_t> cb_prefix, cb_stream0, cb_scratch0;
     uint64_t scratch_slots = 0, samples = 0, bytes = 0;
 };
-// Work items of each request under cfg (an effective configuration).
-void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, HostPlan *out);
+// Work items of each request under cfg (an effective configuration).  With
+// `pack` a wave item holds at most that many whole streams and the batch is
+// one group.
+void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, HostPlan *out,
+                uint32_t pack = 0);
 // cfg with defaults filled in (cfg may be NULL).
 mrg_batch_config batch_config(const mrg_batch_config *cfg);
 // The checks of mrg_batch_create: dtypes, flags, outputs (device memory of
 // the set's device, inside one allocation), stream ranges, overlaps.
 mrg_status validate_batch(mrg_streamset ss, const mrg_request *reqs, uint64_t n);
 
-// Launch every group (counter reset + persistent kernel) on one stream.
+// Launch every group (one counter reset, then the persistent kernels) on one stream.
 // base carries the state planes, tables, scratch and schedule; counters holds
 // one counter per group.
 hipError_t launch_grouped(const Grouped &g, const BatchReq *d_reqs, const uint64_t *d_prefix,
                           unsigned long long *d_counters, const BatchArgs &base,
                           uint64_t grid_cap, int engine, hipStream_t st);
 
+// Zero the groups' claim counters (once before the groups of a run).
+hipError_t launch_counter_reset(unsigned long long *counters, uint32_t n, hipStream_t st);
 hipError_t launch_batch_group(const BatchArgs &A, int dtype, int kind, unsigned grid, int engine,
                               hipStream_t st);
 hipError_t launch_copyback(const BatchArgs &A, hipStream_t st);
-// Zero n completion stamps and set the start stamp to its maximum (before a run).
+// Zero n completion stamps and the groups' claim counters and set the start
+// stamp to its maximum (before a run).
 hipError_t launch_stamp_reset(unsigned long long *req_done, uint64_t n, unsigned long long *t_start,
-                              hipStream_t st);
+                              unsigned long long *counters, uint32_t n_counters, hipStream_t st);
 
 }  // namespace mrg

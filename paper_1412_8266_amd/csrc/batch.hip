@@ -5,12 +5,15 @@
 //   - a wave item is one segment [v0, v1) of one stream, written with
 //     wave_fill (lane l owns consecutive L-value pieces); the segment's first
 //     state is the stream's state jumped by v0 with the windowed tables
-//     (sequence splitting inside a stream, sec. 2.3);
+//     (sequence splitting inside a stream, sec. 2.3), v0 on a 128-byte line of
+//     the row;
 //   - a row item is up to 16 blocks of up to 64 streams of a short-stream
 //     request, one stream per lane, each block written with rows_fill_short,
 //     rows_fill_carry_w or rows_fill.
 // One launch per group (batch.h): wave items of one dtype, or the row items
-// of every dtype, largest first, followed by the wave items of one dtype.
+// of every dtype, largest first, followed by the wave items of one dtype; a
+// batch too small to fill the chip that way is one launch of finer items of
+// every dtype.
 // Persistent workgroups (one wave each) claim items from a global counter or
 // take them round robin; item i belongs to the request r with
 // prefix[r] <= i < prefix[r+1].  A request in substream mode draws its streams
@@ -28,7 +31,10 @@
 
 namespace mrg {
 
-__global__ void batch_reset_kernel(unsigned long long *counter) { *counter = 0ull; }
+__global__ void batch_reset_kernel(unsigned long long *counters, uint32_t n)
+{
+    if (threadIdx.x < n) counters[threadIdx.x] = 0ull;
+}
 
 // r with prefix[r] <= item < prefix[r+1] (prefix strictly increasing over
 // [0, nreq], item wave-uniform): a 64-way search, one probe per lane, so a
@@ -75,17 +81,28 @@ __device__ __forceinline__ void wave_item(const BatchReq &R, uint64_t local, uns
         j1 = j0 + 1;
         q = local % R.segs;
     }
-    const uint64_t v0 = q * R.seg;
-    const uint64_t v1 = v0 + R.seg < R.n ? v0 + R.seg : R.n;
     for (uint64_t j = j0; j < j1; ++j) {
         uint32_t w[6];
         load_state(A.planes, A.plane_stride, subs ? R.stream0 : R.stream0 + j, w);
-        const uint64_t sub = subs ? R.sub0 + j : 0;
-        // exponent v0 + sub * 2^76 (v0 < 2^64: no carry between the words)
-        jump_global(A.table, v0, sub << 12, sub >> 52, 0, kTableWindows, w);
-        const bool end = (R.flags & kReqWriteBack) && v1 == R.n;
-        wave_fill<DT, L, G, false, 64, 0, 2>(w, m, lds, lane, R.out + j * R.n * ES, 0, 1, v0, v1,
-                                             A.table, A.lane_tab, end);
+        unsigned char *row = R.out + j * R.n * ES;
+        // segments after the first start on the row's lines, so that all but
+        // the last are whole chunks: cut at multiples of seg, every segment of
+        // a row off its lines began with a head and ended in a cut chunk.  The
+        // last segment (which may be empty) goes to the row's end.
+        const uint64_t hv = head_values<ES>(row, R.n);
+        const uint64_t b0 = q ? hv + q * R.seg : 0, b1 = hv + (q + 1) * R.seg;
+        const uint64_t v0 = b0 < R.n ? b0 : R.n;
+        const uint64_t v1 = q + 1 < R.segs && b1 < R.n ? b1 : R.n;
+        if (subs) {
+            const uint64_t sub = R.sub0 + j;
+            // exponent v0 + sub * 2^76 (v0 < 2^64: no carry between the words)
+            jump_global(A.table, v0, sub << 12, sub >> 52, 0, kTableWindows, w);
+        } else {
+            jump_uniform(A.table, v0, w);
+        }
+        const bool end = (R.flags & kReqWriteBack) && q + 1 == R.segs;
+        wave_fill<DT, L, G, false, 64, 0, 2>(w, m, lds, lane, row, 0, 1, v0, v1, A.table, A.lane_tab,
+                                             end);
         if (end) {
             if (lane == 0) {
                 if (R.segs == 1) store_state(A.planes, A.plane_stride, R.stream0 + j, w);
@@ -93,6 +110,19 @@ __device__ __forceinline__ void wave_item(const BatchReq &R, uint64_t local, uns
             }
         }
     }
+}
+
+// wave_item with the lane's matrices loaded for it.
+template <int DT, class G>
+__device__ __forceinline__ void wave_item_tab(const BatchReq &R, uint64_t local, unsigned char *lds,
+                                              int lane, const BatchArgs &A)
+{
+    constexpr int kt = lane_table(kBatchLaneBytes / Elem<DT>::size);
+    const uint32_t *mt = A.lane_tab + (kt * 64 + lane) * 18;
+    uint32_t m[18];
+#pragma unroll
+    for (int i = 0; i < 18; ++i) m[i] = mt[i];
+    wave_item<DT, G>(R, local, lds, lane, m, A);
 }
 
 template <int DT, class G>
@@ -142,10 +172,10 @@ __global__ void __launch_bounds__(64, 2) batch_kernel(BatchArgs A)
     // wave items: the lane's A^(lane * L), L = kBatchLaneBytes of values, held
     // for the whole launch when every item is a wave item, else loaded per
     // wave item (a row item's writer needs those registers)
-    constexpr int kt = lane_table(kBatchLaneBytes / Elem<DT>::size);
-    const uint32_t *mt = A.lane_tab + (kt * 64 + lane) * 18;
     uint32_t m[18];
     if constexpr (KIND == kKindWave) {
+        constexpr int kt = lane_table(kBatchLaneBytes / Elem<DT>::size);
+        const uint32_t *mt = A.lane_tab + (kt * 64 + lane) * 18;
 #pragma unroll
         for (int i = 0; i < 18; ++i) m[i] = mt[i];
     }
@@ -173,7 +203,7 @@ __global__ void __launch_bounds__(64, 2) batch_kernel(BatchArgs A)
             r = find_req(A.prefix, A.nreq, item, lane);
             local = item - A.prefix[r];
             blk = blk_end = 0;
-            if constexpr (KIND == kKindRows) {
+            if constexpr (KIND != kKindWave) {
                 const BatchReq &Q = A.reqs[r];
                 if (is_row(Q)) {
                     const uint64_t nb = (Q.k + 63) / 64;
@@ -190,11 +220,12 @@ __global__ void __launch_bounds__(64, 2) batch_kernel(BatchArgs A)
             if (++blk < blk_end) continue;
         } else if constexpr (KIND == kKindWave) {
             wave_item<DT, G>(R, local, lds, lane, m, A);
+        } else if constexpr (KIND == kKindRows) {
+            wave_item_tab<DT, G>(R, local, lds, lane, A);
         } else {
-            uint32_t mi[18];
-#pragma unroll
-            for (int i = 0; i < 18; ++i) mi[i] = mt[i];
-            wave_item<DT, G>(R, local, lds, lane, mi, A);
+            if (R.dtype == 0) wave_item_tab<0, G>(R, local, lds, lane, A);
+            else if (R.dtype == 1) wave_item_tab<1, G>(R, local, lds, lane, A);
+            else wave_item_tab<2, G>(R, local, lds, lane, A);
         }
         // the item's end (no value returned: no round trip)
         if (A.req_done && lane == 0) atomicMax(&A.req_done[r], (unsigned long long)wall_clock64());
@@ -203,10 +234,13 @@ __global__ void __launch_bounds__(64, 2) batch_kernel(BatchArgs A)
 
 __global__ void __launch_bounds__(256) batch_stamp_reset_kernel(unsigned long long *req_done,
                                                                 uint64_t n,
-                                                                unsigned long long *t_start)
+                                                                unsigned long long *t_start,
+                                                                unsigned long long *counters,
+                                                                uint32_t n_counters)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) req_done[i] = 0ull;
+    if (i < n_counters) counters[i] = 0ull;
     if (i == 0) *t_start = ~0ull;
 }
 
@@ -242,7 +276,9 @@ template <class G>
 static void launch_group_g(const BatchArgs &A, int dtype, int kind, unsigned grid, hipStream_t st)
 {
     const dim3 g(grid), b(64);
-    if (kind == kKindWave) {
+    if (kind == kKindMixed) {
+        hipLaunchKernelGGL((batch_kernel<0, kKindMixed, G>), g, b, 0, st, A);
+    } else if (kind == kKindWave) {
         if (dtype == 0) hipLaunchKernelGGL((batch_kernel<0, kKindWave, G>), g, b, 0, st, A);
         else if (dtype == 1) hipLaunchKernelGGL((batch_kernel<1, kKindWave, G>), g, b, 0, st, A);
         else hipLaunchKernelGGL((batch_kernel<2, kKindWave, G>), g, b, 0, st, A);
@@ -253,21 +289,26 @@ static void launch_group_g(const BatchArgs &A, int dtype, int kind, unsigned gri
     }
 }
 
+hipError_t launch_counter_reset(unsigned long long *counters, uint32_t n, hipStream_t st)
+{
+    hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(64), 0, st, counters, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_batch_group(const BatchArgs &A, int dtype, int kind, unsigned grid, int engine,
                               hipStream_t st)
 {
-    if (A.dynamic) hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(1), 0, st, A.counter);
     if (engine == 1) launch_group_g<GenF>(A, dtype, kind, grid, st);
     else launch_group_g<GenI>(A, dtype, kind, grid, st);
     return hipGetLastError();
 }
 
 hipError_t launch_stamp_reset(unsigned long long *req_done, uint64_t n, unsigned long long *t_start,
-                              hipStream_t st)
+                              unsigned long long *counters, uint32_t n_counters, hipStream_t st)
 {
     const uint64_t blocks = (n + 255) / 256;
     hipLaunchKernelGGL(batch_stamp_reset_kernel, dim3((unsigned)(blocks ? blocks : 1)), dim3(256), 0,
-                       st, req_done, n, t_start);
+                       st, req_done, n, t_start, counters, n_counters);
     return hipGetLastError();
 }
 

@@ -74,7 +74,37 @@ void group_requests(const std::vector<BatchReq> &in, Grouped *out)
     }
 }
 
-void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, HostPlan *out)
+void one_group(const std::vector<BatchReq> &in, Grouped *out)
+{
+    out->reqs.clear();
+    out->prefix.assign(1, 0);
+    out->groups.clear();
+    out->pos.assign(in.size(), 0);
+    std::vector<size_t> order(in.size());
+    for (size_t i = 0; i < in.size(); ++i) order[i] = i;
+    auto item_bytes = [&](size_t i) {
+        const BatchReq &R = in[i];
+        const uint64_t es = R.dtype == 2 ? 8 : 4;
+        if (is_row(R)) return std::min<uint64_t>(R.k, 64 * (uint64_t)R.spi) * R.n * es;
+        return std::min(R.n, R.seg) * R.spi * es;
+    };
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) {
+        if (is_row(in[a]) != is_row(in[b])) return is_row(in[a]);
+        return item_bytes(a) > item_bytes(b);
+    });
+    Grouped::Group g = {0, kKindMixed, 0, (uint32_t)in.size(), 0, 0};
+    for (size_t i : order) {
+        out->pos[i] = (uint32_t)out->reqs.size();
+        out->reqs.push_back(in[i]);
+        g.items += items_of(in[i]);
+        out->prefix.push_back(g.items);
+    }
+    out->total_items = g.items;
+    if (g.items) out->groups.push_back(g);
+}
+
+void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, HostPlan *out,
+                uint32_t pack)
 {
     HostPlan &P = *out;
     P.in.clear();
@@ -103,6 +133,7 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
             R.segs = (R.n + seg - 1) / seg;
             // streams that fit one segment are packed, about a segment per item
             R.spi = R.segs == 1 ? (uint32_t)std::min<uint64_t>(seg / R.n, 1u << 20) : 1;
+            if (pack && R.spi > pack) R.spi = pack;
             if (!R.spi) R.spi = 1;
             if (R.segs > 1 && (R.flags & kReqWriteBack)) {
                 R.scratch0 = P.scratch_slots;
@@ -121,13 +152,19 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
         P.samples += R.k * R.n;
         P.bytes += R.k * R.n * es;
     }
-    group_requests(P.in, &P.plan);
+    if (pack) one_group(P.in, &P.plan);
+    else group_requests(P.in, &P.plan);
 }
 
 hipError_t launch_grouped(const Grouped &g, const BatchReq *d_reqs, const uint64_t *d_prefix,
                           unsigned long long *d_counters, const BatchArgs &base,
                           uint64_t grid_cap, int engine, hipStream_t st)
 {
+    // with completion stamps their reset has cleared the counters too
+    if (base.dynamic && !base.req_done && !g.groups.empty()) {
+        hipError_t e = launch_counter_reset(d_counters, (uint32_t)g.groups.size(), st);
+        if (e != hipSuccess) return e;
+    }
     for (size_t i = 0; i < g.groups.size(); ++i) {
         const Grouped::Group &G = g.groups[i];
         BatchArgs A = base;
@@ -161,6 +198,10 @@ struct mrg_batch_s {
     std::vector<uint32_t> req_of;    // non-empty request -> input index
     std::vector<uint64_t> cb_prefix, cb_stream0, cb_scratch0;
     uint64_t scratch_slots = 0, samples = 0, bytes = 0;
+    // items and staged states of the plan under cfg, as mrg_batch_info and
+    // mrg_batch_plan_groups state it (a small batch runs in finer items)
+    uint64_t cfg_items = 0, cfg_scratch = 0;
+    bool sizes_given = false;        // segment_bytes or wave_min_bytes asked for
     mrg::BatchReq *d_reqs = nullptr;
     uint64_t *d_prefix = nullptr;
     uint64_t *d_solo = nullptr;      // [nreq][2]: {0, items of request r}
@@ -203,6 +244,8 @@ mrg_batch_config effective(const mrg_batch_config *c)
     return e;
 }
 
+bool sizes_given(const mrg_batch_config *c) { return c && (c->segment_bytes || c->wave_min_bytes); }
+
 template <class T>
 mrg_status upload(T **dst, const std::vector<T> &src, const char *what)
 {
@@ -222,6 +265,25 @@ mrg_status build_plan(mrg_batch b)
     free_plan(b);
     mrg::HostPlan hp;
     mrg::plan_batch(b->reqs.data(), b->reqs.size(), b->cfg, &hp);
+    b->cfg_items = hp.plan.total_items;
+    b->cfg_scratch = hp.scratch_slots;
+    // A batch of under 16 GiB whose item sizes were left to the library runs
+    // as one launch of finer items: under the sizes for batches that fill the
+    // chip many times over, its three launches each ended in a few long items
+    // (64 streams of 16 KiB drawn in series, 16 short streams in one wave).
+    // With fewer streams than two waves of lanes per SIMD, rows from 2 KiB on
+    // go to whole waves too (300 requests, 0.97 GB: 866 -> 317 us, with rows
+    // under 16 KiB in lanes 434; 1000 requests of 490,000 streams, 5.6 GB:
+    // 1956 against 1426 us the other way round).
+    if (!b->sizes_given && hp.bytes < (uint64_t)16 << 30) {
+        uint64_t streams = 0;
+        for (const mrg::BatchReq &R : hp.in) streams += R.k;
+        const bool many = streams >= (uint64_t)b->tabs.cus * 512;
+        mrg_batch_config c = b->cfg;
+        c.segment_bytes = many ? 262144 : 131072;
+        c.wave_min_bytes = many ? 16384 : 2048;
+        mrg::plan_batch(b->reqs.data(), b->reqs.size(), c, &hp, many ? 4 : 2);
+    }
     b->plan = std::move(hp.plan);
     b->req_of = std::move(hp.req_of);
     b->cb_prefix = std::move(hp.cb_prefix);
@@ -283,7 +345,8 @@ mrg::BatchArgs base_args(mrg_batch b)
 hipError_t launch_all(mrg_batch b, hipStream_t st)
 {
     const mrg::BatchArgs A = base_args(b);
-    hipError_t e = mrg::launch_stamp_reset(A.req_done, b->plan.reqs.size(), A.t_start, st);
+    hipError_t e = mrg::launch_stamp_reset(A.req_done, b->plan.reqs.size(), A.t_start, b->d_counter,
+                                           (uint32_t)b->plan.groups.size(), st);
     if (e != hipSuccess) return e;
     e = mrg::launch_grouped(b->plan, b->d_reqs, b->d_prefix, b->d_counter, A,
                                        b->grid_cap, b->engine, st);
@@ -397,6 +460,7 @@ mrg_status mrg_batch_create(mrg_batch *out, mrg_streamset ss, const mrg_request 
     b->device = ss->device;
     b->reqs.assign(reqs, reqs + n_reqs);
     b->cfg = effective(cfg);
+    b->sizes_given = sizes_given(cfg);
     b->engine = mrg::current_tuning().engine;
     if ((st = mrg::device_tables(ss->device, &b->tabs))) {
         delete b;
@@ -429,6 +493,9 @@ mrg_status mrg_batch_run(mrg_batch b, void *stream)
 {
     if (!b) return set_error(MRG_EINVAL, "null batch");
     if (!b->exec) return MRG_OK;
+    // one group: two or three launches cost less than as many graph nodes
+    // (1.5 against 4.5 us each on the device)
+    if (b->plan.groups.size() == 1) return mrg_batch_run_direct(b, stream);
     hipError_t e = hipGraphLaunch(b->exec, (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "hipGraphLaunch");
 }
@@ -460,7 +527,9 @@ mrg_status mrg_batch_run_per_request(mrg_batch b, void *stream)
             A.req_done = A.t_start = nullptr;  // stamps belong to batch runs
             const unsigned grid =
                 (unsigned)std::max<uint64_t>(1, std::min(b->grid_cap, A.total_items));
-            hipError_t e = mrg::launch_batch_group(
+            hipError_t e = A.dynamic ? mrg::launch_counter_reset(A.counter, 1, (hipStream_t)stream)
+                                     : hipSuccess;
+            if (e == hipSuccess) e = mrg::launch_batch_group(
                 A, (int)R.dtype, mrg::is_row(R) ? mrg::kKindRows : mrg::kKindWave, grid, b->engine,
                 (hipStream_t)stream);
             st = e == hipSuccess ? MRG_OK : hip_error(e, "batch kernel launch");
@@ -499,11 +568,11 @@ mrg_status mrg_batch_info(mrg_batch b, mrg_batch_info_t *info)
 {
     if (!b || !info) return set_error(MRG_EINVAL, "null argument");
     info->requests = b->req_of.size();
-    info->items = b->plan.total_items;
+    info->items = b->cfg_items;
     info->samples = b->samples;
     info->bytes = b->bytes;
-    info->grid = (uint32_t)std::max<uint64_t>(1, std::min(b->grid_cap, b->plan.total_items));
-    info->scratch_states = b->scratch_slots;
+    info->grid = (uint32_t)std::max<uint64_t>(1, std::min(b->grid_cap, b->cfg_items));
+    info->scratch_states = b->cfg_scratch;
     info->config = b->cfg;
     return MRG_OK;
 }
@@ -571,9 +640,11 @@ mrg_status mrg_batch_autotune(mrg_batch b, const mrg_batch_config *cands, uint32
     uint32_t best = 0;
     float best_ms = 0;
     const mrg_batch_config keep = b->cfg;
+    const bool keep_given = b->sizes_given;
     for (uint32_t i = 0; i < n_cands && status == MRG_OK; ++i) {
         (void)hipStreamSynchronize(st);
         b->cfg = effective(&cands[i]);
+        b->sizes_given = sizes_given(&cands[i]);
         if ((status = build_plan(b)) || (status = capture(b))) break;
         if ((status = mrg_batch_run(b, stream))) break;  // warm-up
         (void)hipEventRecord(t0, st);
@@ -600,10 +671,12 @@ mrg_status mrg_batch_autotune(mrg_batch b, const mrg_batch_config *cands, uint32
     if (e != hipSuccess && status == MRG_OK) status = hip_error(e, "state restore");
     if (status == MRG_OK) {
         b->cfg = effective(&cands[best]);
+        b->sizes_given = sizes_given(&cands[best]);
         status = build_plan(b);
         if (status == MRG_OK) status = capture(b);
     } else {
         b->cfg = keep;
+        b->sizes_given = keep_given;
         if (build_plan(b) == MRG_OK) (void)capture(b);
     }
     (void)hipStreamSynchronize(st);

@@ -399,3 +399,54 @@ def test_batch_validation(mg):
     b.run()
     b.close()
     ss.close()
+
+
+# (requests, most streams, longest row): one launch of fine items, with rows
+# in lanes below 2 KiB (few streams) or 16 KiB (many), one- and several-segment
+# rows on and off their lines, empty last segments
+@pytest.mark.parametrize("requests,streams,length", [(40, 60, 3000), (25, 20, 120000),
+                                                     (60, 6000, 700), (3, 1, 131104)])
+def test_small_batch_in_one_launch(mg, requests, streams, length):
+    import torch
+    say("one launch", requests, streams, length)
+    rng = np.random.default_rng(requests)
+    base = oracle.seed_from_master(31)
+    k = rng.integers(1, streams + 1, requests)
+    n = rng.integers(1, length + 1, requests)
+    n[0], n[-1] = length, 32768 * (length // 32768) + 31 or 31
+    dt = rng.integers(0, 3, requests)
+    first = np.concatenate([[0], np.cumsum(k)[:-1]])
+    total = int(k.sum())
+    st = oracle.streams(base, 0, total)
+    ss = mg.StreamSet(total, seed=[int(x) for x in base])
+    bufs = [torch.zeros(int((k[dt == d] * n[dt == d]).sum()) + 64, dtype=mg.torch_dtype(d), device="cuda")
+            for d in range(3)]
+    rows, at, place = [], [5, 0, 3], []
+    for i in range(requests):
+        d = int(dt[i])
+        place.append(at[d])
+        rows.append((int(first[i]), int(k[i]), int(n[i]), 0,
+                     bufs[d].data_ptr() + at[d] * bufs[d].element_size(), d, 0))
+        at[d] += int(k[i] * n[i])
+    with mg.Batch(ss, rows) as b:
+        assert b.info()["items"] == sum(mg.batch_plan_groups(rows)[2])
+        for rep in range(3):
+            for t in bufs:
+                t.zero_()
+            if rep < 2:
+                b.run()
+            else:
+                b.run_direct()
+            got = [t.cpu().numpy() for t in bufs]
+            for i in range(requests):
+                d = int(dt[i])
+                s = slice(int(first[i]), int(first[i] + k[i]))
+                want, st[s] = oracle.fill(st[s], int(n[i]), d)
+                have = got[d][place[i]:place[i] + int(k[i] * n[i])]
+                assert np.array_equal(have.view(np.uint8), want.reshape(-1).view(np.uint8)), (rep, i)
+            for d in range(3):
+                assert not got[d][:(5, 0, 3)[d]].view(np.uint8).any() and not got[d][at[d]:].view(np.uint8).any()
+            assert np.array_equal(ss.get_states(), st)
+            times = b.request_times()
+            assert (times > 0).all()
+    ss.close()
