@@ -26,61 +26,80 @@
 
 namespace mrg {
 
-// Stage windows [w_lo, w_hi) of both components into LDS, then apply them.
+// One component (blockIdx.y) of 256 streams per workgroup, a stream per lane:
+// half the serial chain and twice the waves of a lane with both.  The windows
+// [w_lo, the highest one that any exponent of the workgroup reaches) are
+// staged in LDS with all of a thread's loads in flight, then applied; a matrix
+// is 9 words, so lanes on different digits read different banks.  What bounds
+// it is the chain of products.  Staging all 48 windows of both components a
+// word at a time took most of 19 us for 65536 streams with 77-bit exponents.
 __global__ void __launch_bounds__(256)
 jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
             uint64_t count, const uint64_t *__restrict__ exps, uint64_t g0,
             InitSeed seed, const uint32_t *__restrict__ table, int w_lo, int w_hi)
 {
-    extern __shared__ uint32_t tab[];
-    const int nw = (w_hi - w_lo) * kTableWindowWords;  // words per component
-    for (int i = threadIdx.x; i < nw; i += blockDim.x) {
-        tab[i] = table[(0 * kTableWindows + w_lo) * kTableWindowWords + i];
-        tab[nw + i] = table[(1 * kTableWindows + w_lo) * kTableWindowWords + i];
-    }
-    __syncthreads();
-
+    extern __shared__ __attribute__((aligned(16))) uint32_t tab[];
+    __shared__ int top_all;
+    const int c = blockIdx.y;
     const uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = s < count;
-    uint32_t a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
-    uint64_t e0 = 0, e1 = 0, e2 = 0;
     const uint64_t idx = first + s;
+    uint32_t *pl = planes + 3 * c * plane_stride;
+    uint32_t a0 = 0, a1 = 0, a2 = 0;
+    uint64_t e0 = 0, e1 = 0, e2 = 0;
+    if (threadIdx.x == 0) top_all = w_lo;
     if (active) {
         if (exps) {  // jump the current state by its own exponent
-            a0 = planes[0 * plane_stride + idx];
-            a1 = planes[1 * plane_stride + idx];
-            a2 = planes[2 * plane_stride + idx];
-            b0 = planes[3 * plane_stride + idx];
-            b1 = planes[4 * plane_stride + idx];
-            b2 = planes[5 * plane_stride + idx];
+            a0 = pl[0 * plane_stride + idx];
+            a1 = pl[1 * plane_stride + idx];
+            a2 = pl[2 * plane_stride + idx];
             e0 = exps[3 * s + 0];
             e1 = exps[3 * s + 1];
             e2 = exps[3 * s + 2];
         } else {     // create: start of global stream g = g0 + s is A^(g 2^127) seed
-            a0 = seed.w[0]; a1 = seed.w[1]; a2 = seed.w[2];
-            b0 = seed.w[3]; b1 = seed.w[4]; b2 = seed.w[5];
+            a0 = seed.w[3 * c]; a1 = seed.w[3 * c + 1]; a2 = seed.w[3 * c + 2];
             const uint64_t g = g0 + s;
             e0 = 0;
             e1 = (g & 1u) << 63;
             e2 = g >> 1;
         }
     }
-    for (int w = w_lo; w < w_hi; ++w) {
+    int top = top_window(e0, e1, e2);
+#pragma unroll
+    for (int d = 32; d; d >>= 1) {
+        const int o = __shfl_xor(top, d);
+        top = o > top ? o : top;
+    }
+    __syncthreads();
+    if (threadIdx.x % 64 == 0) atomicMax(&top_all, top);
+    __syncthreads();
+    const int end = top_all < w_hi ? top_all : w_hi;
+    {
+        // 36 units of 16 bytes per window, up to 1728 in all
+        constexpr int kUnits = kTableWindowWords / 4, kPer = (kTableWindows * kUnits + 255) / 256;
+        const uint4 *src = (const uint4 *)(table + (c * kTableWindows + w_lo) * kTableWindowWords);
+        const int units = (end - w_lo) * kUnits;
+        uint4 v[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (k * 256 + (int)threadIdx.x < units) v[k] = src[k * 256 + threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (k * 256 + (int)threadIdx.x < units) ((uint4 *)tab)[k * 256 + threadIdx.x] = v[k];
+    }
+    __syncthreads();
+    for (int w = w_lo; w < end; ++w) {
         const uint32_t d = exp_digit(e0, e1, e2, w);
         if (!__any(d != 0u)) continue;  // wave-uniform skip of empty windows
-        const uint32_t *T1 = tab + ((w - w_lo) * 16 + d) * 9;
-        const uint32_t *T2 = tab + nw + ((w - w_lo) * 16 + d) * 9;
-        matvec3<C1>(T1, a0, a1, a2);
-        matvec3<C2>(T2, b0, b1, b2);
+        const uint32_t *T = tab + ((w - w_lo) * 16 + d) * 9;
+        if (c == 0) matvec3<C1>(T, a0, a1, a2);
+        else matvec3<C2>(T, a0, a1, a2);
     }
     if (active) {
-        planes[0 * plane_stride + idx] = canon1(a0);
-        planes[1 * plane_stride + idx] = canon1(a1);
-        planes[2 * plane_stride + idx] = canon1(a2);
-        planes[3 * plane_stride + idx] = canon2(b0);
-        planes[4 * plane_stride + idx] = canon2(b1);
-        planes[5 * plane_stride + idx] = canon2(b2);
-        if (!exps) planes[ticket_of(plane_stride, idx)] = 0u;
+        pl[0 * plane_stride + idx] = c == 0 ? canon1(a0) : canon2(a0);
+        pl[1 * plane_stride + idx] = c == 0 ? canon1(a1) : canon2(a1);
+        pl[2 * plane_stride + idx] = c == 0 ? canon1(a2) : canon2(a2);
+        if (!exps && c == 0) planes[ticket_of(plane_stride, idx)] = 0u;
     }
 }
 
@@ -428,8 +447,8 @@ hipError_t launch_init(uint32_t *planes, uint64_t plane_stride, uint64_t count,
                        uint64_t g0, const InitSeed &seed, const uint32_t *table,
                        int w_lo, int w_hi, hipStream_t st)
 {
-    const size_t lds = (size_t)2 * (w_hi - w_lo) * kTableWindowWords * sizeof(uint32_t);
-    hipLaunchKernelGGL(jump_kernel, dim3(grid_of(count, 256)), dim3(256), lds, st, planes,
+    const size_t lds = (size_t)(w_hi - w_lo) * kTableWindowWords * sizeof(uint32_t);
+    hipLaunchKernelGGL(jump_kernel, dim3(grid_of(count, 256), 2), dim3(256), lds, st, planes,
                        plane_stride, (uint64_t)0, count, (const uint64_t *)nullptr, g0, seed,
                        table, w_lo, w_hi);
     return hipGetLastError();
@@ -440,9 +459,9 @@ hipError_t launch_jump(uint32_t *planes, uint64_t plane_stride, uint64_t first,
                        hipStream_t st)
 {
     const int w_lo = 0, w_hi = kTableWindows;
-    const size_t lds = (size_t)2 * (w_hi - w_lo) * kTableWindowWords * sizeof(uint32_t);
+    const size_t lds = (size_t)(w_hi - w_lo) * kTableWindowWords * sizeof(uint32_t);
     InitSeed none = {};
-    hipLaunchKernelGGL(jump_kernel, dim3(grid_of(count, 256)), dim3(256), lds, st, planes,
+    hipLaunchKernelGGL(jump_kernel, dim3(grid_of(count, 256), 2), dim3(256), lds, st, planes,
                        plane_stride, first, count, d_exp, (uint64_t)0, none, table, w_lo, w_hi);
     return hipGetLastError();
 }
