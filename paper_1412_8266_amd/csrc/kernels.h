@@ -90,11 +90,13 @@ struct LeapArgs {
     int KB = 64, R = 1;
     JumpMatrices J63 = {};   // A^(63*P): to the next column block (R = 1)
     JumpMatrices Jseg = {};  // A^(T - Ts): to the next segment (R > 1)
+    JumpMatrices end = {};   // A^(P*K): the stream's state after the deal
 };
 
+
 // One stream (plane index sidx) dealt to players, each player's cards in a row.
-hipError_t launch_leap(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
-                       const LeapArgs &A, unsigned grid, const uint32_t *table, void *out,
+hipError_t launch_leap(uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
+                       const LeapArgs &A, unsigned waves, const uint32_t *table, void *out,
                        int engine, hipStream_t st);
 
 // Philox4x32-10 stream sets (philox.hip): states (position, id, key).

@@ -363,33 +363,52 @@ fill_split_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t
 // r = l / KB of each segment of T = R*Ts players, i.e. the stream's outputs
 // [k*P + t0 + r*Ts, ... + Ts) in order, written down its column: a store
 // instruction covers R runs of KB adjacent cards (64 adjacent cards when
-// K >= 64).  Work items are (column block kb, segment); each workgroup takes
-// a contiguous run of the nkb * nseg items, jumps its lanes once (A^(k*P +
+// K >= 64).  Work items are (column block kb, segment); each wave takes a
+// contiguous run of the nkb * nseg items, jumps its lanes once (A^(k*P +
 // t0 + r*Ts)) and from then on only continues: to the next segment by
 // A^(T - Ts) (Jseg; stepping on when R = 1), to the next column block by
 // A^(63*P) (J63; only with R = 1, since K < 64 leaves one column block).  The
-// stream state is not advanced here.
+// waves of a workgroup (up to 16, for at most 256 workgroups) arrive together
+// at the stream's ticket: 4096 arrivals one by one would queue for 80 us.  The
+// last workgroup to read the state moves it by P*K.
 template <int DT, class G>
-__global__ void __launch_bounds__(64)
-fill_leap_kernel(const uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t sidx,
+__global__ void __launch_bounds__(1024)
+fill_leap_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t sidx,
                  LeapArgs A, unsigned char *__restrict__ out, const uint32_t *__restrict__ table)
 {
     constexpr int ES = Elem<DT>::size;
-    const uint64_t lane = threadIdx.x;
-    const uint64_t nb = gridDim.x, b = blockIdx.x;
+    const uint64_t lane = threadIdx.x % 64;
+    uint32_t w[6];
+    load_state(planes, plane_stride, sidx, w);
+    // this wave's state words are in registers, then the workgroup's
+    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5])::"memory");
+    __syncthreads();
+    if (threadIdx.x == 0 &&
+        last_arrival(arrive(planes + ticket_of(plane_stride, sidx), gridDim.x, w), gridDim.x)) {
+        uint32_t e[6] = {w[0], w[1], w[2], w[3], w[4], w[5]};
+        matvec3<C1>(A.end.m, e[0], e[1], e[2]);
+        matvec3<C2>(A.end.m + 9, e[3], e[4], e[5]);
+        store_state(planes, plane_stride, sidx, e);
+    }
+    const uint64_t nb = (uint64_t)gridDim.x * (blockDim.x / 64);
+    const uint64_t b = (uint64_t)blockIdx.x * (blockDim.x / 64) +
+                       (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint64_t q = A.items / nb, rr = A.items % nb;
     const uint64_t i0 = b * q + (b < rr ? b : rr);
     const uint64_t i1 = i0 + q + (b < rr ? 1 : 0);
     if (i0 >= i1 || lane >= (uint64_t)A.R * A.KB) return;
     const uint64_t kl = lane % A.KB, r = lane / A.KB;
     uint64_t kb = i0 / A.nseg, seg = i0 % A.nseg;
-    uint32_t w[6];
-    load_state(planes, plane_stride, sidx, w);
     {
         // lanes past the last column start anywhere in range and write nothing
         const uint64_t k = kb * A.KB + kl < A.K ? kb * A.KB + kl : A.K - 1;
-        const uint64_t t = seg * A.T + r * A.Ts < A.P ? seg * A.T + r * A.Ts : A.P - 1;
-        jump_global(table, k * A.P + t, 0, 0, 0, 16, w);
+        if (A.R == 1) {  // the same segment start in every lane
+            jump_uniform(table, seg * A.T, w);
+            jump_global(table, k * A.P, 0, 0, 0, 16, w);
+        } else {
+            const uint64_t t = seg * A.T + r * A.Ts < A.P ? seg * A.T + r * A.Ts : A.P - 1;
+            jump_global(table, k * A.P + t, 0, 0, 0, 16, w);
+        }
     }
     G g;
     g.load(w);
@@ -564,11 +583,12 @@ hipError_t launch_random_init(uint32_t *planes, uint64_t plane_stride, uint64_t 
 }
 
 template <class G>
-static hipError_t launch_leap_g(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
-                                int dtype, const LeapArgs &A, unsigned grid,
+static hipError_t launch_leap_g(uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
+                                int dtype, const LeapArgs &A, unsigned waves,
                                 const uint32_t *table, unsigned char *o, hipStream_t st)
 {
-    const dim3 g(grid), b(64);
+    const unsigned per = waves <= 256 ? 1 : waves >= 4096 ? 16 : (waves + 255) / 256;
+    const dim3 g((waves + per - 1) / per), b(per * 64);
     if (dtype == 0)
         hipLaunchKernelGGL((fill_leap_kernel<0, G>), g, b, 0, st, planes, plane_stride, sidx, A, o, table);
     else if (dtype == 1)
@@ -578,13 +598,13 @@ static hipError_t launch_leap_g(const uint32_t *planes, uint64_t plane_stride, u
     return hipGetLastError();
 }
 
-hipError_t launch_leap(const uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
-                       const LeapArgs &A, unsigned grid, const uint32_t *table, void *out,
+hipError_t launch_leap(uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
+                       const LeapArgs &A, unsigned waves, const uint32_t *table, void *out,
                        int engine, hipStream_t st)
 {
     unsigned char *o = (unsigned char *)out;
-    if (engine == 1) return launch_leap_g<GenF>(planes, plane_stride, sidx, dtype, A, grid, table, o, st);
-    return launch_leap_g<GenI>(planes, plane_stride, sidx, dtype, A, grid, table, o, st);
+    if (engine == 1) return launch_leap_g<GenF>(planes, plane_stride, sidx, dtype, A, waves, table, o, st);
+    return launch_leap_g<GenI>(planes, plane_stride, sidx, dtype, A, waves, table, o, st);
 }
 
 }  // namespace mrg
