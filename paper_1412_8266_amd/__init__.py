@@ -27,14 +27,26 @@ M2 = 4294944443
 _ESIZE = {U32: 4, F32: 4, F64: 8}
 
 
+# torch and its types, looked up once: a call of a few streams is as long as
+# its host work
+_cached_torch = None
+_torch_dtypes = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _cached_torch
+    if _cached_torch is None:
+        import torch
+        _cached_torch = torch
+    return _cached_torch
 
 
 def torch_dtype(dtype: int):
-    torch = _torch()
-    return {U32: torch.uint32, F32: torch.float32, F64: torch.float64}[dtype]
+    global _torch_dtypes
+    if _torch_dtypes is None:
+        torch = _torch()
+        _torch_dtypes = {U32: torch.uint32, F32: torch.float32, F64: torch.float64}
+    return _torch_dtypes[dtype]
 
 
 def check_tensor(t, device: int, elems: int, esize: int, what: str = "output") -> None:
@@ -53,9 +65,12 @@ def check_tensor(t, device: int, elems: int, esize: int, what: str = "output") -
 
 
 def _stream_handle(stream) -> int:
-    torch = _torch()
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        torch = _torch()
+        if not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        # the same handle without a Stream object around it (2.7 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -108,6 +123,7 @@ class StreamSet:
         self.n_streams = int(n_streams)
         self.first_stream = int(first_stream)
         self.device = _torch().cuda.current_device()  # the set's states live here
+        self._torch_device = _torch().device("cuda", self.device)
 
     # -- lifetime -----------------------------------------------------------
     def close(self) -> None:
@@ -166,7 +182,7 @@ class StreamSet:
         first, count = self._range(first, count)
         shape = (count, n) if layout == STREAM_MAJOR else (n, count)
         if out is None:
-            out = torch.empty(shape, dtype=torch_dtype(dtype), device="cuda:%d" % self.device)
+            out = torch.empty(shape, dtype=torch_dtype(dtype), device=self._torch_device)
         else:
             check_tensor(out, self.device, count * n, _ESIZE[dtype])
         _abi.mrg_fill(self._h, first, count, n, dtype, layout,
@@ -187,7 +203,7 @@ class StreamSet:
         torch = _torch()
         shape = (players, per_player) if layout == STREAM_MAJOR else (per_player, players)
         if out is None:
-            out = torch.empty(shape, dtype=torch_dtype(dtype), device="cuda:%d" % self.device)
+            out = torch.empty(shape, dtype=torch_dtype(dtype), device=self._torch_device)
         else:
             check_tensor(out, self.device, players * per_player, _ESIZE[dtype])
         _abi.mrg_fill_leapfrog(self._h, s, players, per_player, dtype, layout,
