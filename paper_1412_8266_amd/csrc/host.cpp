@@ -747,6 +747,15 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
                 count >= (uint64_t)ctx->cus * 256)
                 fl = mrg::FillLaunch();
         }
+        // lane per stream, rows of whole 4 KiB on lines: two lanes per stream
+        // (fill_sm_kernel's HALVES; other row lengths lose by it: 131072 x 1536
+        // float32 171 -> 189 us, x 512 59 -> 62)
+        if (tune.strategy == 0 && fl.kernel == 0 && tune.tile_bytes == 0 &&
+            (uintptr_t)d_out % 128 == 0 && n_per_stream * es % 4096 == 0) {
+            fl.kernel = 4;
+            const uint64_t e[3] = {n_per_stream / 2, 0, 0};
+            fl.end = jump_matrices(e);
+        }
         // few streams: a wave per stream leaves the chip idle and takes 2.3 us
         // per 4096 uint32 of a row whatever the launch writes, so rows are cut
         // into blocks (256 x 16384 uint32 15.1 -> 11.2 us, 64 x 2^20 590 -> 49).

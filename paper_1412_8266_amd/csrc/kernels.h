@@ -55,7 +55,8 @@ __host__ __device__ constexpr int lane_table(int L) { return L / 16 - 1; }
 // How one stream-major fill is launched (chosen on the host).
 struct FillLaunch {
     // 0 lane per stream, 1 wave per stream, 2 rows in blocks; 3 interleaved in
-    // segments (nblk segments of B steps per stream)
+    // segments (nblk segments of B steps per stream); 4 two lanes per stream
+    // (end = A^(n/2))
     int kernel = 0;
     int L = 0;                          // values per lane per chunk (wave per stream)
     int lanes = 64;                     // lanes per stream (wave per stream)

@@ -145,22 +145,35 @@ random_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
 // ---------------------------------------------------------------------------
 // Lane-per-stream stream-major fill: one wave per 64 streams, each lane
 // generating its stream's n values through the LDS tile writer rows_fill.
-template <int DT, int TB, class G>
+// HALVES: every stream is two lanes, the odd one drawing the second half of
+// its row from J = A^(n/2) on (n even; rows and halves on 128-byte lines), so
+// the wave's rows are 64 halves.  For rows of whole 4 KiB: a step of the
+// wave then writes tiles 2 KiB apart instead of 4, which memory takes at 4.5
+// instead of 3.4 TB/s (65536 x 1024 float32, buffers in turn: 80 -> 59 us).
+template <int DT, int TB, class G, bool HALVES = false>
 __global__ void __launch_bounds__(64)
 fill_sm_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
-               uint64_t count, uint64_t n, unsigned char *__restrict__ out)
+               uint64_t count, uint64_t n, unsigned char *__restrict__ out, JumpMatrices J)
 {
     constexpr int ES = Elem<DT>::size;
     // TB = 0: rows off their lines, written by rows_fill_carry in 128-byte windows
     __shared__ __attribute__((aligned(16))) unsigned char lds[64 * (TB ? TB + 16 : 128 + 160)];
     const int lane = threadIdx.x;
+    const uint64_t rows = HALVES ? 2 * count : count;
+    const uint64_t rn = HALVES ? n / 2 : n;  // values per row of the wave
     const uint64_t s0 = (uint64_t)blockIdx.x * 64;
-    const uint64_t nrows = count - s0 < 64 ? count - s0 : 64;
+    const uint64_t nrows = rows - s0 < 64 ? rows - s0 : 64;
     const bool active = (uint64_t)lane < nrows;
-    const uint64_t idx = first + s0 + lane;
+    const uint64_t idx = first + (HALVES ? (s0 + lane) / 2 : s0 + lane);
 
     uint32_t w[6] = {1u, 1u, 1u, 1u, 1u, 1u};
     if (active) load_state(planes, plane_stride, idx, w);
+    if constexpr (HALVES) {
+        if (lane & 1) {
+            matvec3<C1>(J.m, w[0], w[1], w[2]);
+            matvec3<C2>(J.m + 9, w[3], w[4], w[5]);
+        }
+    }
     G g;
     g.load(w);
     if (n * ES < 128) {  // the wave's rows are one block shorter than 64 lines
@@ -169,9 +182,10 @@ fill_sm_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fi
         if constexpr (TB == 0)
             rows_fill_carry<DT, 128, G>(g, lds, lane, nrows, out + s0 * n * ES, n);
         else
-            rows_fill<DT, TB, G>(g, lds, lane, nrows, out + s0 * n * ES, n * ES, n);
+            rows_fill<DT, TB, G>(g, lds, lane, nrows, out + s0 * rn * ES, rn * ES, rn);
     }
-    if (active) {
+    // the second half ends where the stream goes on (both lanes have read it)
+    if (active && (!HALVES || (lane & 1))) {
         g.store(w);
         store_state(planes, plane_stride, idx, w);
     }
@@ -537,16 +551,19 @@ static hipError_t launch_fill_g(uint32_t *planes, uint64_t plane_stride, uint64_
         else if (fl.L == 8 * TV) MRG_SPLIT(8 * TV);
         else return hipErrorInvalidValue;
 #undef MRG_SPLIT
+    } else if (fl.kernel == 4) {
+        hipLaunchKernelGGL((fill_sm_kernel<DT, 256, G, true>), dim3(grid_of(2 * count, 64)), dim3(64),
+                           0, st, planes, plane_stride, first, count, n, o, fl.end);
     } else if (tile_bytes == 0 && ((uintptr_t)out % 128 || (n * Elem<DT>::size) % 128)) {
         // rows off their lines: one write per shared line (rows_fill_carry)
         hipLaunchKernelGGL((fill_sm_kernel<DT, 0, G>), dim3(grid_of(count, 64)), dim3(64), 0, st,
-                           planes, plane_stride, first, count, n, o);
+                           planes, plane_stride, first, count, n, o, fl.end);
     } else if (tile_bytes == 256 || (tile_bytes == 0 && n * Elem<DT>::size >= 1024)) {
         hipLaunchKernelGGL((fill_sm_kernel<DT, 256, G>), dim3(grid_of(count, 64)), dim3(64), 0, st,
-                           planes, plane_stride, first, count, n, o);
+                           planes, plane_stride, first, count, n, o, fl.end);
     } else {
         hipLaunchKernelGGL((fill_sm_kernel<DT, 128, G>), dim3(grid_of(count, 64)), dim3(64), 0, st,
-                           planes, plane_stride, first, count, n, o);
+                           planes, plane_stride, first, count, n, o, fl.end);
     }
     return hipGetLastError();
 }

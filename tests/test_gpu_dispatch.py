@@ -51,6 +51,9 @@ ROWS = [(1, 95, 0, 0), (1, 96, 0, 0), (5, 97, 1, 3), (2048, 100, 0, 0), (2049, 1
         (16384, 255, 0, 1), (20000, 330, 0, 0), (32768, 257, 2, 0), (32769, 600, 0, 0),
         (65535, 600, 1, 0), (65536, 2050, 0, 0)]
 
+# two lanes per stream (rows of 4 KiB on lines): whole and partial last waves
+ROWS += [(65536, 1024, 0, 0), (65553, 1024, 1, 0), (65569, 512, 2, 0), (65600, 1024, 0, 32)]
+
 
 @pytest.mark.parametrize("count,n,dtype,off", ROWS)
 def test_rows(mg, count, n, dtype, off):
