@@ -335,11 +335,11 @@ typedef struct {
 
 typedef struct {
     uint64_t requests;        /* non-empty requests */
-    uint64_t items;           /* work items */
+    uint64_t items;           /* work items of the plan under config */
     uint64_t samples;         /* outputs per run */
     uint64_t bytes;           /* output bytes per run */
-    uint64_t scratch_states;  /* end states staged before copy-back */
-    uint32_t grid;            /* persistent workgroups */
+    uint64_t scratch_states;  /* end states that plan stages before copy-back */
+    uint32_t grid;            /* its persistent workgroups */
     uint32_t pad;
     mrg_batch_config config;  /* effective configuration */
 } mrg_batch_info_t;
@@ -354,8 +354,11 @@ typedef struct mrg_batch_s *mrg_batch;
  * wave_min_bytes, one per lane), group them into at most one launch per
  * dtype of the long streams' items, the first (least output) led by the
  * short streams' items of every dtype, largest first, and capture one
- * hipGraph (per group a counter reset and a persistent kernel, then the
- * copy-back of end states).  Every non-empty request's d_out must be device
+ * hipGraph (one reset of stamps and counters, a persistent kernel per group,
+ * then the copy-back of end states).  A batch of under 16 GiB of output whose
+ * segment_bytes and wave_min_bytes are left to their defaults runs the same
+ * requests as one group of finer items of every dtype (the plan that
+ * mrg_batch_info and mrg_batch_plan_groups state is the one under cfg).  Every non-empty request's d_out must be device
  * memory of the set's device holding its output inside one allocation (else
  * MRG_EINVAL / MRG_ERANGE naming the request).  reqs is copied; cfg may be
  * NULL.  The plan refers to ss and to the output buffers, which must outlive
@@ -387,8 +390,8 @@ typedef struct {
     uint64_t bytes;        /* output bytes of the group's requests */
 } mrg_plan_group;
 
-/* The launch groups that mrg_batch_create would capture for these requests
- * under cfg (NULL: defaults), computed on the host alone: no stream set,
+/* The launch groups of these requests under cfg (NULL: defaults; what a batch
+ * of 16 GiB or more, or one with sizes in cfg, captures), computed on the host alone: no stream set,
  * device or output memory is touched, d_out is not read, and the requests
  * are not validated against a stream set (dtype and flags are checked).
  * groups receives up to 3 groups in launch order (*n_groups of them); when

@@ -493,9 +493,6 @@ mrg_status mrg_batch_run(mrg_batch b, void *stream)
 {
     if (!b) return set_error(MRG_EINVAL, "null batch");
     if (!b->exec) return MRG_OK;
-    // one group: two or three launches cost less than as many graph nodes
-    // (1.5 against 4.5 us each on the device)
-    if (b->plan.groups.size() == 1) return mrg_batch_run_direct(b, stream);
     hipError_t e = hipGraphLaunch(b->exec, (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "hipGraphLaunch");
 }
