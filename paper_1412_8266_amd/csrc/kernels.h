@@ -94,7 +94,6 @@ struct LeapArgs {
     JumpMatrices end = {};   // A^(P*K): the stream's state after the deal
 };
 
-
 // One stream (plane index sidx) dealt to players, each player's cards in a row.
 hipError_t launch_leap(uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
                        const LeapArgs &A, unsigned waves, const uint32_t *table, void *out,
