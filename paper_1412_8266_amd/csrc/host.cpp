@@ -426,6 +426,7 @@ void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t count, uint64_
     fl->table = ctx->d_table;
     const uint64_t e[3] = {n, 0, 0};
     fl->end = jump_matrices(e);
+    fl->move = fl->nblk <= 256;  // arrivals at a stream's ticket (as in split_rows)
 }
 
 // The fill of split_rows and, when it does not move its streams, their jump.
@@ -780,6 +781,8 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
     }
     hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n_per_stream, (int)dtype,
                                     (int)layout, d_out, fl, tune, (hipStream_t)stream);
+    if (e == hipSuccess && fl.kernel == 3 && !fl.move)
+        e = mrg::launch_jump_uniform(ss->d_planes, ss->n, first, count, fl.end, (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "fill kernel launch");
 }
 

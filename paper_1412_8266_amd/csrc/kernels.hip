@@ -225,15 +225,15 @@ fill_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fi
 // Interleaved fill of fewer streams than fill the chip one lane each: each
 // stream's n steps are cut into nseg segments of S, lane t taking segment
 // t / count of stream t % count (consecutive lanes still write consecutive
-// elements), started by a jump of q * S; a stream's last segment to read its
-// state moves it by n (J = A^n; arrive()).  Without segments a lane draws its
+// elements), started by a jump of q * S; with `move` a stream's last segment to read
+// its state moves it by n (J = A^n; arrive()).  Without segments a lane draws its
 // whole stream in series, about 42 ns a step: 4096 x 16384 binary64 took
 // 677 us on 64 waves.
 template <int DT, class G>
 __global__ void __launch_bounds__(256)
 fill_il_seg_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
                    uint32_t count, uint64_t n, uint32_t nseg, uint64_t S,
-                   unsigned char *__restrict__ out, JumpMatrices J,
+                   unsigned char *__restrict__ out, int move, JumpMatrices J,
                    const uint32_t *__restrict__ table)
 {
     constexpr int ES = Elem<DT>::size;
@@ -242,7 +242,8 @@ fill_il_seg_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     if (q >= nseg) return;
     uint32_t w[6];
     load_state(planes, plane_stride, first + s, w);
-    const uint32_t arrived = arrive(planes + ticket_of(plane_stride, first + s), nseg, w);
+    uint32_t arrived = 0;
+    if (move) arrived = arrive(planes + ticket_of(plane_stride, first + s), nseg, w);
     uint32_t b[6] = {w[0], w[1], w[2], w[3], w[4], w[5]};
     const uint32_t q0 = __builtin_amdgcn_readfirstlane(q);
     if (__all(q == q0)) jump_uniform(table, (uint64_t)q0 * S, b);
@@ -264,7 +265,7 @@ fill_il_seg_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
         put1<DT>(p, g);
         p += step;
     }
-    if (last_arrival(arrived, nseg)) {
+    if (move && last_arrival(arrived, nseg)) {
         matvec3<C1>(J.m, w[0], w[1], w[2]);
         matvec3<C2>(J.m + 9, w[3], w[4], w[5]);
         store_state(planes, plane_stride, first + s, w);
@@ -516,7 +517,7 @@ static hipError_t launch_fill_g(uint32_t *planes, uint64_t plane_stride, uint64_
     if (layout == 1 && fl.kernel == 3) {
         hipLaunchKernelGGL((fill_il_seg_kernel<DT, G>), dim3(grid_of(count * fl.nblk, 256)),
                            dim3(256), 0, st, planes, plane_stride, first, (uint32_t)count, n,
-                           fl.nblk, fl.B, o, fl.end, fl.table);
+                           fl.nblk, fl.B, o, fl.move, fl.end, fl.table);
     } else if (layout == 1) {
         hipLaunchKernelGGL((fill_il_kernel<DT, G>), dim3(grid_of(count, 256)), dim3(256), 0, st,
                            planes, plane_stride, first, count, n, o);

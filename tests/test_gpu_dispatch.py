@@ -81,7 +81,7 @@ def test_rows_in_blocks(mg, count, n, dtype, off, engine):
 
 # interleaved in segments: lanes of one wave in two segments and in one, a
 # last segment of one step, tickets on lines of their own and packed
-STEPS = [(1, 64, 0, 0), (1, 70001, 1, 3), (3, 1000, 2, 1), (63, 127, 0, 0), (64, 129, 1, 0),
+STEPS = [(2, 40000, 0, 1), (70, 20000, 2, 0), (1, 64, 0, 0), (1, 70001, 1, 3), (3, 1000, 2, 1), (63, 127, 0, 0), (64, 129, 1, 0),
          (100, 4097, 0, 5), (4095, 300, 2, 0), (4096, 193, 0, 0), (5000, 1000, 1, 1),
          (32768, 129, 2, 0), (32769, 129, 2, 0), (65536, 145, 0, 0), (65537, 145, 0, 0)]
 
