@@ -13,6 +13,8 @@
 //   philox_runs_kernel    stream-major fill of longer rows: a wave per run of
 //                         a row, one 16-byte aligned unit of 4 values per lane
 //                         and step
+//   philox_lined_kernel   the same for many rows of 8-16 KiB on lines, the
+//                         waves of a row side by side
 //   philox_il_kernel      interleaved fill: one stream (or a segment of one)
 //                         per lane, consecutive lanes write consecutive
 //                         elements
@@ -292,6 +294,58 @@ philox_runs_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     }
 }
 
+// Stream-major, rows of 8-16 KiB on 128-byte lines in large numbers: a
+// workgroup owns rpw rows, tpr = 256 / rpw threads each; thread j of a row
+// writes blocks j, j + tpr, ... of the row, so the waves of a row write it
+// side by side (2^20 x 2048 uint32 1.43 ms, 1.49 with a wave to a row).  The
+// positions are moved by a launch after it.
+template <int DT>
+__global__ void __launch_bounds__(256)
+philox_lined_kernel(const uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
+                 uint64_t count, uint64_t n, int rpw, unsigned char *__restrict__ out)
+{
+    using T = typename PhiloxOut<DT>::T;
+    const int tpr = 256 / rpw;
+    // several rows per workgroup: row groups in the chunked XCD order, so the
+    // rows whose states share a state-plane line run on one XCD and each line
+    // is fetched into one L2 (one row per workgroup keeps the dispatch order,
+    // measured faster for such long rows)
+    const uint64_t wg = rpw > 1 ? xcd_chunk(gridDim.x).first : blockIdx.x;
+    const uint64_t s = wg * rpw + threadIdx.x / tpr;
+    if (s >= count || (int)threadIdx.x >= rpw * tpr) return;
+    uint32_t w[6];
+    load_state(planes, plane_stride, first + s, w);
+    const uint64_t pos = position(w);
+    const uint64_t off = pos & 3, b0 = pos >> 2;
+    const uint64_t nb = (off + n + 3) / 4;
+    T *row = (T *)out + s * n;
+    for (uint64_t b = threadIdx.x % tpr; b < nb; b += tpr) {
+        uint32_t v[4];
+        philox_block(w, b0 + b, v);
+        const uint64_t k0 = 4 * b - off;  // row index of word 0 (wraps below 0 for b = 0)
+        if (off == 0 && k0 + 4 <= n && ((uintptr_t)(row + k0) % (4 * sizeof(T))) == 0) {
+            T *p = row + k0;
+            if constexpr (DT == 2) {
+                *(double2 *)p = make_double2(PhiloxOut<2>::conv(v[0]), PhiloxOut<2>::conv(v[1]));
+                *(double2 *)(p + 2) = make_double2(PhiloxOut<2>::conv(v[2]), PhiloxOut<2>::conv(v[3]));
+            } else {
+                uint4 q;
+                q.x = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[0]));
+                q.y = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[1]));
+                q.z = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[2]));
+                q.w = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[3]));
+                *(uint4 *)p = q;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint64_t k = k0 + j;  // below 0 wraps to a huge value: skipped
+                if (k < n) row[k] = PhiloxOut<DT>::conv(v[j]);
+            }
+        }
+    }
+}
+
 // Interleaved: out[k * count + s]; lane t draws segment t / count (sb blocks,
 // nseg segments per stream) of stream t % count.
 template <int DT>
@@ -403,6 +457,21 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
     uint64_t rw = nrun > 1 || n * ES >= 6144 ? 1 : count / ((uint64_t)cus * 32);
     rw = rw < 1 ? 1 : rw > 8 ? 8 : rw;
     const uint64_t wgs = ((count + rw - 1) / rw * nrun + 3) / 4;
+    // rows of one run on lines, enough of them to fill the chip
+    if (nrun == 1 && neg == 0 && n * ES >= 8192 && count >= (uint64_t)cus * 256) {
+        int tpr = 64;
+        while (tpr < 256 && (uint64_t)tpr * 16 < (n + 6) / 4) tpr *= 2;
+        const int rpw = 256 / tpr;
+        const uint64_t groups = (count + rpw - 1) / rpw;
+        if (groups <= cap) {
+            hipLaunchKernelGGL((philox_lined_kernel<DT>), dim3((unsigned)groups), dim3(256), 0, st,
+                               planes, plane_stride, first, count, n, rpw, o);
+            hipError_t e = hipGetLastError();
+            if (e == hipSuccess)
+                e = launch_philox_jump(planes, plane_stride, first, count, nullptr, n, st);
+            return e;
+        }
+    }
     const uint64_t per_line = ticket_pitch(plane_stride) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
     const int move = nrun == 1 || nrun * per_line <= 256;
     hipLaunchKernelGGL((philox_runs_kernel<DT>), dim3((unsigned)(wgs < cap ? wgs : cap)), dim3(256), 0, st,

@@ -127,7 +127,7 @@ def test_captured_fill_advances_each_replay(mg):
 # Philox: rows in LDS blocks (one block per row, rows that a workgroup cannot
 # hold whole, the longest), runs of a row (one, several, more than the tickets
 # take), segments of a stream; (streams, n, dtype, layout, offset, position)
-PHILOX = [(300, 1, 0, 0, 1, 3), (5000, 2, 1, 0, 0, 1), (1300, 255, 2, 0, 1, 2), (9000, 61, 0, 0, 3, 0),
+PHILOX = [(65537, 2048, 0, 0, 0, 4), (65538, 1024, 2, 0, 0, 1), (300, 1, 0, 0, 1, 3), (5000, 2, 1, 0, 0, 1), (1300, 255, 2, 0, 1, 2), (9000, 61, 0, 0, 3, 0),
           (2, 511, 0, 0, 5, 1), (2, 512, 0, 0, 5, 1), (70, 2001, 1, 0, 2, 0), (3, 1 << 17, 0, 0, 0, 0),
           (2, 70001, 2, 0, 1, 3), (1, 1 << 21, 1, 0, 7, 2), (5000, 1100, 0, 0, 0, 0),
           (70000, 4, 0, 0, 0, 4), (3000, 1020, 0, 0, 0, 8), (3000, 508, 2, 0, 0, 2), (20000, 1030, 1, 0, 0, 1),
