@@ -289,7 +289,9 @@ mrg_status mrg_get_states(mrg_streamset ss, uint64_t first, uint64_t count,
 
 /* Overwrite the states of streams [first, first+count) from host memory
  * h_in ([count][6] uint32, each a valid state; checked on the host, else
- * MRG_EINVAL and nothing is written).  Synchronous with respect to `stream`. */
+ * MRG_EINVAL and nothing is written).  Synchronous with respect to `stream`.
+ * Streams whose states two calls spoiled by running unordered are whole again
+ * afterwards. */
 mrg_status mrg_set_states(mrg_streamset ss, uint64_t first, uint64_t count,
                           const uint32_t *h_in, void *stream);
 

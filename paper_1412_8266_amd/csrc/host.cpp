@@ -909,7 +909,9 @@ mrg_status mrg_set_states(mrg_streamset ss, uint64_t first, uint64_t count, cons
                                       count * 4, hipMemcpyHostToDevice, (hipStream_t)stream);
         if (e != hipSuccess) return hip_error(e, "hipMemcpyAsync(states)");
     }
-    hipError_t e = hipStreamSynchronize((hipStream_t)stream);
+    hipError_t e = mrg::launch_ticket_reset(ss->d_planes, ss->n, first, count, (hipStream_t)stream);
+    if (e != hipSuccess) return hip_error(e, "ticket reset launch");
+    e = hipStreamSynchronize((hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "hipStreamSynchronize");
 }
 

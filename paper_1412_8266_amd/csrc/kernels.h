@@ -11,7 +11,9 @@ constexpr int kTableWords = 2 * kTableWindows * kTableWindowWords;
 
 // A set's device memory: the six state planes, then one ticket word per stream
 // (arrive() in gen_device.hpp), 0 between launches and set by the kernels that
-// create the streams.  Arrivals at one 128-byte line queue up, 20 ns each over
+// create the streams and by mrg_set_states: fills of one stream that a caller
+// failed to order can leave its ticket in between, and every later fill would
+// then move the stream before all its parts have read the state.  Arrivals at one 128-byte line queue up, 20 ns each over
 // the eight XCDs, so sets of up to 4096 streams give each ticket its own line.
 __host__ __device__ constexpr uint64_t ticket_pitch(uint64_t n) { return n <= 4096 ? 32 : 1; }
 __host__ __device__ constexpr uint64_t ticket_of(uint64_t n, uint64_t i)
@@ -80,6 +82,10 @@ hipError_t launch_fill(uint32_t *planes, uint64_t plane_stride, uint64_t first, 
 
 // Random spacing: stream g0 + s of a set starts at the state expanded from
 // SplitMix64 output g0 + s of the master seed.
+// Tickets of streams [first, first + count) of a set of n streams back to 0.
+hipError_t launch_ticket_reset(uint32_t *planes, uint64_t n, uint64_t first, uint64_t count,
+                               hipStream_t st);
+
 hipError_t launch_random_init(uint32_t *planes, uint64_t plane_stride, uint64_t count,
                               uint64_t g0, uint64_t master, hipStream_t st);
 

@@ -140,6 +140,13 @@ random_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     planes[ticket_of(plane_stride, s)] = 0u;
 }
 
+__global__ void __launch_bounds__(256)
+ticket_reset_kernel(uint32_t *__restrict__ planes, uint64_t n, uint64_t first, uint64_t count)
+{
+    const uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < count) planes[ticket_of(n, first + s)] = 0u;
+}
+
 // ---------------------------------------------------------------------------
 // generation
 // ---------------------------------------------------------------------------
@@ -597,6 +604,14 @@ hipError_t launch_random_init(uint32_t *planes, uint64_t plane_stride, uint64_t 
 {
     hipLaunchKernelGGL(random_init_kernel, dim3(grid_of(count, 256)), dim3(256), 0, st, planes,
                        plane_stride, count, g0, master);
+    return hipGetLastError();
+}
+
+hipError_t launch_ticket_reset(uint32_t *planes, uint64_t n, uint64_t first, uint64_t count,
+                               hipStream_t st)
+{
+    hipLaunchKernelGGL(ticket_reset_kernel, dim3(grid_of(count, 256)), dim3(256), 0, st, planes, n,
+                       first, count);
     return hipGetLastError();
 }
 

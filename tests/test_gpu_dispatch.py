@@ -124,6 +124,40 @@ def test_captured_fill_advances_each_replay(mg):
     ss.close()
 
 
+class Words:
+    """Device words at an address, for torch."""
+
+    def __init__(self, ptr, n):
+        self.__cuda_array_interface__ = {"shape": (n,), "typestr": "<i4", "data": (ptr, False),
+                                         "version": 2}
+
+
+# fills whose parts count their arrivals: rows in blocks, interleaved segments,
+# Philox runs; sets with a line per ticket and with packed tickets
+@pytest.mark.parametrize("generator,streams,first,count,n,layout", [
+    ("mrg32k3a", 8, 2, 5, 20001, 0), ("mrg32k3a", 70, 3, 64, 4097, 1), ("mrg32k3a", 5000, 3, 64, 4097, 1),
+    ("philox", 8, 2, 5, 70001, 0)])
+def test_set_states_makes_spoiled_streams_whole(mg, generator, streams, first, count, n, layout):
+    """Fills of one stream that were not ordered can leave its arrivals counted
+    in part; set_states restores the stream, not its state words alone."""
+    import torch
+    with mg.StreamSet(streams, master_seed=9, generator=generator) as ss:
+        st = ss.get_states()
+        pitch = 32 if streams <= 4096 else 1
+        tickets = torch.as_tensor(Words(ss.states_ptr + 24 * streams, streams * pitch), device="cuda")
+        assert not tickets.cpu().numpy()[::pitch].any()
+        tickets[first * pitch:(first + count) * pitch:pitch] = 1
+        torch.cuda.synchronize()
+        ss.set_states(st[first:first + count], first=first)
+        fill = oracle.fill if generator == "mrg32k3a" else oracle.philox_fill
+        for _ in range(2):
+            got = ss.fill(n, mg.U32, layout, first=first, count=count).cpu().numpy()
+            want, st[first:first + count] = fill(st[first:first + count], n, oracle.U32, layout)
+            assert np.array_equal(got, want)
+            assert np.array_equal(ss.get_states(), st)
+        assert not tickets.cpu().numpy()[::pitch].any()
+
+
 # Philox: rows in LDS blocks (one block per row, rows that a workgroup cannot
 # hold whole, the longest), runs of a row (one, several, more than the tickets
 # take), segments of a stream; (streams, n, dtype, layout, offset, position)
