@@ -37,10 +37,15 @@ constexpr uint32_t kPhiloxW0 = 0x9E3779B9u;  // Weyl key increments: 2^32 (sqrt 
 constexpr uint32_t kPhiloxW1 = 0xBB67AE85u;  //                       2^32 (sqrt 3 - 1)
 
 // a ^ b ^ c in one instruction (gfx950's three-input bit operation, truth table
-// 0x96), which the compiler does not form by itself.
+// 0x96), which the compiler does not form by itself.  Older chips, for which a
+// user's program may be compiled too, do not have it.
 __device__ __forceinline__ uint32_t philox_xor3(uint32_t a, uint32_t b, uint32_t c)
 {
+#if defined(__gfx950__)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+    return a ^ b ^ c;
+#endif
 }
 
 // Ten rounds on the counter c under the key (k0, k1): each round multiplies

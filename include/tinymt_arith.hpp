@@ -55,10 +55,11 @@ constexpr int kRecPhi = 4;
 constexpr int kRecPow = 8;
 
 // a ^ b ^ c and a ^ (b & c): one instruction each on gfx950 (three-input bit
-// operation), which the compiler does not always form by itself.
+// operation; other chips and the host spell it out), which the compiler does
+// not always form by itself.
 TMT_HD uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
+#if defined(__gfx950__)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 #else
     return a ^ b ^ c;
@@ -66,7 +67,7 @@ TMT_HD uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 }
 TMT_HD uint32_t xor_and(uint32_t a, uint32_t b, uint32_t c)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
+#if defined(__gfx950__)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x78);
 #else
     return a ^ (b & c);
