@@ -102,6 +102,23 @@ tmt_jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t f
     r.store(planes, plane_stride, first + s);
 }
 
+// The stream as the row writers draw from it.
+struct RowStream : TinyMTStream {
+    __device__ __forceinline__ uint32_t next_u32()
+    {
+        tmt::step_rows(s0, s1, s2, s3, mat1, mat2);
+        return tmt::temper(s0, s2, s3, tmat);
+    }
+    __device__ __forceinline__ float next_f32()
+    {
+        return __uint_as_float(0x3F800000u | (next_u32() >> 9)) - 0x1.fffffep-1f;  // exact
+    }
+    __device__ __forceinline__ double next_f64()
+    {
+        return __fma_rn((double)next_u32(), 0x1p-32, 0x1p-33);  // exact
+    }
+};
+
 // Stream-major: rows of n values, row s at out + s*n; one wave of 64 lanes
 // per 64 rows (lanes past the last row draw from a dummy state and write
 // nothing).
@@ -118,7 +135,7 @@ tmt_sm_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fir
     const uint64_t s0 = (uint64_t)blockIdx.x * 64;
     const uint64_t nrows = count - s0 < 64 ? count - s0 : 64;
     const bool active = (uint64_t)lane < nrows;
-    TinyMTStream g;
+    RowStream g;
     if (active) {
         g.load(planes, plane_stride, first + s0 + lane, records, q0);
     } else {
@@ -128,12 +145,12 @@ tmt_sm_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fir
         g.rec = records;
     }
     if (n * ES < 128) {  // the wave's rows are one block shorter than 64 lines
-        rows_fill_short<DT, TinyMTStream>(g, lds, lane, nrows, out + s0 * n * ES, n);
+        rows_fill_short<DT, RowStream>(g, lds, lane, nrows, out + s0 * n * ES, n);
     } else {
         if constexpr (TB == 0)
-            rows_fill_carry<DT, 128, TinyMTStream>(g, lds, lane, nrows, out + s0 * n * ES, n);
+            rows_fill_carry<DT, 128, RowStream>(g, lds, lane, nrows, out + s0 * n * ES, n);
         else
-            rows_fill<DT, TB, TinyMTStream>(g, lds, lane, nrows, out + s0 * n * ES, n * ES, n);
+            rows_fill<DT, TB, RowStream>(g, lds, lane, nrows, out + s0 * n * ES, n * ES, n);
     }
     if (active) g.store(planes, plane_stride, first + s0 + lane);
 }

@@ -17,6 +17,15 @@ void tshim_draw(uint32_t *s, const uint32_t *p, uint64_t n, uint32_t *out)
     }
 }
 
+// The same with the row writers' form of the step.
+void tshim_draw_rows(uint32_t *s, const uint32_t *p, uint64_t n, uint32_t *out)
+{
+    for (uint64_t k = 0; k < n; ++k) {
+        step_rows(s[0], s[1], s[2], s[3], p[0], p[1]);
+        out[k] = temper(s[0], s[2], s[3], p[2]);
+    }
+}
+
 void tshim_seed(uint32_t seed, const uint32_t *p, uint32_t *s) { seed_status(seed, p[0], p[1], p[2], s); }
 
 void tshim_candidate(uint64_t master, uint64_t c, uint32_t *p) { candidate(master, c, p); }

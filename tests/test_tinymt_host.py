@@ -81,6 +81,18 @@ def test_draws_and_seeding_match_oracle(shim):
             assert np.array_equal(s, wst)
 
 
+def test_row_writers_step_is_the_step(shim):
+    shim.tshim_draw_rows.argtypes = [P, P, ctypes.c_uint64, P]
+    for p in params(21, 3)[0]:
+        p = u32(p)
+        for seed in [0, 0xFFFFFFFF, 77]:
+            s = u32(oracle.tmt_init(seed, p))
+            want, wst = oracle.tmt_outputs(s, p, 300)
+            got = np.zeros(300, dtype=np.uint32)
+            shim.tshim_draw_rows(_p(s), _p(p), 300, _p(got))
+            assert np.array_equal(got, want) and np.array_equal(s, wst)
+
+
 def test_conversions_match_oracle(shim):
     rng = random.Random(2)
     for w in [0, 1, 511, 512, 0x7FFFFFFF, 0x80000000, 0xFFFFFFFE, 0xFFFFFFFF] + \
