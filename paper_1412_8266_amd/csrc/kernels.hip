@@ -26,6 +26,11 @@
 
 namespace mrg {
 
+// 16-byte units of a window's 16 matrices, and how many of `windows` windows'
+// units a thread of a workgroup of 256 stages.
+constexpr int kJumpUnits = kTableWindowWords / 4;
+constexpr int jump_per(int windows) { return (windows * kJumpUnits + 255) / 256; }
+
 // One component (blockIdx.y) of 256 streams per workgroup, a stream per lane:
 // half the serial chain and twice the waves of a lane with both.  The windows
 // [w_lo, the highest one that any exponent of the workgroup reaches) are
@@ -33,12 +38,18 @@ namespace mrg {
 // is 9 words, so lanes on different digits read different banks.  What bounds
 // it is the chain of products.  Staging all 48 windows of both components a
 // word at a time took most of 19 us for 65536 streams with 77-bit exponents.
+// Every thread loads and stores each of its PER units (jump_per of the windows
+// the launch can reach), those past the windows in use from the first one into
+// room that nothing reads: under a condition of their own the units went
+// through scratch memory one by one (192-bit jumps of 262144 streams 56.7 us,
+// 43.8 now, 52.3 with both components in a lane).
+template <int PER>
 __global__ void __launch_bounds__(256)
 jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
             uint64_t count, const uint64_t *__restrict__ exps, uint64_t g0,
             InitSeed seed, const uint32_t *__restrict__ table, int w_lo, int w_hi)
 {
-    extern __shared__ __attribute__((aligned(16))) uint32_t tab[];
+    __shared__ __attribute__((aligned(16))) uint32_t tab[PER * 256 * 4];
     __shared__ int top_all;
     const int c = blockIdx.y;
     const uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -75,17 +86,16 @@ jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first
     __syncthreads();
     const int end = top_all < w_hi ? top_all : w_hi;
     {
-        // 36 units of 16 bytes per window, up to 1728 in all
-        constexpr int kUnits = kTableWindowWords / 4, kPer = (kTableWindows * kUnits + 255) / 256;
         const uint4 *src = (const uint4 *)(table + (c * kTableWindows + w_lo) * kTableWindowWords);
-        const int units = (end - w_lo) * kUnits;
-        uint4 v[kPer];
+        const int units = (end - w_lo) * kJumpUnits;
+        uint4 v[PER];
 #pragma unroll
-        for (int k = 0; k < kPer; ++k)
-            if (k * 256 + (int)threadIdx.x < units) v[k] = src[k * 256 + threadIdx.x];
+        for (int k = 0; k < PER; ++k) {
+            const int u = k * 256 + (int)threadIdx.x;
+            v[k] = src[u < units ? u : 0];
+        }
 #pragma unroll
-        for (int k = 0; k < kPer; ++k)
-            if (k * 256 + (int)threadIdx.x < units) ((uint4 *)tab)[k * 256 + threadIdx.x] = v[k];
+        for (int k = 0; k < PER; ++k) ((uint4 *)tab)[k * 256 + threadIdx.x] = v[k];
     }
     __syncthreads();
     for (int w = w_lo; w < end; ++w) {
@@ -488,10 +498,16 @@ hipError_t launch_init(uint32_t *planes, uint64_t plane_stride, uint64_t count,
                        uint64_t g0, const InitSeed &seed, const uint32_t *table,
                        int w_lo, int w_hi, hipStream_t st)
 {
-    const size_t lds = (size_t)(w_hi - w_lo) * kTableWindowWords * sizeof(uint32_t);
-    hipLaunchKernelGGL(jump_kernel, dim3(grid_of(count, 256), 2), dim3(256), lds, st, planes,
-                       plane_stride, (uint64_t)0, count, (const uint64_t *)nullptr, g0, seed,
-                       table, w_lo, w_hi);
+    const dim3 grid(grid_of(count, 256), 2), block(256);
+    const uint64_t *none = nullptr;
+#define MRG_INIT(PER)                                                                           \
+    hipLaunchKernelGGL(jump_kernel<PER>, grid, block, 0, st, planes, plane_stride, (uint64_t)0,  \
+                       count, none, g0, seed, table, w_lo, w_hi)
+    // start states use 7 windows up to stream 2^24, 17 up to 2^64
+    if (jump_per(w_hi - w_lo) <= 1) MRG_INIT(1);
+    else if (jump_per(w_hi - w_lo) <= 3) MRG_INIT(3);
+    else MRG_INIT(jump_per(kTableWindows));
+#undef MRG_INIT
     return hipGetLastError();
 }
 
@@ -499,11 +515,10 @@ hipError_t launch_jump(uint32_t *planes, uint64_t plane_stride, uint64_t first,
                        uint64_t count, const uint64_t *d_exp, const uint32_t *table,
                        hipStream_t st)
 {
-    const int w_lo = 0, w_hi = kTableWindows;
-    const size_t lds = (size_t)(w_hi - w_lo) * kTableWindowWords * sizeof(uint32_t);
     InitSeed none = {};
-    hipLaunchKernelGGL(jump_kernel, dim3(grid_of(count, 256), 2), dim3(256), lds, st, planes,
-                       plane_stride, first, count, d_exp, (uint64_t)0, none, table, w_lo, w_hi);
+    hipLaunchKernelGGL(jump_kernel<jump_per(kTableWindows)>, dim3(grid_of(count, 256), 2),
+                       dim3(256), 0, st, planes, plane_stride, first, count, d_exp, (uint64_t)0,
+                       none, table, 0, kTableWindows);
     return hipGetLastError();
 }
 
