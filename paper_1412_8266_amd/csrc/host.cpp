@@ -401,7 +401,7 @@ void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t
     // up to 256 arrivals per ticket line (5 us of them in a row) the fill moves
     // its streams itself, which spares a launch; beyond, a launch follows
     const uint64_t per_line = mrg::ticket_pitch(set_n) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
-    fl->move = fl->nblk * per_line <= 256;
+    fl->move = mrg::ticket_pitch(set_n) && fl->nblk * per_line <= 256;
 }
 
 // Interleaved fill in segments of each stream (fill_il_seg_kernel): as many as
@@ -413,7 +413,8 @@ void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t
 // streams (4096 x 4096 26.6 against 23.0 us, eight 33.6), segments of 32
 // steps no faster, and 65536 binary64 streams in two segments slower (x 1000
 // 98.6 -> 105 us).
-void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t count, uint64_t n, uint64_t es)
+void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t count, uint64_t n,
+                 uint64_t es)
 {
     const uint64_t lanes = (uint64_t)ctx->cus * 2048 / es;
     uint64_t nseg = lanes / count;
@@ -426,7 +427,8 @@ void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t count, uint64_
     fl->table = ctx->d_table;
     const uint64_t e[3] = {n, 0, 0};
     fl->end = jump_matrices(e);
-    fl->move = fl->nblk <= 256;  // arrivals at a stream's ticket (as in split_rows)
+    // arrivals at a stream's ticket (as in split_rows)
+    fl->move = mrg::ticket_pitch(set_n) && fl->nblk <= 256;
 }
 
 // The fill of split_rows and, when it does not move its streams, their jump.
@@ -777,7 +779,7 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
     if (layout == MRG_INTERLEAVED && tune.strategy == 0) {
         DevCtx *ctx;
         if ((st = device_ctx(ss->device, &ctx))) return st;
-        split_steps(&fl, ctx, count, n_per_stream, es);
+        split_steps(&fl, ctx, ss->n, count, n_per_stream, es);
     }
     hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n_per_stream, (int)dtype,
                                     (int)layout, d_out, fl, tune, (hipStream_t)stream);
@@ -851,10 +853,13 @@ mrg_status mrg_fill_leapfrog(mrg_streamset ss, uint64_t s, uint64_t players,
     const uint64_t es_[3] = {A.T - A.Ts, 0, 0};
     A.Jseg = jump_matrices(es_);
     A.end = jump_matrices(en);  // the stream moves past the N outputs dealt
+    A.move = mrg::ticket_pitch(ss->n) != 0;
     const uint64_t waves = A.items < slots ? A.items : slots;
     hipError_t e = mrg::launch_leap(ss->d_planes, ss->n, s, (int)dtype, A,
                                     (unsigned)waves, ctx->d_table, d_out,
                                     tune.engine, (hipStream_t)stream);
+    if (e == hipSuccess && !A.move)
+        e = mrg::launch_jump_uniform(ss->d_planes, ss->n, s, 1, A.end, (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "leapfrog kernel launch");
 }
 
@@ -909,7 +914,9 @@ mrg_status mrg_set_states(mrg_streamset ss, uint64_t first, uint64_t count, cons
                                       count * 4, hipMemcpyHostToDevice, (hipStream_t)stream);
         if (e != hipSuccess) return hip_error(e, "hipMemcpyAsync(states)");
     }
-    hipError_t e = mrg::launch_ticket_reset(ss->d_planes, ss->n, first, count, (hipStream_t)stream);
+    hipError_t e = hipSuccess;
+    if (ss->gen != mrg::kGenTinyMT)  // its fills have no parts
+        e = mrg::launch_ticket_reset(ss->d_planes, ss->n, first, count, (hipStream_t)stream);
     if (e != hipSuccess) return hip_error(e, "ticket reset launch");
     e = hipStreamSynchronize((hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "hipStreamSynchronize");

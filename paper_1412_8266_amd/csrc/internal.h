@@ -12,7 +12,7 @@ struct mrg_streamset_s {
     uint64_t first = 0;            // global index of stream 0 of the set
     uint32_t seed[6] = {};         // base state (global stream 0)
     int gen = 0;                   // 0 MRG32k3a, 1 Philox4x32-10, 2 TinyMT32
-    uint32_t *d_planes = nullptr;  // [6][n] state words, then the tickets
+    uint32_t *d_planes = nullptr;  // [6][n] state words, then the tickets (kernels.h)
     // TinyMT32 sets: records of parameter sets q0 .. q0 + n_sets - 1, each
     // shared by per_param consecutive global streams
     uint32_t *d_records = nullptr;

@@ -9,13 +9,19 @@ namespace mrg {
 
 constexpr int kTableWords = 2 * kTableWindows * kTableWindowWords;
 
-// A set's device memory: the six state planes, then one ticket word per stream
-// (arrive() in gen_device.hpp), 0 between launches and set by the kernels that
+// A set's device memory: the six state planes, then in sets of up to 2^20
+// streams one ticket word per stream (arrive() in gen_device.hpp), 0 between launches and set by the kernels that
 // create the streams and by mrg_set_states: fills of one stream that a caller
 // failed to order can leave its ticket in between, and every later fill would
 // then move the stream before all its parts have read the state.  Arrivals at one 128-byte line queue up, 20 ns each over
 // the eight XCDs, so sets of up to 4096 streams give each ticket its own line.
-__host__ __device__ constexpr uint64_t ticket_pitch(uint64_t n) { return n <= 4096 ? 32 : 1; }
+// Larger sets than 2^20 streams have no tickets: few of their fills are cut
+// into parts, a launch moves those, and every set would pay a sixth more memory
+// and time to create (2^24 streams: 64 of 448 MiB).
+__host__ __device__ constexpr uint64_t ticket_pitch(uint64_t n)
+{
+    return n <= 4096 ? 32 : n <= ((uint64_t)1 << 20) ? 1 : 0;
+}
 __host__ __device__ constexpr uint64_t ticket_of(uint64_t n, uint64_t i)
 {
     return 6 * n + i * ticket_pitch(n);
@@ -97,6 +103,7 @@ struct LeapArgs {
     int KB = 64, R = 1;
     JumpMatrices J63 = {};   // A^(63*P): to the next column block (R = 1)
     JumpMatrices Jseg = {};  // A^(T - Ts): to the next segment (R > 1)
+    int move = 1;            // the last workgroup to read the state moves it (ticket)
     JumpMatrices end = {};   // A^(P*K): the stream's state after the deal
 };
 

@@ -109,7 +109,7 @@ jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first
         pl[0 * plane_stride + idx] = c == 0 ? canon1(a0) : canon2(a0);
         pl[1 * plane_stride + idx] = c == 0 ? canon1(a1) : canon2(a1);
         pl[2 * plane_stride + idx] = c == 0 ? canon1(a2) : canon2(a2);
-        if (!exps && c == 0) planes[ticket_of(plane_stride, idx)] = 0u;
+        if (!exps && c == 0 && ticket_pitch(plane_stride)) planes[ticket_of(plane_stride, idx)] = 0u;
     }
 }
 
@@ -147,7 +147,7 @@ random_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     uint32_t w[6];
     expand_seed(splitmix64_mix(master + (g0 + s + 1) * kSplitMixGamma), w);
     store_state(planes, plane_stride, s, w);
-    planes[ticket_of(plane_stride, s)] = 0u;
+    if (ticket_pitch(plane_stride)) planes[ticket_of(plane_stride, s)] = 0u;
 }
 
 __global__ void __launch_bounds__(256)
@@ -401,8 +401,9 @@ fill_split_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t
 // A^(T - Ts) (Jseg; stepping on when R = 1), to the next column block by
 // A^(63*P) (J63; only with R = 1, since K < 64 leaves one column block).  The
 // waves of a workgroup (up to 16, for at most 256 workgroups) arrive together
-// at the stream's ticket: 4096 arrivals one by one would queue for 80 us.  The
-// last workgroup to read the state moves it by P*K.
+// at the stream's ticket: 4096 arrivals one by one would queue for 80 us.  With
+// `move` the last workgroup to read the state moves it by P*K, else a launch
+// after this one.
 template <int DT, class G>
 __global__ void __launch_bounds__(1024)
 fill_leap_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t sidx,
@@ -415,7 +416,7 @@ fill_leap_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t 
     // this wave's state words are in registers, then the workgroup's
     asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5])::"memory");
     __syncthreads();
-    if (threadIdx.x == 0 &&
+    if (A.move && threadIdx.x == 0 &&
         last_arrival(arrive(planes + ticket_of(plane_stride, sidx), gridDim.x, w), gridDim.x)) {
         uint32_t e[6] = {w[0], w[1], w[2], w[3], w[4], w[5]};
         matvec3<C1>(A.end.m, e[0], e[1], e[2]);
@@ -625,6 +626,7 @@ hipError_t launch_random_init(uint32_t *planes, uint64_t plane_stride, uint64_t 
 hipError_t launch_ticket_reset(uint32_t *planes, uint64_t n, uint64_t first, uint64_t count,
                                hipStream_t st)
 {
+    if (!ticket_pitch(n)) return hipSuccess;
     hipLaunchKernelGGL(ticket_reset_kernel, dim3(grid_of(count, 256)), dim3(256), 0, st, planes, n,
                        first, count);
     return hipGetLastError();

@@ -62,7 +62,7 @@ philox_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
     const uint32_t w[6] = {0u, 0u, (uint32_t)g, (uint32_t)(g >> 32), (uint32_t)key,
                            (uint32_t)(key >> 32)};
     store_state(planes, plane_stride, s, w);
-    planes[ticket_of(plane_stride, s)] = 0u;
+    if (ticket_pitch(plane_stride)) planes[ticket_of(plane_stride, s)] = 0u;
 }
 
 __global__ void __launch_bounds__(256)
@@ -351,7 +351,7 @@ philox_lined_kernel(const uint32_t *__restrict__ planes, uint64_t plane_stride, 
 template <int DT>
 __global__ void __launch_bounds__(256)
 philox_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
-                 uint64_t count, uint64_t n, uint32_t nseg, uint64_t sb,
+                 uint64_t count, uint64_t n, uint32_t nseg, uint64_t sb, int move,
                  unsigned char *__restrict__ out)
 {
     using T = typename PhiloxOut<DT>::T;
@@ -365,7 +365,7 @@ philox_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t 
     uint32_t w[6];
     load_state(planes, plane_stride, first + s, w);
     uint32_t arrived = 0;
-    if (nseg > 1) arrived = arrive(planes + ticket_of(plane_stride, first + s), nseg, w);
+    if (move && nseg > 1) arrived = arrive(planes + ticket_of(plane_stride, first + s), nseg, w);
     const uint64_t pos = position(w);
     const uint64_t off = pos & 3, b0 = pos >> 2;
     const uint64_t nb = (off + n + 3) / 4;
@@ -380,7 +380,7 @@ philox_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t 
             if (k < n) col[k * count] = PhiloxOut<DT>::conv(v[j]);
         }
     }
-    if (last_arrival(arrived, nseg)) store_position(planes, plane_stride, first + s, pos + n);
+    if (move && last_arrival(arrived, nseg)) store_position(planes, plane_stride, first + s, pos + n);
 }
 
 unsigned grid256(uint64_t items) { return (unsigned)((items + 255) / 256); }
@@ -420,9 +420,13 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
         if (nseg < 1) nseg = 1;
         const uint64_t sb = (nb + nseg - 1) / nseg;
         nseg = (nb + sb - 1) / sb;
+        const int move = nseg == 1 || ticket_pitch(plane_stride);
         hipLaunchKernelGGL((philox_il_kernel<DT>), dim3(grid256(count * nseg)), dim3(256), 0, st,
-                           planes, plane_stride, first, count, n, (uint32_t)nseg, sb, o);
-        return hipGetLastError();
+                           planes, plane_stride, first, count, n, (uint32_t)nseg, sb, move, o);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess && !move)
+            e = launch_philox_jump(planes, plane_stride, first, count, nullptr, n, st);
+        return e;
     }
     // short rows a workgroup at a time (rows of 600 and 1000 float32 off 16
     // bytes or blocks are faster in runs: 65536 x 600 42 against 39 us)
@@ -473,7 +477,7 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
         }
     }
     const uint64_t per_line = ticket_pitch(plane_stride) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
-    const int move = nrun == 1 || nrun * per_line <= 256;
+    const int move = nrun == 1 || (ticket_pitch(plane_stride) && nrun * per_line <= 256);
     hipLaunchKernelGGL((philox_runs_kernel<DT>), dim3((unsigned)(wgs < cap ? wgs : cap)), dim3(256), 0, st,
                        planes, plane_stride, first, count, n, (uint32_t)rw,
                        (uint32_t)nrun, (uint32_t)(per * 64), move, o);

@@ -81,7 +81,6 @@ tmt_init_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t c
     tmt::jump(st, mat1, mat2, rec + tmt::kRecPhi, rec + tmt::kRecPow, 0, j, 0);
     const uint32_t w[6] = {st[0], st[1], st[2], st[3], (uint32_t)q, 0u};
     store_state(planes, plane_stride, s, w);
-    planes[ticket_of(plane_stride, s)] = 0u;
 }
 
 __global__ void __launch_bounds__(256)

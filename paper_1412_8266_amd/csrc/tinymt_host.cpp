@@ -188,7 +188,7 @@ mrg_status mrg_streamset_create_tinymt(mrg_streamset *out, uint64_t n_streams,
     ss->per_param = per_param;
     ss->q0 = q0;
     ss->n_sets = nsets;
-    e = hipMalloc(&ss->d_planes, mrg::set_words(n_streams) * sizeof(uint32_t));
+    e = hipMalloc(&ss->d_planes, 6 * n_streams * sizeof(uint32_t));
     if (e != hipSuccess) {
         delete ss;
         return fail(set_error(MRG_ENOMEM, "hipMalloc(%llu states): %s",

@@ -124,6 +124,44 @@ def test_captured_fill_advances_each_replay(mg):
     ss.close()
 
 
+def test_sets_hold_what_their_fills_need(mg):
+    """24 bytes a stream, tickets beside them in sets of up to 2^20 streams of
+    the generators that cut streams into parts."""
+    import torch
+    n = 1 << 26
+    for generator in ("mrg32k3a", "philox", "tinymt"):
+        with mg.StreamSet(n, master_seed=1, generator=generator, per_param=n) as ss:  # tables, records
+            ss.fill(4, mg.U32, count=1)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        with mg.StreamSet(n, master_seed=1, generator=generator, per_param=n):
+            used = before - torch.cuda.mem_get_info()[0]
+        assert used < 25 * n, (generator, used / n)
+
+
+# a range of a set with a ticket per stream and of one without: rows in blocks,
+# segments, a deal, Philox runs and segments; both move their streams
+@pytest.mark.parametrize("streams", [1 << 20, (1 << 20) + 1])
+@pytest.mark.parametrize("generator,count,n,layout", [
+    ("mrg32k3a", 3, 20001, 0), ("mrg32k3a", 100, 1000, 1), ("mrg32k3a", 1, 9, 2),
+    ("philox", 3, 70001, 0), ("philox", 40, 4001, 1)])
+def test_ranges_of_sets_with_and_without_tickets(mg, streams, generator, count, n, layout):
+    with mg.StreamSet(streams, master_seed=3, generator=generator) as ss:
+        first = streams - count - 1
+        st = ss.get_states(first, count)
+        fill = oracle.fill if generator == "mrg32k3a" else oracle.philox_fill
+        for _ in range(2):
+            if layout == 2:  # n cards to each of 500 players
+                got = ss.fill_leapfrog(first, 500, n, mg.U32).cpu().numpy()
+                want, st = oracle.fill(st, 500 * n, oracle.U32)
+                want = want.reshape(n, 500).T
+            else:
+                got = ss.fill(n, mg.U32, layout, first=first, count=count).cpu().numpy()
+                want, st = fill(st, n, oracle.U32, layout)
+            assert np.array_equal(got, want)
+            assert np.array_equal(ss.get_states(first, count), st)
+
+
 class Words:
     """Device words at an address, for torch."""
 
