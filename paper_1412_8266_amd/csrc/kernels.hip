@@ -43,32 +43,40 @@ constexpr int jump_per(int windows) { return (windows * kJumpUnits + 255) / 256;
 // room that nothing reads: under a condition of their own the units went
 // through scratch memory one by one (192-bit jumps of 262144 streams 56.7 us,
 // 43.8 now, 52.3 with both components in a lane).
-template <int PER>
+// BOTH: the lane has both components, one after the other, for set creation on
+// a full chip, where the chain is hidden and the exponents are shared (2^24
+// streams 353 us, 420 with a component per lane; 2^18 9.7 and 9.9, 2^17 6.3 and
+// 6.1).
+template <int PER, bool BOTH = false>
 __global__ void __launch_bounds__(256)
 jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
             uint64_t count, const uint64_t *__restrict__ exps, uint64_t g0,
             InitSeed seed, const uint32_t *__restrict__ table, int w_lo, int w_hi)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t tab[PER * 256 * 4];
+    constexpr int NC = BOTH ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) uint32_t tab[NC][PER * 256 * 4];
     __shared__ int top_all;
-    const int c = blockIdx.y;
+    const int c0 = BOTH ? 0 : blockIdx.y;
     const uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = s < count;
     const uint64_t idx = first + s;
-    uint32_t *pl = planes + 3 * c * plane_stride;
-    uint32_t a0 = 0, a1 = 0, a2 = 0;
+    uint32_t a[NC][3] = {};
     uint64_t e0 = 0, e1 = 0, e2 = 0;
     if (threadIdx.x == 0) top_all = w_lo;
     if (active) {
         if (exps) {  // jump the current state by its own exponent
-            a0 = pl[0 * plane_stride + idx];
-            a1 = pl[1 * plane_stride + idx];
-            a2 = pl[2 * plane_stride + idx];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) a[c][i] = planes[(3 * (c0 + c) + i) * plane_stride + idx];
             e0 = exps[3 * s + 0];
             e1 = exps[3 * s + 1];
             e2 = exps[3 * s + 2];
         } else {     // create: start of global stream g = g0 + s is A^(g 2^127) seed
-            a0 = seed.w[3 * c]; a1 = seed.w[3 * c + 1]; a2 = seed.w[3 * c + 2];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) a[c][i] = seed.w[3 * (c0 + c) + i];
             const uint64_t g = g0 + s;
             e0 = 0;
             e1 = (g & 1u) << 63;
@@ -86,30 +94,40 @@ jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first
     __syncthreads();
     const int end = top_all < w_hi ? top_all : w_hi;
     {
-        const uint4 *src = (const uint4 *)(table + (c * kTableWindows + w_lo) * kTableWindowWords);
         const int units = (end - w_lo) * kJumpUnits;
-        uint4 v[PER];
+        uint4 v[NC][PER];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int u = k * 256 + (int)threadIdx.x;
-            v[k] = src[u < units ? u : 0];
+        for (int c = 0; c < NC; ++c) {
+            const uint4 *src =
+                (const uint4 *)(table + ((c0 + c) * kTableWindows + w_lo) * kTableWindowWords);
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int u = k * 256 + (int)threadIdx.x;
+                v[c][k] = src[u < units ? u : 0];
+            }
         }
 #pragma unroll
-        for (int k = 0; k < PER; ++k) ((uint4 *)tab)[k * 256 + threadIdx.x] = v[k];
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 0; k < PER; ++k) ((uint4 *)tab[c])[k * 256 + threadIdx.x] = v[c][k];
     }
     __syncthreads();
     for (int w = w_lo; w < end; ++w) {
         const uint32_t d = exp_digit(e0, e1, e2, w);
         if (!__any(d != 0u)) continue;  // wave-uniform skip of empty windows
-        const uint32_t *T = tab + ((w - w_lo) * 16 + d) * 9;
-        if (c == 0) matvec3<C1>(T, a0, a1, a2);
-        else matvec3<C2>(T, a0, a1, a2);
+        const uint32_t at = ((w - w_lo) * 16 + d) * 9;
+        if (c0 == 0) matvec3<C1>(tab[0] + at, a[0][0], a[0][1], a[0][2]);
+        else matvec3<C2>(tab[0] + at, a[0][0], a[0][1], a[0][2]);
+        if (BOTH) matvec3<C2>(tab[NC - 1] + at, a[NC - 1][0], a[NC - 1][1], a[NC - 1][2]);
     }
     if (active) {
-        pl[0 * plane_stride + idx] = c == 0 ? canon1(a0) : canon2(a0);
-        pl[1 * plane_stride + idx] = c == 0 ? canon1(a1) : canon2(a1);
-        pl[2 * plane_stride + idx] = c == 0 ? canon1(a2) : canon2(a2);
-        if (!exps && c == 0 && ticket_pitch(plane_stride)) planes[ticket_of(plane_stride, idx)] = 0u;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                planes[(3 * (c0 + c) + i) * plane_stride + idx] =
+                    c0 + c == 0 ? canon1(a[c][i]) : canon2(a[c][i]);
+        if (!exps && c0 == 0 && ticket_pitch(plane_stride)) planes[ticket_of(plane_stride, idx)] = 0u;
     }
 }
 
@@ -505,7 +523,10 @@ hipError_t launch_init(uint32_t *planes, uint64_t plane_stride, uint64_t count,
     hipLaunchKernelGGL(jump_kernel<PER>, grid, block, 0, st, planes, plane_stride, (uint64_t)0,  \
                        count, none, g0, seed, table, w_lo, w_hi)
     // start states use 7 windows up to stream 2^24, 17 up to 2^64
-    if (jump_per(w_hi - w_lo) <= 1) MRG_INIT(1);
+    if (jump_per(w_hi - w_lo) <= 1 && count >= ((uint64_t)1 << 18))
+        hipLaunchKernelGGL((jump_kernel<1, true>), dim3(grid_of(count, 256)), block, 0, st, planes,
+                           plane_stride, (uint64_t)0, count, none, g0, seed, table, w_lo, w_hi);
+    else if (jump_per(w_hi - w_lo) <= 1) MRG_INIT(1);
     else if (jump_per(w_hi - w_lo) <= 3) MRG_INIT(3);
     else MRG_INIT(jump_per(kTableWindows));
 #undef MRG_INIT
