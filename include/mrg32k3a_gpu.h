@@ -295,6 +295,36 @@ mrg_status mrg_get_states(mrg_streamset ss, uint64_t first, uint64_t count,
 mrg_status mrg_set_states(mrg_streamset ss, uint64_t first, uint64_t count,
                           const uint32_t *h_in, void *stream);
 
+/* How mrg_fill and mrg_fill_leapfrog launch an MRG32k3a call under the current
+ * tuning keys, computed on the host alone: no stream set, device or output
+ * memory is touched.  For tests and tools. */
+#define MRG_ROUTE_LANES 0   /* rows, one lane per stream */
+#define MRG_ROUTE_WAVE 1    /* rows, `lanes` lanes per stream */
+#define MRG_ROUTE_BLOCKS 2  /* rows cut into blocks of a wave each */
+#define MRG_ROUTE_PARTS 3   /* steps, each stream in several segments */
+#define MRG_ROUTE_HALVES 4  /* rows, two lanes per stream, half a row each */
+#define MRG_ROUTE_STEPS 5   /* steps, one lane per stream */
+#define MRG_ROUTE_DEAL 6    /* each player's cards in a row */
+typedef struct {
+    int32_t kernel;            /* MRG_ROUTE_* */
+    int32_t lanes;             /* lanes per stream */
+    uint64_t parts;            /* blocks or segments per stream; items of a deal */
+    uint64_t part_values;      /* values of a part; players per lane of a deal */
+    uint32_t chunk_values;     /* values of a wave's chunk (WAVE: of a stream's; BLOCKS) */
+    uint32_t waves;            /* DEAL: waves, and how many to a workgroup */
+    uint32_t waves_per_group;
+    int32_t moves;             /* 0: a launch after the fill moves the streams */
+} mrg_route;
+
+/* `count` streams of a set of set_streams, output at a byte offset of
+ * out_offset from a 128-byte line, on a device of `cus` compute units.
+ * Errors: MRG_EINVAL (null), MRG_ERANGE. */
+mrg_status mrg_fill_route(uint64_t set_streams, uint64_t count, uint64_t n_per_stream,
+                          mrg_dtype dtype, mrg_layout layout, uint64_t out_offset, int32_t cus,
+                          mrg_route *route);
+mrg_status mrg_leapfrog_route(uint64_t set_streams, uint64_t players, uint64_t per_player,
+                              mrg_dtype dtype, mrg_layout layout, int32_t cus, mrg_route *route);
+
 /* ---------------------------------------------------------------------- */
 /* Batched generation: many fill requests in one graph of persistent launches */
 /* ---------------------------------------------------------------------- */
@@ -586,6 +616,12 @@ mrg_status mrg_state_check(const uint32_t state6[6]);
  *                64 for rows of 64 KiB and more, else as many as give two
  *                waves per SIMD, at least 16, or 8 for many short rows off
  *                their lines).
+ * Under strategy 0 the long rows of few streams are cut into blocks of a wave
+ * each, rows of whole 4 KiB on lines that go to lanes take two lanes per
+ * stream unless tile_bytes is set, the streams of an interleaved fill that are
+ * too few to fill the chip are cut into segments, and one interleaved stream
+ * is filled as a row.  Strategies 1 and 2 do none of this, in either layout,
+ * and a coop key that is set keeps rows out of the blocks.
  * Unknown keys or values: MRG_EINVAL.  Takes effect for later launches. */
 mrg_status mrg_config_set(const char *key, int64_t value);
 mrg_status mrg_config_get(const char *key, int64_t *value);

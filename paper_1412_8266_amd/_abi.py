@@ -68,6 +68,8 @@ _SIGS = {
     "mrg_jump_substreams": [_P, _U64, _U64, _U64, _P],
     "mrg_fill": [_P, _U64, _U64, _U64, _I32, _I32, _P, _P],
     "mrg_fill_leapfrog": [_P, _U64, _U64, _U64, _I32, _I32, _P, _P],
+    "mrg_fill_route": [_U64, _U64, _U64, _I32, _I32, _U64, _I32, _P],
+    "mrg_leapfrog_route": [_U64, _U64, _U64, _I32, _I32, _I32, _P],
     "mrg_get_states": [_P, _U64, _U64, _PU32, _P],
     "mrg_set_states": [_P, _U64, _U64, _PU32, _P],
     "mrg_seed_from_master": [_U64, _PU32],
@@ -312,6 +314,28 @@ def mrg_fill(ss: int, first: int, count: int, n_per_stream: int, dtype: int, lay
 def mrg_fill_leapfrog(ss: int, s: int, players: int, per_player: int, dtype: int, layout: int,
                       d_out: int, stream: int = 0) -> None:
     _call("mrg_fill_leapfrog", ss, s, players, per_player, dtype, layout, d_out, stream)
+
+
+class mrg_route(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("lanes", ctypes.c_int32), ("parts", ctypes.c_uint64),
+                ("part_values", ctypes.c_uint64), ("chunk_values", ctypes.c_uint32),
+                ("waves", ctypes.c_uint32), ("waves_per_group", ctypes.c_uint32),
+                ("moves", ctypes.c_int32)]
+
+
+def mrg_fill_route(set_streams: int, count: int, n: int, dtype: int, layout: int,
+                   out_offset: int = 0, cus: int = 256) -> mrg_route:
+    r = mrg_route()
+    _call("mrg_fill_route", set_streams, count, n, dtype, layout, out_offset, cus, ctypes.byref(r))
+    return r
+
+
+def mrg_leapfrog_route(set_streams: int, players: int, per_player: int, dtype: int, layout: int,
+                       cus: int = 256) -> mrg_route:
+    r = mrg_route()
+    _call("mrg_leapfrog_route", set_streams, players, per_player, dtype, layout, cus,
+          ctypes.byref(r))
+    return r
 
 
 def mrg_get_states(ss: int, first: int, count: int, stream: int = 0):

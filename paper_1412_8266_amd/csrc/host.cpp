@@ -378,10 +378,9 @@ mrg::JumpMatrices jump_matrices(const uint64_t e[3])
 // whole number of 64-lane chunks -- of 64 KiB (256 uint32 per lane and start
 // state) when the blocks are that long, else of 16 or 8 KiB -- and at most 256
 // KiB (one stream of 2^32 uint32 in order: 2 MiB blocks 2 % slower).
-void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t count, uint64_t n,
-                uint64_t es)
+void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es)
 {
-    const uint64_t row = n * es, want = row / 16 * count / (uint64_t)ctx->cus;
+    const uint64_t row = n * es, want = row / 16 * count / (uint64_t)cus;
     const uint64_t unit = want >= 65536 ? 65536 : want >= 16384 ? 16384 : 8192;
     uint64_t bb = want / unit * unit;
     bb = bb < unit ? unit : bb > 262144 ? 262144 : bb;
@@ -392,9 +391,6 @@ void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t
     fl->B = bb / es;
     // a remainder under an eighth of a block goes to the last block
     fl->nblk = (uint32_t)(n / fl->B + (n % fl->B > fl->B / 8 || n < fl->B));
-    fl->lane_tab = ctx->d_lane_tab + mrg::lane_table(fl->L) * 64 * 18;
-    fl->tabs = ctx->d_lane_tab;
-    fl->table = ctx->d_table;
     fl->grid = (unsigned)(count * fl->nblk);
     const uint64_t e[3] = {n, 0, 0};
     fl->end = jump_matrices(e);
@@ -413,10 +409,9 @@ void split_rows(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t
 // streams (4096 x 4096 26.6 against 23.0 us, eight 33.6), segments of 32
 // steps no faster, and 65536 binary64 streams in two segments slower (x 1000
 // 98.6 -> 105 us).
-void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_t count, uint64_t n,
-                 uint64_t es)
+void split_steps(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es)
 {
-    const uint64_t lanes = (uint64_t)ctx->cus * 2048 / es;
+    const uint64_t lanes = (uint64_t)cus * 2048 / es;
     uint64_t nseg = lanes / count;
     if (nseg > n / 64) nseg = n / 64;
     if (nseg < 2) return;
@@ -424,21 +419,162 @@ void split_steps(mrg::FillLaunch *fl, const DevCtx *ctx, uint64_t set_n, uint64_
     fl->nblk = (uint32_t)((n + fl->B - 1) / fl->B);
     if (fl->nblk < 2) return;
     fl->kernel = 3;
-    fl->table = ctx->d_table;
     const uint64_t e[3] = {n, 0, 0};
     fl->end = jump_matrices(e);
     // arrivals at a stream's ticket (as in split_rows)
     fl->move = mrg::ticket_pitch(set_n) && fl->nblk <= 256;
 }
 
-// The fill of split_rows and, when it does not move its streams, their jump.
-hipError_t run_split(mrg_streamset ss, const mrg::FillLaunch &fl, const mrg::FillTuning &tune,
-                     uint64_t first, uint64_t count, uint64_t n, mrg_dtype dtype, void *d_out,
-                     hipStream_t st)
+// How an MRG32k3a fill is launched under `tune` on a device of `cus` compute
+// units (the tables' addresses apart).  *layout becomes stream-major where one
+// stream is drawn in order.
+mrg::FillLaunch plan_fill(const mrg::FillTuning &tune, int cus, uint64_t set_n, uint64_t count,
+                          uint64_t n_per_stream, uint64_t es, mrg_layout *layout, uintptr_t out)
 {
-    hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n, (int)dtype, 0, d_out, fl,
-                                    tune, st);
-    if (e == hipSuccess && !fl.move)
+    mrg::FillLaunch fl;
+    // one stream: both layouts are its values in a row
+    if (count == 1 && tune.strategy == 0) *layout = MRG_STREAM_MAJOR;
+    if (*layout == MRG_STREAM_MAJOR) {
+        // several lanes per stream (or when forced) for rows from coop_min_bytes
+        // on (see below for rows under 16 KiB); lane per stream for the others
+        const bool coop = tune.strategy == 2 ||
+                          (tune.strategy == 0 && n_per_stream * es >= coop_min_bytes(count, cus));
+        if (coop) {
+            // GL lanes per stream, 64/GL streams per wave; each lane takes
+            // 64/GL or 2*64/GL pieces of 128 bytes per chunk (a chunk is then
+            // 64 or 128 lines), whichever generates fewer values past the end
+            // of a row (the longer chunk on a tie).  A row's line-aligned
+            // part is n values, or about n - tv/2 when rows start anywhere.
+            const bool rows_aligned = out % 128 == 0 && (n_per_stream * es) % 128 == 0;
+            const int GL = tune.coop_lanes ? tune.coop_lanes
+                                           : coop_auto_lanes(count, n_per_stream * es, rows_aligned, cus);
+            const uint64_t tv = 128 / es;
+            const uint64_t nh_min = 64 / GL, nh_max = 2 * nh_min;
+            const uint64_t body = rows_aligned || n_per_stream <= tv ? n_per_stream : n_per_stream - tv / 2;
+            const uint64_t ch_min = (uint64_t)GL * nh_min * tv, ch_max = 2 * ch_min;
+            const uint64_t gen_min = (body + ch_min - 1) / ch_min * ch_min;
+            const uint64_t gen_max = (body + ch_max - 1) / ch_max * ch_max;
+            const uint64_t nh = gen_max <= gen_min ? nh_max : nh_min;
+            const int L = (int)(nh * tv);
+            fl.kernel = 1;
+            fl.L = L;
+            fl.lanes = GL;
+            // resident workgroups stride over the stream groups, or one per group
+            const uint64_t groups = (count + (64 / GL) - 1) / (64 / GL);
+            const uint64_t cap = tune.coop_wgs_per_cu ? (uint64_t)cus * tune.coop_wgs_per_cu
+                                                      : ((uint64_t)1 << 31) - 1;
+            fl.grid = (unsigned)(groups < cap ? groups : cap);
+            fl.order = tune.coop_order;
+            // the bulk case: rows on lines, whole chunks, a group's rows
+            // addressable with 32-bit offsets
+            fl.whole = rows_aligned && n_per_stream % ((uint64_t)GL * L) == 0 &&
+                       (uint64_t)(64 / GL) * n_per_stream * es < ((uint64_t)1 << 32);
+            // automatic choice: a row under 16 KiB that is not whole chunks on
+            // lines is one cut chunk for this writer (values drawn past the
+            // row's end, one piece per flush), and with enough streams for one
+            // wave of them on every SIMD (2^16 on 256 CUs) the lane-per-stream
+            // writer is the faster one (uint32 rows of 3000: 190 us against
+            // 210-235 for 2^16 streams, 4.0-4.5 against 3.4 TB/s for 2^17 and
+            // more; of 4000: 228 against 264-276 us, 4.2-4.4 against 3.6-3.7
+            // TB/s; from 4500 values this writer leads, 4.7-4.8 against
+            // 4.0-4.5).  With fewer streams this writer keeps the launch short
+            // (49152 x 3000: 160 against 177 us).
+            if (tune.strategy == 0 && !fl.whole && n_per_stream * es < 16 * 1024 &&
+                count >= (uint64_t)cus * 256)
+                fl = mrg::FillLaunch();
+        }
+        // lane per stream, rows of whole 4 KiB on lines: two lanes per stream
+        // (fill_sm_kernel's HALVES; other row lengths lose by it: 131072 x 1536
+        // float32 171 -> 189 us, x 512 59 -> 62)
+        if (tune.strategy == 0 && fl.kernel == 0 && tune.tile_bytes == 0 &&
+            out % 128 == 0 && n_per_stream * es % 4096 == 0) {
+            fl.kernel = 4;
+            const uint64_t e[3] = {n_per_stream / 2, 0, 0};
+            fl.end = jump_matrices(e);
+        }
+        // few streams: a wave per stream leaves the chip idle and takes 2.3 us
+        // per 4096 uint32 of a row whatever the launch writes, so rows are cut
+        // into blocks (256 x 16384 uint32 15.1 -> 11.2 us, 64 x 2^20 590 -> 49).
+        // With two waves or more per CU the rows have to be long enough for the
+        // blocks' jumps (512 x 10000 15.7 -> 16.9, 512 x 40000 35.4 -> 28.4),
+        // and with a wave per SIMD the rows alone fill the chip (1000 x 65536
+        // 50 -> 56).  A key of the wave-per-stream writer that is set keeps it.
+        const bool asked = tune.coop_lanes || tune.coop_wgs_per_cu || tune.coop_order;
+        if (tune.strategy == 0 && !asked &&
+            ((count <= (uint64_t)cus && n_per_stream * es >= 16 * 1024) ||
+             (count <= (uint64_t)cus * 2 && n_per_stream * es >= 64 * 1024))) {
+            fl = mrg::FillLaunch();
+            split_rows(&fl, cus, set_n, count, n_per_stream, es);
+        }
+    }
+    if (*layout == MRG_INTERLEAVED && tune.strategy == 0)
+        split_steps(&fl, cus, set_n, count, n_per_stream, es);
+    return fl;
+}
+
+// How a deal is launched: true for one drawn in order (fl: the stream as one
+// row in blocks), else A.
+bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, uint64_t es,
+               mrg_layout layout, mrg::FillLaunch *fl, mrg::LeapArgs *leap)
+{
+    const uint64_t N = players * per_player;
+    const uint64_t en[3] = {N, 0, 0};
+    // with one player or one card per player both layouts are the stream in order
+    if (layout == MRG_INTERLEAVED || players == 1 || per_player == 1) {
+        split_rows(fl, cus, set_n, 1, N, es);
+        return true;
+    }
+    mrg::LeapArgs &A = *leap;
+    // each player's cards in a row: items of KB = min(K, 64) card columns
+    // x T players (R = 64 / KB lanes per column, Ts = T / R players
+    // each), T chosen for about 4 items per resident wave, at least 32
+    // players per lane (65536 players of 52 cards: 256 to a lane left 256
+    // waves and 20.9 us, 32 are 11.6 us, 16 no faster: 14.0)
+    const uint64_t slots = (uint64_t)cus * 16;  // resident waves
+    A.P = players;
+    A.K = per_player;
+    A.KB = (int)(per_player < 64 ? per_player : 64);
+    A.R = 64 / A.KB;
+    const uint64_t nkb = (per_player + A.KB - 1) / A.KB;
+    const uint64_t target = 4 * slots;
+    uint64_t Ts = (players + A.R - 1) / A.R;
+    if (nkb < target) {
+        const uint64_t segs = (target + nkb - 1) / nkb;
+        Ts = (players + segs * A.R - 1) / (segs * A.R);
+        if (Ts < 32) Ts = 32;
+    }
+    const uint64_t ts_max = (players + A.R - 1) / A.R;
+    if (Ts > ts_max) Ts = ts_max;
+    A.Ts = Ts;
+    A.T = Ts * A.R;
+    A.nseg = (players + A.T - 1) / A.T;
+    A.items = nkb * A.nseg;
+    // 63 * players and T - Ts as 192-bit exponents
+    const unsigned __int128 e63 = (unsigned __int128)players * 63u;
+    const uint64_t ew[3] = {(uint64_t)e63, (uint64_t)(e63 >> 64), 0};
+    A.J63 = jump_matrices(ew);
+    const uint64_t es_[3] = {A.T - A.Ts, 0, 0};
+    A.Jseg = jump_matrices(es_);
+    A.end = jump_matrices(en);  // the stream moves past the N outputs dealt
+    // up to 16 waves a workgroup, for at most 256 arrivals at the ticket
+    A.waves = (unsigned)(A.items < slots ? A.items : slots);
+    A.per_group = A.waves <= 256 ? 1 : A.waves >= 4096 ? 16 : (A.waves + 255) / 256;
+    A.move = mrg::ticket_pitch(set_n) != 0;
+    return false;
+}
+
+// The fill planned in fl and, when it cuts streams into parts that do not move
+// them, their jump.
+hipError_t run_fill(mrg_streamset ss, const DevCtx *ctx, mrg::FillLaunch fl,
+                    const mrg::FillTuning &tune, uint64_t first, uint64_t count, uint64_t n,
+                    mrg_dtype dtype, mrg_layout layout, void *d_out, hipStream_t st)
+{
+    fl.tabs = ctx->d_lane_tab;
+    fl.lane_tab = ctx->d_lane_tab + (fl.L ? mrg::lane_table(fl.L) * 64 * 18 : 0);
+    fl.table = ctx->d_table;
+    hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n, (int)dtype, (int)layout,
+                                    d_out, fl, tune, st);
+    if (e == hipSuccess && (fl.kernel == 2 || fl.kernel == 3) && !fl.move)
         e = mrg::launch_jump_uniform(ss->d_planes, ss->n, first, count, fl.end, st);
     return e;
 }
@@ -692,99 +828,12 @@ mrg_status mrg_fill(mrg_streamset ss, uint64_t first, uint64_t count, uint64_t n
                                             tune.tile_bytes, (hipStream_t)stream);
         return e == hipSuccess ? MRG_OK : hip_error(e, "tinymt fill kernel launch");
     }
-    mrg::FillLaunch fl;
-    // one stream: both layouts are its values in a row
-    if (count == 1 && tune.strategy == 0) layout = MRG_STREAM_MAJOR;
-    if (layout == MRG_STREAM_MAJOR) {
-        // several lanes per stream (or when forced) for rows from coop_min_bytes
-        // on (see below for rows under 16 KiB); lane per stream for the others
-        DevCtx *ctx;
-        if ((st = device_ctx(ss->device, &ctx))) return st;
-        const bool coop = tune.strategy == 2 ||
-                          (tune.strategy == 0 && n_per_stream * es >= coop_min_bytes(count, ctx->cus));
-        if (coop) {
-            // GL lanes per stream, 64/GL streams per wave; each lane takes
-            // 64/GL or 2*64/GL pieces of 128 bytes per chunk (a chunk is then
-            // 64 or 128 lines), whichever generates fewer values past the end
-            // of a row (the longer chunk on a tie).  A row's line-aligned
-            // part is n values, or about n - tv/2 when rows start anywhere.
-            const bool rows_aligned = (uintptr_t)d_out % 128 == 0 && (n_per_stream * es) % 128 == 0;
-            const int GL = tune.coop_lanes ? tune.coop_lanes
-                                           : coop_auto_lanes(count, n_per_stream * es, rows_aligned, ctx->cus);
-            const uint64_t tv = 128 / es;
-            const uint64_t nh_min = 64 / GL, nh_max = 2 * nh_min;
-            const uint64_t body = rows_aligned || n_per_stream <= tv ? n_per_stream : n_per_stream - tv / 2;
-            const uint64_t ch_min = (uint64_t)GL * nh_min * tv, ch_max = 2 * ch_min;
-            const uint64_t gen_min = (body + ch_min - 1) / ch_min * ch_min;
-            const uint64_t gen_max = (body + ch_max - 1) / ch_max * ch_max;
-            const uint64_t nh = gen_max <= gen_min ? nh_max : nh_min;
-            const int L = (int)(nh * tv);
-            if (L % 16 || L < 16 || L > 512) return set_error(MRG_EINVAL, "no lane table for L = %d", L);
-            fl.kernel = 1;
-            fl.L = L;
-            fl.lanes = GL;
-            fl.lane_tab = ctx->d_lane_tab + mrg::lane_table(L) * 64 * 18;
-            fl.tabs = ctx->d_lane_tab;
-            fl.table = ctx->d_table;
-            // resident workgroups stride over the stream groups, or one per group
-            const uint64_t groups = (count + (64 / GL) - 1) / (64 / GL);
-            const uint64_t cap = tune.coop_wgs_per_cu ? (uint64_t)ctx->cus * tune.coop_wgs_per_cu
-                                                      : ((uint64_t)1 << 31) - 1;
-            fl.grid = (unsigned)(groups < cap ? groups : cap);
-            fl.order = tune.coop_order;
-            // the bulk case: rows on lines, whole chunks, a group's rows
-            // addressable with 32-bit offsets
-            fl.whole = rows_aligned && n_per_stream % ((uint64_t)GL * L) == 0 &&
-                       (uint64_t)(64 / GL) * n_per_stream * es < ((uint64_t)1 << 32);
-            // automatic choice: a row under 16 KiB that is not whole chunks on
-            // lines is one cut chunk for this writer (values drawn past the
-            // row's end, one piece per flush), and with enough streams for one
-            // wave of them on every SIMD (2^16 on 256 CUs) the lane-per-stream
-            // writer is the faster one (uint32 rows of 3000: 190 us against
-            // 210-235 for 2^16 streams, 4.0-4.5 against 3.4 TB/s for 2^17 and
-            // more; of 4000: 228 against 264-276 us, 4.2-4.4 against 3.6-3.7
-            // TB/s; from 4500 values this writer leads, 4.7-4.8 against
-            // 4.0-4.5).  With fewer streams this writer keeps the launch short
-            // (49152 x 3000: 160 against 177 us).
-            if (tune.strategy == 0 && !fl.whole && n_per_stream * es < 16 * 1024 &&
-                count >= (uint64_t)ctx->cus * 256)
-                fl = mrg::FillLaunch();
-        }
-        // lane per stream, rows of whole 4 KiB on lines: two lanes per stream
-        // (fill_sm_kernel's HALVES; other row lengths lose by it: 131072 x 1536
-        // float32 171 -> 189 us, x 512 59 -> 62)
-        if (tune.strategy == 0 && fl.kernel == 0 && tune.tile_bytes == 0 &&
-            (uintptr_t)d_out % 128 == 0 && n_per_stream * es % 4096 == 0) {
-            fl.kernel = 4;
-            const uint64_t e[3] = {n_per_stream / 2, 0, 0};
-            fl.end = jump_matrices(e);
-        }
-        // few streams: a wave per stream leaves the chip idle and takes 2.3 us
-        // per 4096 uint32 of a row whatever the launch writes, so rows are cut
-        // into blocks (256 x 16384 uint32 15.1 -> 11.2 us, 64 x 2^20 590 -> 49).
-        // With two waves or more per CU the rows have to be long enough for the
-        // blocks' jumps (512 x 10000 15.7 -> 16.9, 512 x 40000 35.4 -> 28.4),
-        // and with a wave per SIMD the rows alone fill the chip (1000 x 65536
-        // 50 -> 56).
-        if (tune.strategy == 0 &&
-            ((count <= (uint64_t)ctx->cus && n_per_stream * es >= 16 * 1024) ||
-             (count <= (uint64_t)ctx->cus * 2 && n_per_stream * es >= 64 * 1024))) {
-            fl = mrg::FillLaunch();
-            split_rows(&fl, ctx, ss->n, count, n_per_stream, es);
-            hipError_t e = run_split(ss, fl, tune, first, count, n_per_stream, dtype, d_out,
-                                     (hipStream_t)stream);
-            return e == hipSuccess ? MRG_OK : hip_error(e, "fill kernel launch");
-        }
-    }
-    if (layout == MRG_INTERLEAVED && tune.strategy == 0) {
-        DevCtx *ctx;
-        if ((st = device_ctx(ss->device, &ctx))) return st;
-        split_steps(&fl, ctx, ss->n, count, n_per_stream, es);
-    }
-    hipError_t e = mrg::launch_fill(ss->d_planes, ss->n, first, count, n_per_stream, (int)dtype,
-                                    (int)layout, d_out, fl, tune, (hipStream_t)stream);
-    if (e == hipSuccess && fl.kernel == 3 && !fl.move)
-        e = mrg::launch_jump_uniform(ss->d_planes, ss->n, first, count, fl.end, (hipStream_t)stream);
+    DevCtx *ctx;
+    if ((st = device_ctx(ss->device, &ctx))) return st;
+    const mrg::FillLaunch fl = plan_fill(tune, ctx->cus, ss->n, count, n_per_stream, es, &layout,
+                                         (uintptr_t)d_out);
+    hipError_t e = run_fill(ss, ctx, fl, tune, first, count, n_per_stream, dtype, layout, d_out,
+                            (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "fill kernel launch");
 }
 
@@ -812,55 +861,67 @@ mrg_status mrg_fill_leapfrog(mrg_streamset ss, uint64_t s, uint64_t players,
     DevCtx *ctx;
     if ((st = device_ctx(ss->device, &ctx))) return st;
     const mrg::FillTuning tune = tuning();
-    const uint64_t en[3] = {N, 0, 0};
-    // with one player or one card per player both layouts are the stream in order
-    if (layout == MRG_INTERLEAVED || players == 1 || per_player == 1) {
+    mrg::LeapArgs A;
+    mrg::FillLaunch fl;
+    if (plan_leap(ctx->cus, ss->n, players, per_player, es, layout, &fl, &A)) {
         // the stream's outputs in order: one row in blocks
-        mrg::FillLaunch fl;
-        split_rows(&fl, ctx, ss->n, 1, N, es);
-        hipError_t e = run_split(ss, fl, tune, s, 1, N, dtype, d_out, (hipStream_t)stream);
+        hipError_t e = run_fill(ss, ctx, fl, tune, s, 1, N, dtype, MRG_STREAM_MAJOR, d_out,
+                                (hipStream_t)stream);
         return e == hipSuccess ? MRG_OK : hip_error(e, "leapfrog kernel launch");
     }
-    // each player's cards in a row: items of KB = min(K, 64) card columns
-    // x T players (R = 64 / KB lanes per column, Ts = T / R players
-    // each), T chosen for about 4 items per resident wave, at least 32
-    // players per lane (65536 players of 52 cards: 256 to a lane left 256
-    // waves and 20.9 us, 32 are 11.6 us, 16 no faster: 14.0)
-    const uint64_t slots = (uint64_t)ctx->cus * 16;  // resident waves
-    mrg::LeapArgs A;
-    A.P = players;
-    A.K = per_player;
-    A.KB = (int)(per_player < 64 ? per_player : 64);
-    A.R = 64 / A.KB;
-    const uint64_t nkb = (per_player + A.KB - 1) / A.KB;
-    const uint64_t target = 4 * slots;
-    uint64_t Ts = (players + A.R - 1) / A.R;
-    if (nkb < target) {
-        const uint64_t segs = (target + nkb - 1) / nkb;
-        Ts = (players + segs * A.R - 1) / (segs * A.R);
-        if (Ts < 32) Ts = 32;
-    }
-    const uint64_t ts_max = (players + A.R - 1) / A.R;
-    if (Ts > ts_max) Ts = ts_max;
-    A.Ts = Ts;
-    A.T = Ts * A.R;
-    A.nseg = (players + A.T - 1) / A.T;
-    A.items = nkb * A.nseg;
-    // 63 * players and T - Ts as 192-bit exponents
-    const unsigned __int128 e63 = (unsigned __int128)players * 63u;
-    const uint64_t ew[3] = {(uint64_t)e63, (uint64_t)(e63 >> 64), 0};
-    A.J63 = jump_matrices(ew);
-    const uint64_t es_[3] = {A.T - A.Ts, 0, 0};
-    A.Jseg = jump_matrices(es_);
-    A.end = jump_matrices(en);  // the stream moves past the N outputs dealt
-    A.move = mrg::ticket_pitch(ss->n) != 0;
-    const uint64_t waves = A.items < slots ? A.items : slots;
-    hipError_t e = mrg::launch_leap(ss->d_planes, ss->n, s, (int)dtype, A,
-                                    (unsigned)waves, ctx->d_table, d_out,
+    hipError_t e = mrg::launch_leap(ss->d_planes, ss->n, s, (int)dtype, A, ctx->d_table, d_out,
                                     tune.engine, (hipStream_t)stream);
     if (e == hipSuccess && !A.move)
         e = mrg::launch_jump_uniform(ss->d_planes, ss->n, s, 1, A.end, (hipStream_t)stream);
     return e == hipSuccess ? MRG_OK : hip_error(e, "leapfrog kernel launch");
+}
+
+mrg_status mrg_fill_route(uint64_t set_streams, uint64_t count, uint64_t n_per_stream,
+                          mrg_dtype dtype, mrg_layout layout, uint64_t out_offset, int32_t cus,
+                          mrg_route *route)
+{
+    if (!route) return set_error(MRG_EINVAL, "null argument");
+    if (!count || !n_per_stream || count > set_streams || cus < 1)
+        return set_error(MRG_ERANGE, "no such fill");
+    const uint64_t es = dtype == MRG_F64 ? 8 : 4;
+    const mrg::FillLaunch fl = plan_fill(tuning(), cus, set_streams, count, n_per_stream, es,
+                                         &layout, (uintptr_t)out_offset);
+    *route = mrg_route();
+    route->kernel = layout == MRG_INTERLEAVED && fl.kernel != 3 ? MRG_ROUTE_STEPS : fl.kernel;
+    const bool parts = fl.kernel == 2 || fl.kernel == 3;
+    route->lanes = fl.kernel == 1 ? fl.lanes : fl.kernel == 2 ? 64 : fl.kernel == 4 ? 2 : 1;
+    route->parts = parts ? fl.nblk : 1;
+    route->part_values = parts ? fl.B : n_per_stream;
+    route->chunk_values = fl.kernel == 1 || fl.kernel == 2 ? (uint32_t)(fl.L * route->lanes) : 0;
+    route->moves = !parts || fl.move;
+    return MRG_OK;
+}
+
+mrg_status mrg_leapfrog_route(uint64_t set_streams, uint64_t players, uint64_t per_player,
+                              mrg_dtype dtype, mrg_layout layout, int32_t cus, mrg_route *route)
+{
+    if (!route) return set_error(MRG_EINVAL, "null argument");
+    if (!players || !per_player || !set_streams || cus < 1) return set_error(MRG_ERANGE, "no such deal");
+    mrg::LeapArgs A;
+    mrg::FillLaunch fl;
+    *route = mrg_route();
+    if (plan_leap(cus, set_streams, players, per_player, dtype == MRG_F64 ? 8 : 4, layout, &fl, &A)) {
+        route->kernel = fl.kernel;
+        route->lanes = 64;
+        route->parts = fl.nblk;
+        route->part_values = fl.B;
+        route->chunk_values = (uint32_t)(fl.L * 64);
+        route->moves = fl.move;
+    } else {
+        route->kernel = MRG_ROUTE_DEAL;
+        route->lanes = A.KB * A.R;
+        route->parts = A.items;
+        route->part_values = A.Ts;
+        route->waves = A.waves;
+        route->waves_per_group = A.per_group;
+        route->moves = A.move;
+    }
+    return MRG_OK;
 }
 
 mrg_status mrg_get_states(mrg_streamset ss, uint64_t first, uint64_t count, uint32_t *h_out,

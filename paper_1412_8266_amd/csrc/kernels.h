@@ -103,14 +103,15 @@ struct LeapArgs {
     int KB = 64, R = 1;
     JumpMatrices J63 = {};   // A^(63*P): to the next column block (R = 1)
     JumpMatrices Jseg = {};  // A^(T - Ts): to the next segment (R > 1)
+    unsigned waves = 0, per_group = 1;  // waves, and how many to a workgroup
     int move = 1;            // the last workgroup to read the state moves it (ticket)
     JumpMatrices end = {};   // A^(P*K): the stream's state after the deal
 };
 
 // One stream (plane index sidx) dealt to players, each player's cards in a row.
 hipError_t launch_leap(uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
-                       const LeapArgs &A, unsigned waves, const uint32_t *table, void *out,
-                       int engine, hipStream_t st);
+                       const LeapArgs &A, const uint32_t *table, void *out, int engine,
+                       hipStream_t st);
 
 // Philox4x32-10 stream sets (philox.hip): states (position, id, key).
 hipError_t launch_philox_init(uint32_t *planes, uint64_t plane_stride, uint64_t count,

@@ -655,11 +655,10 @@ hipError_t launch_ticket_reset(uint32_t *planes, uint64_t n, uint64_t first, uin
 
 template <class G>
 static hipError_t launch_leap_g(uint32_t *planes, uint64_t plane_stride, uint64_t sidx,
-                                int dtype, const LeapArgs &A, unsigned waves,
-                                const uint32_t *table, unsigned char *o, hipStream_t st)
+                                int dtype, const LeapArgs &A, const uint32_t *table,
+                                unsigned char *o, hipStream_t st)
 {
-    const unsigned per = waves <= 256 ? 1 : waves >= 4096 ? 16 : (waves + 255) / 256;
-    const dim3 g((waves + per - 1) / per), b(per * 64);
+    const dim3 g((A.waves + A.per_group - 1) / A.per_group), b(A.per_group * 64);
     if (dtype == 0)
         hipLaunchKernelGGL((fill_leap_kernel<0, G>), g, b, 0, st, planes, plane_stride, sidx, A, o, table);
     else if (dtype == 1)
@@ -670,12 +669,12 @@ static hipError_t launch_leap_g(uint32_t *planes, uint64_t plane_stride, uint64_
 }
 
 hipError_t launch_leap(uint32_t *planes, uint64_t plane_stride, uint64_t sidx, int dtype,
-                       const LeapArgs &A, unsigned waves, const uint32_t *table, void *out,
-                       int engine, hipStream_t st)
+                       const LeapArgs &A, const uint32_t *table, void *out, int engine,
+                       hipStream_t st)
 {
     unsigned char *o = (unsigned char *)out;
-    if (engine == 1) return launch_leap_g<GenF>(planes, plane_stride, sidx, dtype, A, waves, table, o, st);
-    return launch_leap_g<GenI>(planes, plane_stride, sidx, dtype, A, waves, table, o, st);
+    if (engine == 1) return launch_leap_g<GenF>(planes, plane_stride, sidx, dtype, A, table, o, st);
+    return launch_leap_g<GenI>(planes, plane_stride, sidx, dtype, A, table, o, st);
 }
 
 }  // namespace mrg
