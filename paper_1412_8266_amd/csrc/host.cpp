@@ -409,8 +409,30 @@ void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, ui
 // streams (4096 x 4096 26.6 against 23.0 us, eight 33.6), segments of 32
 // steps no faster, and 65536 binary64 streams in two segments slower (x 1000
 // 98.6 -> 105 us).
-void split_steps(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es)
+//
+// Segments write as many places at once, which the memory takes worse the more
+// streams there are and the more their rows share lines, so with many streams
+// the segments have to pay for it.  uint32, up to half a wave of streams per
+// SIMD they do (32768 x 4096 184 -> 100 us on lines, 168 -> 155 off them); up
+// to 40960 on lines and from 192 steps on (36000 x 1000 46 -> 34; off lines
+// x 4096 171 -> 197, x 128 9.2 -> 9.9); beyond, only near a wave per SIMD, on
+// lines and for long fills (65536 x 1000 53 -> 51, off lines 72 -> 76; 52000 x
+// 4096 1.04 times).  binary64: up to 18432 always (18001 x 4096 off lines 0.92
+// times, 20001 1.02, 24000 x 1000 47 -> 52), up to 28672 on lines (28000 x 4096
+// 0.97 times, 30000 1.04), up to 32768 for short fills (x 512 0.90 times).
+bool steps_cut(int cus, uint64_t count, uint64_t n, uint64_t es, bool lined)
 {
+    const uint64_t c = (uint64_t)cus;
+    if (es == 4)
+        return count <= c * 128 || (lined && n >= 192 && count <= c * 160) ||
+               (lined && n >= 1000 && count >= c * 224);
+    return count <= c * 72 || (count <= c * 128 && (n <= 512 || (lined && (n < 1000 || count <= c * 112))));
+}
+
+void split_steps(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es,
+                 bool lined)
+{
+    if (!steps_cut(cus, count, n, es, lined)) return;
     const uint64_t lanes = (uint64_t)cus * 2048 / es;
     uint64_t nseg = lanes / count;
     if (nseg > n / 64) nseg = n / 64;
@@ -508,7 +530,8 @@ mrg::FillLaunch plan_fill(const mrg::FillTuning &tune, int cus, uint64_t set_n, 
         }
     }
     if (*layout == MRG_INTERLEAVED && tune.strategy == 0)
-        split_steps(&fl, cus, set_n, count, n_per_stream, es);
+        split_steps(&fl, cus, set_n, count, n_per_stream, es,
+                    out % 128 == 0 && count * es % 128 == 0);
     return fl;
 }
 

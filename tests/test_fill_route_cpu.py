@@ -54,3 +54,25 @@ def test_refused():
             _abi.mrg_fill_route(*args, U32, ROWS)
     with pytest.raises(_abi.MRGError):
         _abi.mrg_leapfrog_route(1, 0, 4, U32, ROWS)
+
+
+# (streams, steps, dtype, offset, cut): both sides of each line of the rule that
+# cuts interleaved streams into segments
+STEP_RULE = [
+    (64, 127, U32, 0, False), (64, 128, U32, 0, True), (32768, 4096, U32, 20, True),
+    (32800, 4096, U32, 20, False), (32800, 191, U32, 0, False), (32800, 192, U32, 0, True),
+    (40960, 1000, U32, 0, True), (40992, 1000, U32, 0, False), (40959, 1000, U32, 0, False),
+    (57344, 999, F32, 0, False), (57344, 1000, F32, 0, True), (65536, 4096, F32, 0, True),
+    (65536, 4096, F32, 20, False), (65535, 4096, F32, 0, False), (65537, 4096, U32, 0, False),
+    (18432, 4096, F64, 24, True), (18433, 4096, F64, 24, False), (18448, 4096, F64, 0, True),
+    (28672, 4096, F64, 0, True), (28688, 4096, F64, 0, False), (32768, 999, F64, 0, True),
+    (32768, 1000, F64, 0, False), (32768, 512, F64, 8, True), (32768, 513, F64, 8, False),
+    (32784, 512, F64, 0, False)]
+
+
+@pytest.mark.parametrize("count,n,dtype,off,cut", STEP_RULE)
+def test_interleaved_streams_are_cut_where_it_pays(count, n, dtype, off, cut):
+    r = steps(count, n, dtype, off)
+    assert r.kernel == (PARTS if cut else STEPS)
+    if cut:
+        assert r.part_values % 16 == 0 and (r.parts - 1) * r.part_values < n <= r.parts * r.part_values

@@ -86,6 +86,11 @@ STEPS = [(2, 40000, 0, 1), (70, 20000, 2, 0), (1, 64, 0, 0), (1, 70001, 1, 3), (
          (32768, 129, 2, 0), (32769, 129, 2, 0), (65536, 145, 0, 0), (65537, 145, 0, 0)]
 
 
+# both sides of the lines where many streams stop being cut
+STEPS += [(32800, 192, 0, 0), (32800, 192, 0, 5), (57344, 1000, 1, 0), (65536, 1001, 0, 0),
+          (18432, 700, 2, 1), (28672, 1000, 2, 0), (28688, 1000, 2, 0), (32768, 520, 2, 0)]
+
+
 @pytest.mark.parametrize("engine", [1, 0], ids=["f64", "int"])
 @pytest.mark.parametrize("count,n,dtype,off", STEPS)
 def test_steps_in_segments(mg, count, n, dtype, off, engine):
