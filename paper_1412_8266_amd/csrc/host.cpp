@@ -394,10 +394,7 @@ void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, ui
     fl->grid = (unsigned)(count * fl->nblk);
     const uint64_t e[3] = {n, 0, 0};
     fl->end = jump_matrices(e);
-    // up to 256 arrivals per ticket line (5 us of them in a row) the fill moves
-    // its streams itself, which spares a launch; beyond, a launch follows
-    const uint64_t per_line = mrg::ticket_pitch(set_n) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
-    fl->move = mrg::ticket_pitch(set_n) && fl->nblk * per_line <= 256;
+    fl->move = mrg::parts_move(set_n, count, fl->nblk, false);
 }
 
 // Interleaved fill in segments of each stream (fill_il_seg_kernel): as many as
@@ -443,8 +440,7 @@ void split_steps(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, u
     fl->kernel = 3;
     const uint64_t e[3] = {n, 0, 0};
     fl->end = jump_matrices(e);
-    // arrivals at a stream's ticket (as in split_rows)
-    fl->move = mrg::ticket_pitch(set_n) && fl->nblk <= 256;
+    fl->move = mrg::parts_move(set_n, count, fl->nblk, true);
 }
 
 // How an MRG32k3a fill is launched under `tune` on a device of `cus` compute

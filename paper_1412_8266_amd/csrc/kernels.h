@@ -26,6 +26,20 @@ __host__ __device__ constexpr uint64_t ticket_of(uint64_t n, uint64_t i)
 {
     return 6 * n + i * ticket_pitch(n);
 }
+// Whether the parts of a fill of `count` streams of a set of n count themselves
+// in, and the last one moves its stream (a single part does so without a
+// ticket); else a launch follows (1.5-4 us).  The
+// arrivals at one line must not take longer.  One per wave: 256 a line (5 us in
+// a row).  One per lane, up to 32 of them in a step of a wave: 256 a ticket, and
+// 2048 a line, 4096 where the fill is long enough to hide them (segments of 16 x
+// 16384 uint32 of a set with packed tickets 15.8 us at 4096 a line, 9.7 with a
+// launch; 32 x 4096 7.9 at 2048 and 7.9-8.4; 1024 x 16384 20.3 at 4096 and 21.4).
+constexpr bool parts_move(uint64_t n, uint64_t count, uint64_t parts, bool per_lane)
+{
+    const uint64_t line = ticket_pitch(n) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
+    const uint64_t most = per_lane && line > 1 ? (count < 512 ? 2048 : 4096) : 256;
+    return parts == 1 || (ticket_pitch(n) && parts <= 256 && parts * line <= most);
+}
 constexpr uint64_t set_words(uint64_t n) { return 6 * n + n * ticket_pitch(n); }
 
 struct InitSeed { uint32_t w[6]; };

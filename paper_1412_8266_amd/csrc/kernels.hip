@@ -387,7 +387,8 @@ fill_split_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t
         uint32_t w[6];
         load_state(planes, plane_stride, first + s, w);
         uint32_t arrived = 0;
-        if (move && lane == 0) arrived = arrive(planes + ticket_of(plane_stride, first + s), nblk, w);
+        if (move && nblk > 1 && lane == 0)
+            arrived = arrive(planes + ticket_of(plane_stride, first + s), nblk, w);
         unsigned char *row = out + s * n * ES;
         const uint64_t hv = head_values<ES>(row, n);
         const uint64_t v0 = q ? hv + q * B : 0;

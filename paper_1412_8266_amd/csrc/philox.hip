@@ -416,11 +416,11 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
         // binary64: 65536 x 1000 in four segments 89 -> 110 us)
         const uint64_t lanes = (uint64_t)cus * (ES == 8 ? 256 : 1024), nb = (n + 6) / 4;
         uint64_t nseg = lanes / count < nb / 16 ? lanes / count : nb / 16;
-        if (nseg > 256) nseg = 256;  // arrivals per ticket line
+        if (nseg > 256) nseg = 256;  // arrivals per ticket
         if (nseg < 1) nseg = 1;
         const uint64_t sb = (nb + nseg - 1) / nseg;
         nseg = (nb + sb - 1) / sb;
-        const int move = nseg == 1 || ticket_pitch(plane_stride);
+        const int move = parts_move(plane_stride, count, nseg, true);
         hipLaunchKernelGGL((philox_il_kernel<DT>), dim3(grid256(count * nseg)), dim3(256), 0, st,
                            planes, plane_stride, first, count, n, (uint32_t)nseg, sb, move, o);
         hipError_t e = hipGetLastError();
@@ -476,8 +476,7 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
             return e;
         }
     }
-    const uint64_t per_line = ticket_pitch(plane_stride) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
-    const int move = nrun == 1 || (ticket_pitch(plane_stride) && nrun * per_line <= 256);
+    const int move = parts_move(plane_stride, count, nrun, false);
     hipLaunchKernelGGL((philox_runs_kernel<DT>), dim3((unsigned)(wgs < cap ? wgs : cap)), dim3(256), 0, st,
                        planes, plane_stride, first, count, n, (uint32_t)rw,
                        (uint32_t)nrun, (uint32_t)(per * 64), move, o);

@@ -56,6 +56,23 @@ def test_refused():
         _abi.mrg_leapfrog_route(1, 0, 4, U32, ROWS)
 
 
+def test_streams_move_in_the_fill_unless_arrivals_queue():
+    """At most 256 arrivals a ticket; on a line that 32 tickets share, 256 by
+    waves and 2048 (4096 from 512 streams on) by lanes; none without tickets."""
+    # own lines (4096 streams and fewer), packed tickets, no tickets
+    for streams, n, want in ((4096, 16384, 1), (4096, 65536, 0), (4097, 2048, 1), (4097, 16384, 0),
+                             (1 << 20, 2048, 1), ((1 << 20) + 1, 2048, 0)):
+        r = steps(64, n, streams=streams)
+        assert r.kernel == PARTS and r.moves == want, (streams, n, r.parts)
+    assert steps(1024, 8192, streams=5000).moves == 1      # 128 segments
+    assert steps(300, 8192, streams=5000).moves == 0
+    for streams, want in ((4096, 1), (4097, 0)):
+        r = rows(40, 1 << 16, streams=streams)
+        assert r.kernel == BLOCKS and 8 < r.parts <= 256 and r.moves == want
+    assert rows(1, 1 << 16, streams=1 << 20).moves == 1
+    assert rows(1, 1 << 16, streams=(1 << 20) + 1).moves == 0
+
+
 # (streams, steps, dtype, offset, cut): both sides of each line of the rule that
 # cuts interleaved streams into segments
 STEP_RULE = [

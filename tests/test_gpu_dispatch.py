@@ -148,8 +148,9 @@ def test_sets_hold_what_their_fills_need(mg):
 # segments, a deal, Philox runs and segments; both move their streams
 @pytest.mark.parametrize("streams", [1 << 20, (1 << 20) + 1])
 @pytest.mark.parametrize("generator,count,n,layout", [
-    ("mrg32k3a", 3, 20001, 0), ("mrg32k3a", 100, 1000, 1), ("mrg32k3a", 1, 9, 2),
-    ("philox", 3, 70001, 0), ("philox", 40, 4001, 1)])
+    ("mrg32k3a", 3, 20001, 0), ("mrg32k3a", 1, 2000, 0), ("mrg32k3a", 2, 4100, 0), ("mrg32k3a", 100, 1000, 1), ("mrg32k3a", 1, 9, 2),
+    ("mrg32k3a", 33, 8193, 1), ("philox", 3, 70001, 0), ("philox", 40, 4001, 1),
+    ("philox", 40, 20001, 1)])
 def test_ranges_of_sets_with_and_without_tickets(mg, streams, generator, count, n, layout):
     with mg.StreamSet(streams, master_seed=3, generator=generator) as ss:
         first = streams - count - 1
