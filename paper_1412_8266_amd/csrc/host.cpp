@@ -373,21 +373,30 @@ mrg::JumpMatrices jump_matrices(const uint64_t e[3])
     return J;
 }
 
-// Rows in blocks of a wave each (fill_split_kernel): about 16 blocks per
-// compute unit in all (two rounds of the waves that are resident), each a
-// whole number of 64-lane chunks -- of 64 KiB (256 uint32 per lane and start
-// state) when the blocks are that long, else of 16 or 8 KiB -- and at most 256
-// KiB (one stream of 2^32 uint32 in order: 2 MiB blocks 2 % slower).
+// Rows in blocks of a wave each (fill_split_kernel), by the bytes of the fill
+// (in order, one stream): blocks of one 8 KiB chunk up to 12 MiB, where the
+// blocks have to reach all CUs (8 MiB of uint32: 9.3 us, in blocks of 16 KiB
+// 9.6, of 64 KiB 14.9); of one 16 KiB chunk up to 48 MiB (16 MiB 11.2 us, in 8
+// KiB 12.2; 27 MiB 13.7 and 16.7, in 64 KiB 17.4), binary64 up to 192 MiB (128
+// MiB 26.7 us, in 64 KiB 28.0; 512 x 40000 37, 42); then of 64 KiB chunks (256
+// uint32 per lane and start state; 64 MiB 18.6 us, in 16 KiB 20.0, 256 MiB 46.1
+// and 58.9), about 16 blocks per compute unit (two rounds of the waves that are
+// resident) of at most 256 KiB (2^32 uint32: 2 MiB blocks 2 % slower).  Lanes
+// stage one piece per flush, for four waves per SIMD (32 MiB 14.6 us, with two
+// pieces and half the waves 15.6), two where memory is the bound: more than 256
+// MiB (1 GiB of uint32 194 us, with one 206; 256 MiB 50.0 and 46.1) and 64 KiB
+// chunks of binary64 (256 MiB 45.8 us, with one 50.6).
 void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es)
 {
     const uint64_t row = n * es, want = row / 16 * count / (uint64_t)cus;
-    const uint64_t unit = want >= 65536 ? 65536 : want >= 16384 ? 16384 : 8192;
-    uint64_t bb = want / unit * unit;
+    const uint64_t unit = want < 3072 ? 8192 : want < (es == 8 ? 49152 : 12288) ? 16384 : 65536;
+    uint64_t bb = unit == 65536 ? want / unit * unit : unit;
     bb = bb < unit ? unit : bb > 262144 ? 262144 : bb;
     // fewer blocks than 2^32 per row, and than 2^31 workgroups in all
     while (row / bb >= ((uint64_t)1 << 31) / count) bb *= 2;
     fl->kernel = 2;
     fl->L = (int)(unit / 64 / es);
+    fl->pieces = unit == 65536 && (es == 8 || want > 65536) ? 2 : 1;
     fl->B = bb / es;
     // a remainder under an eighth of a block goes to the last block
     fl->nblk = (uint32_t)(n / fl->B + (n % fl->B > fl->B / 8 || n < fl->B));
@@ -512,9 +521,9 @@ mrg::FillLaunch plan_fill(const mrg::FillTuning &tune, int cus, uint64_t set_n, 
         }
         // few streams: a wave per stream leaves the chip idle and takes 2.3 us
         // per 4096 uint32 of a row whatever the launch writes, so rows are cut
-        // into blocks (256 x 16384 uint32 15.1 -> 11.2 us, 64 x 2^20 590 -> 49).
+        // into blocks (256 x 16384 uint32 13.8 -> 8.9 us, 64 x 2^20 730 -> 58).
         // With two waves or more per CU the rows have to be long enough for the
-        // blocks' jumps (512 x 10000 15.7 -> 16.9, 512 x 40000 35.4 -> 28.4),
+        // blocks' jumps (512 x 10000 15.7 -> 16.9, 512 x 40000 33.7 -> 23.1),
         // and with a wave per SIMD the rows alone fill the chip (1000 x 65536
         // 50 -> 56).  A key of the wave-per-stream writer that is set keeps it.
         const bool asked = tune.coop_lanes || tune.coop_wgs_per_cu || tune.coop_order;

@@ -92,6 +92,7 @@ struct FillLaunch {
     // 128-byte line on, a wave each; the streams then move by n (end = A^n)
     uint64_t B = 0;
     uint32_t nblk = 0;
+    int pieces = 1;                     // 128-byte pieces a lane stages per flush
     int move = 0;                       // the last block to read a state moves it (tickets)
     JumpMatrices end = {};
 };

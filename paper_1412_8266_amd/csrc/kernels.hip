@@ -366,8 +366,11 @@ fill_coop_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t 
 // the states are left to a launch after this one.  Each XCD takes one
 // contiguous range of blocks (one stream in order: 4 % faster than the
 // chunked order of the stream-major fill).
-template <int DT, int L, class G>
-__global__ void __launch_bounds__(64, (coop_pieces<DT, L>() == 2 ? 2 : 4))
+//
+// NP: pieces that members stage per flush; with one, four waves per SIMD, with
+// two, longer runs of lines (FillLaunch::pieces).
+template <int DT, int L, class G, int NP>
+__global__ void __launch_bounds__(64, (NP == 2 ? 2 : 4))
 fill_split_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
                   uint64_t count, uint64_t n, uint64_t B, uint32_t nblk,
                   unsigned char *__restrict__ out, int move, JumpMatrices J,
@@ -375,7 +378,6 @@ fill_split_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t
                   const uint32_t *__restrict__ table)
 {
     constexpr int ES = Elem<DT>::size;
-    constexpr int NP = coop_pieces<DT, L>();
     __shared__ __attribute__((aligned(16))) unsigned char lds[64 * (NP * 128 + 16)];
     const int lane = threadIdx.x;
     uint32_t m[18];
@@ -588,13 +590,14 @@ static hipError_t launch_fill_g(uint32_t *planes, uint64_t plane_stride, uint64_
     } else if (fl.kernel == 2) {
         constexpr int TV = 128 / Elem<DT>::size;
         const dim3 grid(fl.grid), block(64);
-#define MRG_SPLIT(L)                                                                            \
-    hipLaunchKernelGGL((fill_split_kernel<DT, L, G>), grid, block, 0, st, planes, plane_stride,  \
-                       first, count, n, fl.B, fl.nblk, o, fl.move, fl.end, fl.lane_tab,       \
-                       fl.tabs, fl.table)
-        if (fl.L == TV) MRG_SPLIT(TV);
-        else if (fl.L == 2 * TV) MRG_SPLIT(2 * TV);
-        else if (fl.L == 8 * TV) MRG_SPLIT(8 * TV);
+#define MRG_SPLIT(L, NP)                                                                        \
+    hipLaunchKernelGGL((fill_split_kernel<DT, L, G, NP>), grid, block, 0, st, planes,            \
+                       plane_stride, first, count, n, fl.B, fl.nblk, o, fl.move, fl.end,         \
+                       fl.lane_tab, fl.tabs, fl.table)
+        if (fl.L == TV && fl.pieces == 1) MRG_SPLIT(TV, 1);
+        else if (fl.L == 2 * TV && fl.pieces == 1) MRG_SPLIT(2 * TV, 1);
+        else if (fl.L == 8 * TV && fl.pieces == 1 && DT != 2) MRG_SPLIT(8 * TV, (DT == 2 ? 2 : 1));
+        else if (fl.L == 8 * TV && fl.pieces == 2) MRG_SPLIT(8 * TV, 2);
         else return hipErrorInvalidValue;
 #undef MRG_SPLIT
     } else if (fl.kernel == 4) {

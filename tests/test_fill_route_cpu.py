@@ -93,3 +93,21 @@ def test_interleaved_streams_are_cut_where_it_pays(count, n, dtype, off, cut):
     assert r.kernel == (PARTS if cut else STEPS)
     if cut:
         assert r.part_values % 16 == 0 and (r.parts - 1) * r.part_values < n <= r.parts * r.part_values
+
+
+# (MiB of one stream in order, dtype, block bytes, chunk bytes): both sides of
+# the block sizes' lines
+ORDER_RULE = [(1, U32, 8, 8), (11, U32, 8, 8), (12, U32, 16, 16), (27, U32, 16, 16), (32, F64, 16, 16),
+              (47, F32, 16, 16), (48, U32, 64, 64), (191, F64, 16, 16), (192, F64, 64, 64), (256, U32, 64, 64),
+              (512, U32, 128, 64), (4096, F32, 256, 64)]
+
+
+@pytest.mark.parametrize("mib,dtype,block,chunk", ORDER_RULE)
+def test_blocks_of_a_stream_in_order(mib, dtype, block, chunk):
+    es = 8 if dtype == F64 else 4
+    n = (mib << 20) // es
+    for r in (_abi.mrg_leapfrog_route(1, n // 4, 4, dtype, ILV), rows(1, n, dtype), steps(1, n, dtype),
+              rows(64, n // 64, dtype)):
+        assert r.kernel == BLOCKS
+        assert (r.part_values * es, r.chunk_values * es) == (block << 10, chunk << 10)
+        assert (r.parts - 1) * r.part_values <= n

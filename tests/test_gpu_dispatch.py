@@ -68,6 +68,11 @@ BLOCKS = [(1, 4096, 0, 0), (1, 4097, 0, 31), (3, 8193, 1, 1), (2, 6144, 2, 0), (
           (256, 4100, 0, 7), (257, 4100, 0, 7), (512, 16400, 0, 9), (513, 16400, 0, 0)]
 
 
+# both sides of 12 and 48 MiB in all, where the blocks and their chunks grow
+BLOCKS += [(1, (3 << 20) - 1, 0, 0), (1, 3 << 20, 0, 3), (5, (3 << 19) // 5 + 1, 2, 1), (1, (12 << 20) - 9, 1, 1),
+           (1, 12 << 20, 0, 0), (200, 70001, 0, 1), (1, 7 << 20, 2, 1), (40, 170001, 2, 1), (1, 25 << 20, 2, 3), (1, (64 << 20) + 999, 0, 0)]
+
+
 @pytest.mark.parametrize("engine", [1, 0], ids=["f64", "int"])
 @pytest.mark.parametrize("count,n,dtype,off", BLOCKS)
 def test_rows_in_blocks(mg, count, n, dtype, off, engine):
