@@ -373,30 +373,31 @@ mrg::JumpMatrices jump_matrices(const uint64_t e[3])
     return J;
 }
 
-// Rows in blocks of a wave each (fill_split_kernel), by the bytes of the fill
-// (in order, one stream): blocks of one 8 KiB chunk up to 12 MiB, where the
-// blocks have to reach all CUs (8 MiB of uint32: 9.3 us, in blocks of 16 KiB
-// 9.6, of 64 KiB 14.9); of one 16 KiB chunk up to 48 MiB (16 MiB 11.2 us, in 8
-// KiB 12.2; 27 MiB 13.7 and 16.7, in 64 KiB 17.4), binary64 up to 192 MiB (128
-// MiB 26.7 us, in 64 KiB 28.0; 512 x 40000 37, 42); then of 64 KiB chunks (256
-// uint32 per lane and start state; 64 MiB 18.6 us, in 16 KiB 20.0, 256 MiB 46.1
-// and 58.9), about 16 blocks per compute unit (two rounds of the waves that are
-// resident) of at most 256 KiB (2^32 uint32: 2 MiB blocks 2 % slower).  Lanes
-// stage one piece per flush, for four waves per SIMD (32 MiB 14.6 us, with two
-// pieces and half the waves 15.6), two where memory is the bound: more than 256
-// MiB (1 GiB of uint32 194 us, with one 206; 256 MiB 50.0 and 46.1) and 64 KiB
-// chunks of binary64 (256 MiB 45.8 us, with one 50.6).
+// Rows in blocks of a wave each (fill_split_kernel), by the bytes of the fill;
+// the figures are of one stream in order, uint32 unless said.  Blocks are to be
+// short enough to reach all SIMDs evenly, several to each, and long enough for
+// their jump:
+//   up to 12 MiB   8 KiB, one chunk (8 MiB 9.3 us, 16 KiB blocks 9.6)
+//   up to 48 MiB   16 KiB, one chunk (27 MiB 13.7 us, 8 KiB 16.7, 32 KiB 14.0)
+//   up to 192 MiB  32 KiB, two chunks (72 MB 22.9 us, 16 KiB 23.6, 64 KiB, just
+//                  over one to a SIMD, 28.9; 128 MiB 29.4, 32.5 and 28.2);
+//                  binary64 up to 320 MiB (260 MB 44.8 us, 64 KiB 45.2)
+//   up to 320 MiB  64 KiB, in chunks of 64 KiB: 256 uint32 per lane and start
+//                  state (260 MB 47.4 us, 32 KiB 52.9)
+//   beyond         the same with two pieces staged per flush, half the waves
+//                  and longer runs of lines (1.1 GB 204 us, with one piece 214);
+//                  128 KiB from 2 GiB on (4 GiB 763, 64 KiB 786, 2 MiB 2 % more)
 void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es)
 {
-    const uint64_t row = n * es, want = row / 16 * count / (uint64_t)cus;
-    const uint64_t unit = want < 3072 ? 8192 : want < (es == 8 ? 49152 : 12288) ? 16384 : 65536;
-    uint64_t bb = unit == 65536 ? want / unit * unit : unit;
-    bb = bb < unit ? unit : bb > 262144 ? 262144 : bb;
+    const uint64_t row = n * es, want = row / 16 * count / (uint64_t)cus;  // 16 per CU
+    const bool large = want >= (es == 8 ? 81920u : 49152u);
+    const uint64_t unit = want < 3072 ? 8192 : large ? 65536 : 16384;  // a chunk of 64 lanes
+    uint64_t bb = want < 3072 ? 8192 : want < 12288 ? 16384 : !large ? 32768 : want < 524288 ? 65536 : 131072;
     // fewer blocks than 2^32 per row, and than 2^31 workgroups in all
     while (row / bb >= ((uint64_t)1 << 31) / count) bb *= 2;
     fl->kernel = 2;
     fl->L = (int)(unit / 64 / es);
-    fl->pieces = unit == 65536 && (es == 8 || want > 65536) ? 2 : 1;
+    fl->pieces = want >= 81920 ? 2 : 1;
     fl->B = bb / es;
     // a remainder under an eighth of a block goes to the last block
     fl->nblk = (uint32_t)(n / fl->B + (n % fl->B > fl->B / 8 || n < fl->B));
@@ -555,9 +556,17 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     mrg::LeapArgs &A = *leap;
     // each player's cards in a row: items of KB = min(K, 64) card columns
     // x T players (R = 64 / KB lanes per column, Ts = T / R players
-    // each), T chosen for about 4 items per resident wave, at least 32
-    // players per lane (65536 players of 52 cards: 256 to a lane left 256
-    // waves and 20.9 us, 32 are 11.6 us, 16 no faster: 14.0)
+    // each), T chosen for about 4 items per resident wave, with at least 64
+    // players per lane, 32 where that leaves under four waves per CU (65536 x
+    // 52: with 256 18.4 us, with 32 10.6, with 16 14.0).  While the items at 64
+    // players do not fill the chip, up to 16 waves to a workgroup, which count
+    // themselves in together, and the stream moved in the kernel; then a wave
+    // to a workgroup, since the waves of one share a CU and write far apart, and
+    // a launch for the stream (65536 x 8000 uint32 439 us, in groups of 16 475;
+    // 8192 x 6000 43.4 and 45.8; 4096 x 2048 16.9 and 15.4).  Over 109 deals of
+    // 1 MB to 2 GB these rules took 1.03 times the best of 32 to 256 players per
+    // lane in groups of 1, 4 and 16 waves, 32 players and 16 waves for all 1.05,
+    // 256 players and one wave 1.40.
     const uint64_t slots = (uint64_t)cus * 16;  // resident waves
     A.P = players;
     A.K = per_player;
@@ -565,14 +574,21 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     A.R = 64 / A.KB;
     const uint64_t nkb = (per_player + A.KB - 1) / A.KB;
     const uint64_t target = 4 * slots;
-    uint64_t Ts = (players + A.R - 1) / A.R;
+    const uint64_t ts_max = (players + A.R - 1) / A.R;
+    const uint64_t at64 = nkb * ((ts_max + 63) / 64);
+    const bool few = at64 < (uint64_t)cus * 15;
+    const uint64_t ts_min = at64 < (uint64_t)cus * 4 ? 32 : 64;
+    uint64_t Ts = ts_max;
     if (nkb < target) {
         const uint64_t segs = (target + nkb - 1) / nkb;
         Ts = (players + segs * A.R - 1) / (segs * A.R);
-        if (Ts < 32) Ts = 32;
+        if (Ts < ts_min) Ts = ts_min;
     }
-    const uint64_t ts_max = (players + A.R - 1) / A.R;
     if (Ts > ts_max) Ts = ts_max;
+    // few segments are even ones, no shorter than 64 (76 players as 64 and 12 took
+    // 17.9 us, whole 16.0) and no longer than 32 (114 as 3 x 38 10.3 us, 4 x 29 8.5)
+    if (const uint64_t nseg = ts_min == 64 ? ts_max / Ts : (ts_max + Ts - 1) / Ts; nseg < 8)
+        Ts = (ts_max + nseg - 1) / nseg;
     A.Ts = Ts;
     A.T = Ts * A.R;
     A.nseg = (players + A.T - 1) / A.T;
@@ -586,8 +602,8 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     A.end = jump_matrices(en);  // the stream moves past the N outputs dealt
     // up to 16 waves a workgroup, for at most 256 arrivals at the ticket
     A.waves = (unsigned)(A.items < slots ? A.items : slots);
-    A.per_group = A.waves <= 256 ? 1 : A.waves >= 4096 ? 16 : (A.waves + 255) / 256;
-    A.move = mrg::ticket_pitch(set_n) != 0;
+    A.per_group = !few || A.waves <= 256 ? 1 : A.waves >= 4096 ? 16 : (A.waves + 255) / 256;
+    A.move = few && mrg::ticket_pitch(set_n);
     return false;
 }
 

@@ -97,9 +97,9 @@ def test_interleaved_streams_are_cut_where_it_pays(count, n, dtype, off, cut):
 
 # (MiB of one stream in order, dtype, block bytes, chunk bytes): both sides of
 # the block sizes' lines
-ORDER_RULE = [(1, U32, 8, 8), (11, U32, 8, 8), (12, U32, 16, 16), (27, U32, 16, 16), (32, F64, 16, 16),
-              (47, F32, 16, 16), (48, U32, 64, 64), (191, F64, 16, 16), (192, F64, 64, 64), (256, U32, 64, 64),
-              (512, U32, 128, 64), (4096, F32, 256, 64)]
+ORDER_RULE = [(1, U32, 8, 8), (11, U32, 8, 8), (12, U32, 16, 16), (47, F32, 16, 16), (48, U32, 32, 16),
+              (191, F32, 32, 16), (192, U32, 64, 64), (319, F64, 32, 16), (320, F64, 64, 64),
+              (320, U32, 64, 64), (2047, U32, 64, 64), (2048, F64, 128, 64)]
 
 
 @pytest.mark.parametrize("mib,dtype,block,chunk", ORDER_RULE)
@@ -111,3 +111,20 @@ def test_blocks_of_a_stream_in_order(mib, dtype, block, chunk):
         assert r.kernel == BLOCKS
         assert (r.part_values * es, r.chunk_values * es) == (block << 10, chunk << 10)
         assert (r.parts - 1) * r.part_values <= n
+
+
+# (players, cards, waves, waves to a workgroup, players a lane, moved in the
+# kernel): both sides of 4 and of 15 waves per CU at 64 players a lane
+DEAL_RULE = [(2, 5, 1, 1, 1, 1), (1000, 1000, 512, 2, 32, 1), (65472, 52, 2046, 8, 32, 1),
+             (65473, 52, 1024, 4, 64, 1), (245696, 52, 3839, 15, 64, 1), (245697, 52, 3840, 1, 64, 0),
+             (60, 64 * 3839, 3839, 15, 60, 1), (60, 64 * 3840, 3840, 1, 60, 0),
+             (65536, 8000, 4096, 1, 497, 0), (65536, 65536, 4096, 1, 4096, 0)]
+
+
+@pytest.mark.parametrize("players,cards,waves,per,lane,moves", DEAL_RULE)
+def test_deals_by_player(players, cards, waves, per, lane, moves):
+    r = _abi.mrg_leapfrog_route(1, players, cards, U32, ROWS)
+    assert r.kernel == DEAL
+    assert r.waves_per_group == per and r.moves == moves and r.part_values == lane
+    assert r.waves == waves == min(r.parts, 4096) and r.parts * lane * r.lanes >= players * cards
+    assert (r.waves + per - 1) // per <= 256 or not moves

@@ -68,9 +68,12 @@ BLOCKS = [(1, 4096, 0, 0), (1, 4097, 0, 31), (3, 8193, 1, 1), (2, 6144, 2, 0), (
           (256, 4100, 0, 7), (257, 4100, 0, 7), (512, 16400, 0, 9), (513, 16400, 0, 0)]
 
 
-# both sides of 12 and 48 MiB in all, where the blocks and their chunks grow
+# both sides of the sizes where blocks and their chunks grow: 12, 48, 192 and
+# 320 MiB in all
 BLOCKS += [(1, (3 << 20) - 1, 0, 0), (1, 3 << 20, 0, 3), (5, (3 << 19) // 5 + 1, 2, 1), (1, (12 << 20) - 9, 1, 1),
-           (1, 12 << 20, 0, 0), (200, 70001, 0, 1), (1, 7 << 20, 2, 1), (40, 170001, 2, 1), (1, 25 << 20, 2, 3), (1, (64 << 20) + 999, 0, 0)]
+           (1, 12 << 20, 0, 0), (200, 70001, 0, 1), (40, 170001, 2, 1), (1, (48 << 20) - 100, 0, 3),
+           (1, (48 << 20) + 999, 1, 0), (1, (40 << 20) - 99, 2, 5), (1, (40 << 20) + 99, 2, 0),
+           (500, 170001, 0, 7)]
 
 
 @pytest.mark.parametrize("engine", [1, 0], ids=["f64", "int"])
@@ -103,6 +106,27 @@ def test_steps_in_segments(mg, count, n, dtype, off, engine):
     mg.mrg_config_set("engine", engine)
     try:
         check(mg, 1, count, n, dtype, 1, off)
+    finally:
+        mg.mrg_config_set("engine", old)
+
+
+# deals by player on both sides of 4 and of 15 waves per CU at 64 players a
+# lane: the stream moved in the kernel, by a launch after it
+@pytest.mark.parametrize("engine", [1, 0], ids=["f64", "int"])
+@pytest.mark.parametrize("players,cards,dtype", [(65472, 52, 0), (65473, 52, 2), (245696, 52, 1), (245697, 52, 0),
+                                                 (3001, 1001, 1), (75, 64 * 1919, 0), (75, 64 * 1920 + 1, 2)])
+def test_deals(mg, players, cards, dtype, engine):
+    old = mg.mrg_config_get("engine")
+    mg.mrg_config_set("engine", engine)
+    try:
+        with mg.StreamSet(3, master_seed=8) as ss:
+            st = ss.get_states()
+            for _ in range(2):
+                got = ss.fill_leapfrog(1, players, cards, dtype).cpu().numpy()
+                want, st[1:2] = oracle.fill(st[1:2], players * cards, dtype)
+                want = np.ascontiguousarray(want.reshape(cards, players).T)
+                assert np.array_equal(got.view(np.uint8), want.view(np.uint8))
+                assert np.array_equal(ss.get_states(), st)
     finally:
         mg.mrg_config_set("engine", old)
 
