@@ -597,9 +597,10 @@ mrg_status mrg_state_check(const uint32_t state6[6]);
  *                stream-major fill, 128 or 256, or 0 (default: 128 for rows
  *                shorter than 1 KiB, else 256);
  *   "strategy"   stream-major fill: 0 = automatic (default: several lanes
- *                per stream for rows of 64 x 128 bytes and more, of 384 bytes
- *                and a byte per 16 streams and more while the streams are at
- *                most two waves of lanes per compute unit; except rows under
+ *                per stream for rows of 64 x 128 bytes and more, and while the
+ *                streams are at most two waves of lanes per compute unit for
+ *                rows from 384 bytes to 6 KiB on, by their number, type and
+ *                place on lines; except rows under
  *                16 KiB that are not whole chunks on 128-byte lines when a
  *                wave of streams fills every SIMD; else one lane per
  *                stream), 1 = always lane per stream,

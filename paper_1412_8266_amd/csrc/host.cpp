@@ -10,6 +10,7 @@
 #include <array>
 #include <cstdarg>
 #include <cstdio>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -324,15 +325,24 @@ mrg_status new_streamset(uint64_t n_streams, uint64_t first_stream, mrg_streamse
 // 90 ns a binary64 when its wave has the SIMD to itself, so a launch of few
 // streams takes that time its row length whatever it writes (64 x 1000
 // uint32: 58 us; 9 us with 64 lanes per stream, the time of the call itself).
-// Several lanes cost a jump per lane instead, which grows with the streams:
-// the line lies at about one byte per 16 streams (uint32, lane against
-// several: 4096 x 100 10.7 against 9.4 us, 16384 x 200 17.2 against 14.0,
-// 32768 x 200 18.7 against 25, x 500 35.7 against 34.3), and from half a wave
-// per SIMD on at a whole chunk of 64 lines (49152 x 1000: 64 against 69).
-uint64_t coop_min_bytes(uint64_t count, int cus)
+// Several lanes cost a jump per lane instead, which grows with the streams,
+// and cut rows; the lane writer is at its best on lines and per byte with
+// binary64.  The line (several lanes against one, us): on lines, uint32 600
+// bytes for 8192 streams (512 bytes 8.5 and 7.8, 768 8.1 and 9.9), 1450 for
+// 16384 (1280 17.8 and 17.1, 1536 17.9 and 19.5), 5600 for 32768 (5120 59.2 and
+// 54.9, 6144 60.6 and 65.7); binary64 768, 2900 and 8192 (32768 x 256 28.4 and
+// 18.9); off lines 512, 1024 and 2730 (32768 x 2052 bytes 40.0 and 35.8, 3076 47.9
+// and 49.5).  From half a wave per SIMD on a whole chunk of 64 lines (49152 x
+// 1000: 64 against 69 us).
+uint64_t coop_min_bytes(uint64_t count, uint64_t es, bool rows_aligned, int cus)
 {
     if (count > (uint64_t)cus * 128) return 64 * 128;
-    return count / 16 > 384 ? count / 16 : 384;
+    const double c = (double)count / (32.0 * cus);  // 1 for 8192 streams
+    double line = c <= 2 ? 512 * c : 683 * c;
+    if (rows_aligned && es == 8) line = (c <= 1 ? 768 : 1024) * c * std::sqrt(c);
+    else if (rows_aligned) line = c > 3.5 ? 1408 * c : (c <= 1 ? 600 : 512) * c * std::sqrt(c);
+    const double least = !rows_aligned ? 384 : es == 8 ? 512 : 448;
+    return (uint64_t)(line > least ? line : least);
 }
 
 // Lanes per stream of the automatic stream-major fill: as many as bring the
@@ -465,15 +475,16 @@ mrg::FillLaunch plan_fill(const mrg::FillTuning &tune, int cus, uint64_t set_n, 
     if (*layout == MRG_STREAM_MAJOR) {
         // several lanes per stream (or when forced) for rows from coop_min_bytes
         // on (see below for rows under 16 KiB); lane per stream for the others
-        const bool coop = tune.strategy == 2 ||
-                          (tune.strategy == 0 && n_per_stream * es >= coop_min_bytes(count, cus));
+        const bool rows_aligned = out % 128 == 0 && (n_per_stream * es) % 128 == 0;
+        const bool coop =
+            tune.strategy == 2 || (tune.strategy == 0 && n_per_stream * es >=
+                                                             coop_min_bytes(count, es, rows_aligned, cus));
         if (coop) {
             // GL lanes per stream, 64/GL streams per wave; each lane takes
             // 64/GL or 2*64/GL pieces of 128 bytes per chunk (a chunk is then
             // 64 or 128 lines), whichever generates fewer values past the end
             // of a row (the longer chunk on a tie).  A row's line-aligned
             // part is n values, or about n - tv/2 when rows start anywhere.
-            const bool rows_aligned = out % 128 == 0 && (n_per_stream * es) % 128 == 0;
             const int GL = tune.coop_lanes ? tune.coop_lanes
                                            : coop_auto_lanes(count, n_per_stream * es, rows_aligned, cus);
             const uint64_t tv = 128 / es;

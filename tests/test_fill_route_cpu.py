@@ -128,3 +128,23 @@ def test_deals_by_player(players, cards, waves, per, lane, moves):
     assert r.waves_per_group == per and r.moves == moves and r.part_values == lane
     assert r.waves == waves == min(r.parts, 4096) and r.parts * lane * r.lanes >= players * cards
     assert (r.waves + per - 1) // per <= 256 or not moves
+
+
+# (streams, row bytes, dtype, offset, several lanes): both sides of the shortest
+# row that several lanes draw
+LANE_RULE = [(1, 380, U32, 0, False), (1, 384, U32, 4, True), (1, 384, U32, 0, False), (1, 512, U32, 0, True),
+             (2048, 504, F64, 8, True), (2048, 384, F64, 0, False), (2048, 512, F64, 0, True),
+             (8192, 508, U32, 4, False), (8192, 512, U32, 4, True), (8192, 512, F32, 0, False),
+             (8192, 640, F32, 0, True), (8192, 640, F64, 0, False), (8192, 768, F64, 0, True),
+             (16384, 1020, F32, 0, False), (16384, 1028, F32, 0, True), (16384, 1408, U32, 0, False),
+             (16384, 1536, U32, 0, True), (16384, 2816, F64, 0, False), (16384, 2944, F64, 0, True),
+             (20000, 1660, U32, 0, False), (20000, 1672, U32, 0, True), (28672, 3328, F32, 0, False),
+             (28672, 3456, F32, 0, True), (32768, 2728, U32, 0, False), (32768, 2732, U32, 0, True),
+             (32768, 5504, F32, 0, False), (32768, 5632, F32, 0, True), (32768, 8064, F64, 0, False),
+             (32768, 8192, F64, 0, True), (32769, 8188, U32, 0, False), (32769, 8192, U32, 0, True)]
+
+
+@pytest.mark.parametrize("count,row,dtype,off,several", LANE_RULE)
+def test_shortest_row_of_several_lanes(count, row, dtype, off, several):
+    r = rows(count, row // (8 if dtype == F64 else 4), dtype, off)
+    assert (r.kernel == WAVE) == several

@@ -51,6 +51,10 @@ ROWS = [(1, 95, 0, 0), (1, 96, 0, 0), (5, 97, 1, 3), (2048, 100, 0, 0), (2049, 1
         (16384, 255, 0, 1), (20000, 330, 0, 0), (32768, 257, 2, 0), (32769, 600, 0, 0),
         (65535, 600, 1, 0), (65536, 2050, 0, 0)]
 
+# and by the rows' type and place on lines
+ROWS += [(8192, 96, 2, 0), (8192, 80, 2, 0), (16384, 352, 0, 0), (16384, 384, 0, 0), (16384, 272, 2, 0),
+         (32768, 760, 0, 0), (32768, 1024, 1, 0), (32768, 992, 1, 0), (32768, 768, 2, 0), (32768, 761, 0, 3)]
+
 # two lanes per stream (rows of 4 KiB on lines): whole and partial last waves
 ROWS += [(65536, 1024, 0, 0), (65553, 1024, 1, 0), (65569, 512, 2, 0), (65600, 1024, 0, 32)]
 
