@@ -13,14 +13,13 @@
 //   philox_runs_kernel    stream-major fill of longer rows: a wave per run of
 //                         a row, one 16-byte aligned unit of 4 values per lane
 //                         and step
-//   philox_lined_kernel   the same for many rows of 8-16 KiB on lines, the
-//                         waves of a row side by side
 //   philox_il_kernel      interleaved fill: one stream (or a segment of one)
 //                         per lane, consecutive lanes write consecutive
 //                         elements
 // A fill moves the positions itself: the workgroup or lane that holds a whole
-// row, or the last to read it of several (arrive(), gen_device.hpp); only rows
-// of very many runs leave it to a jump launch after the fill.
+// row, or the last to read it of several (arrive(), gen_device.hpp); rows of
+// very many parts (parts_move, kernels.h) leave it to a jump launch after the
+// fill.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -209,7 +208,8 @@ philox_rows_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
 // lane from the first one of the next step, which is why a step's units are
 // stored after the next step's blocks are drawn.  A wave takes rw rows (one
 // when they are cut), lane r loading row r's state, so that short rows share
-// the wait for it.
+// the wait for it.  With `chunked` the workgroups take the rows in the chunked
+// XCD order.
 __device__ __forceinline__ uint32_t from_next_lane(uint32_t v, uint32_t last)
 {
     // wave_shl:1, lane 63 keeps `last`
@@ -220,12 +220,13 @@ template <int DT>
 __global__ void __launch_bounds__(256)
 philox_runs_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
                    uint64_t count, uint64_t n, uint32_t rw, uint32_t nrun, uint32_t units, int move,
-                   unsigned char *__restrict__ out)
+                   int chunked, unsigned char *__restrict__ out)
 {
     using T = typename PhiloxOut<DT>::T;
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t items = (count + rw - 1) / rw * nrun;
-    for (uint64_t item = (uint64_t)blockIdx.x * 4 +
+    const uint64_t wg = chunked ? xcd_chunk(gridDim.x).first : blockIdx.x;
+    for (uint64_t item = wg * 4 +
                          (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
          item < items; item += (uint64_t)gridDim.x * 4) {
         const uint64_t s0 = item / nrun * rw, q = item % nrun;
@@ -291,58 +292,6 @@ philox_runs_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
         }
         if (move && lane < rows && last_arrival(arrived, nrun))
             store_position(planes, plane_stride, first + s0 + lane, position(w) + n);
-    }
-}
-
-// Stream-major, rows of 8-16 KiB on 128-byte lines in large numbers: a
-// workgroup owns rpw rows, tpr = 256 / rpw threads each; thread j of a row
-// writes blocks j, j + tpr, ... of the row, so the waves of a row write it
-// side by side (2^20 x 2048 uint32 1.43 ms, 1.49 with a wave to a row).  The
-// positions are moved by a launch after it.
-template <int DT>
-__global__ void __launch_bounds__(256)
-philox_lined_kernel(const uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
-                 uint64_t count, uint64_t n, int rpw, unsigned char *__restrict__ out)
-{
-    using T = typename PhiloxOut<DT>::T;
-    const int tpr = 256 / rpw;
-    // several rows per workgroup: row groups in the chunked XCD order, so the
-    // rows whose states share a state-plane line run on one XCD and each line
-    // is fetched into one L2 (one row per workgroup keeps the dispatch order,
-    // measured faster for such long rows)
-    const uint64_t wg = rpw > 1 ? xcd_chunk(gridDim.x).first : blockIdx.x;
-    const uint64_t s = wg * rpw + threadIdx.x / tpr;
-    if (s >= count || (int)threadIdx.x >= rpw * tpr) return;
-    uint32_t w[6];
-    load_state(planes, plane_stride, first + s, w);
-    const uint64_t pos = position(w);
-    const uint64_t off = pos & 3, b0 = pos >> 2;
-    const uint64_t nb = (off + n + 3) / 4;
-    T *row = (T *)out + s * n;
-    for (uint64_t b = threadIdx.x % tpr; b < nb; b += tpr) {
-        uint32_t v[4];
-        philox_block(w, b0 + b, v);
-        const uint64_t k0 = 4 * b - off;  // row index of word 0 (wraps below 0 for b = 0)
-        if (off == 0 && k0 + 4 <= n && ((uintptr_t)(row + k0) % (4 * sizeof(T))) == 0) {
-            T *p = row + k0;
-            if constexpr (DT == 2) {
-                *(double2 *)p = make_double2(PhiloxOut<2>::conv(v[0]), PhiloxOut<2>::conv(v[1]));
-                *(double2 *)(p + 2) = make_double2(PhiloxOut<2>::conv(v[2]), PhiloxOut<2>::conv(v[3]));
-            } else {
-                uint4 q;
-                q.x = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[0]));
-                q.y = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[1]));
-                q.z = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[2]));
-                q.w = __builtin_bit_cast(uint32_t, PhiloxOut<DT>::conv(v[3]));
-                *(uint4 *)p = q;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint64_t k = k0 + j;  // below 0 wraps to a huge value: skipped
-                if (k < n) row[k] = PhiloxOut<DT>::conv(v[j]);
-            }
-        }
     }
 }
 
@@ -445,12 +394,14 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
                            plane_stride, first, count, (uint32_t)n, (uint32_t)rpw, mb, magic, quads, o);
         return hipGetLastError();
     }
-    // runs of up to 16 steps of 64 units (16 KiB of 4-byte values), fewer
+    // runs of up to 16 KiB (16 steps of 64 units, 8 of binary64: 131072 x 4096
+    // binary64 748 us, in runs of 16 steps 777, x 5120 881 and 999), fewer steps
     // while that leaves under eight waves per SIMD
     const uint64_t neg = (uintptr_t)out % 128 || (n * ES) % 128 ? 128 / ES - 1 : 0;
     const uint64_t steps = ((n + neg + 3) / 4 + 63) / 64;
     uint64_t per = steps * count / ((uint64_t)cus * 32);
-    per = per < 1 ? 1 : per > 16 ? 16 : per;
+    const uint64_t most = ES == 8 ? 8 : 16;
+    per = per < 1 ? 1 : per > most ? most : per;
     while (per < steps && (steps + per - 1) / per >= (uint64_t)1 << 31) per *= 2;
     uint64_t nrun = (steps + per - 1) / per;
     per = (steps + nrun - 1) / nrun;
@@ -461,25 +412,15 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
     uint64_t rw = nrun > 1 || n * ES >= 6144 ? 1 : count / ((uint64_t)cus * 32);
     rw = rw < 1 ? 1 : rw > 8 ? 8 : rw;
     const uint64_t wgs = ((count + rw - 1) / rw * nrun + 3) / 4;
-    // rows of one run on lines, enough of them to fill the chip
-    if (nrun == 1 && neg == 0 && n * ES >= 8192 && count >= (uint64_t)cus * 256) {
-        int tpr = 64;
-        while (tpr < 256 && (uint64_t)tpr * 16 < (n + 6) / 4) tpr *= 2;
-        const int rpw = 256 / tpr;
-        const uint64_t groups = (count + rpw - 1) / rpw;
-        if (groups <= cap) {
-            hipLaunchKernelGGL((philox_lined_kernel<DT>), dim3((unsigned)groups), dim3(256), 0, st,
-                               planes, plane_stride, first, count, n, rpw, o);
-            hipError_t e = hipGetLastError();
-            if (e == hipSuccess)
-                e = launch_philox_jump(planes, plane_stride, first, count, nullptr, n, st);
-            return e;
-        }
-    }
+    // rows of one run in the chunked order, so that rows whose states share a
+    // line meet in one L2 (131072 x 3072 uint32 290 us, in dispatch order 305;
+    // x 4096 368 and 379), but for 8 KiB (2^19 x 1024 binary64 932 and 730, 2048
+    // uint32 804 and 677) and cut rows (131072 x 5120 uint32 690 and 448)
+    const int chunked = nrun == 1 && n * ES > 8192;
     const int move = parts_move(plane_stride, count, nrun, false);
     hipLaunchKernelGGL((philox_runs_kernel<DT>), dim3((unsigned)(wgs < cap ? wgs : cap)), dim3(256), 0, st,
                        planes, plane_stride, first, count, n, (uint32_t)rw,
-                       (uint32_t)nrun, (uint32_t)(per * 64), move, o);
+                       (uint32_t)nrun, (uint32_t)(per * 64), move, chunked, o);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && !move)
         e = launch_philox_jump(planes, plane_stride, first, count, nullptr, n, st);

@@ -245,6 +245,12 @@ PHILOX = [(65537, 2048, 0, 0, 0, 4), (65538, 1024, 2, 0, 0, 1), (300, 1, 0, 0, 1
           (1, 5001, 0, 1, 0, 1), (33, 4100, 2, 1, 0, 3), (5000, 700, 1, 1, 1, 0), (64, 20000, 0, 1, 0, 1)]
 
 
+# many rows of one run in the chunked order and not, of two runs of binary64
+PHILOX += [(65539, 2049, 0, 0, 0, 1), (65541, 4096, 0, 0, 0, 0), (33333, 4096, 1, 0, 1, 3),
+           (65539, 1025, 2, 0, 0, 2), (33333, 2048, 2, 0, 0, 0), (33333, 4096, 2, 0, 0, 1),
+           (16411, 4097, 0, 0, 3, 2)]
+
+
 @pytest.mark.parametrize("count,n,dtype,layout,off,pos", PHILOX)
 def test_philox(mg, count, n, dtype, layout, off, pos):
     import torch
