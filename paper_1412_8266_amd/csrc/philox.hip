@@ -103,32 +103,37 @@ __device__ __forceinline__ void store_unit(typename PhiloxOut<DT>::T *p, const u
     }
 }
 
-// Stream-major, short rows: a workgroup owns rpw adjacent rows (at most
-// kPhiloxLds bytes, 4 blocks per thread), one piece of memory.  Item i is
-// block i % mb of row i / mb (mb: the most blocks a row can touch; magic =
-// ceil(2^32 / mb), exact for the few thousand items here).  With `quads` (rows
-// of whole 16-byte units on 16-byte boundaries; mb is then n / 4) and every
-// position at a block's start (and one key), the items are the piece's units
-// in order and go straight to memory; else an item's values go to LDS at their byte in the
-// piece (off by the piece's own place in 16 bytes) and the piece is then
-// written as 16-byte stores.
+// Stream-major, short rows: a workgroup owns rpw adjacent rows, one piece of
+// memory; MANY (its own instance: the loop over pieces costs the others 5-10 %):
+// rows_wg rows, several such pieces, in the chunked XCD order, so that rows whose
+// states share a line meet in one L2 and an XCD's workgroups write one front.
+// Item i is block i % mb of row i / mb (mb: the most blocks a row can touch;
+// magic = ceil(2^32 / mb), exact for the few thousand items here).  With `quads`
+// (rows of whole 16-byte units on 16-byte boundaries; mb is then n / 4) and every
+// position at a block's start (and one key), the items are the piece's units in
+// order and go straight to memory; else the rows are staged rpw at a time (at
+// most kPhiloxLds bytes, 4 blocks per thread): an item's values go to LDS at
+// their byte in the piece (off by the piece's own place in 16 bytes) and the
+// piece is then written as 16-byte stores.
 constexpr int kPhiloxLds = 16384;
 
-template <int DT>
+template <int DT, bool MANY>
 __global__ void __launch_bounds__(256)
 philox_rows_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
-                   uint64_t count, uint32_t n, uint32_t rpw, uint32_t mb, uint32_t magic, int quads,
-                   unsigned char *__restrict__ out)
+                   uint64_t count, uint32_t n, uint32_t rows_wg, uint32_t rpw, uint32_t mb,
+                   uint32_t magic, int quads, unsigned char *__restrict__ out)
 {
     using T = typename PhiloxOut<DT>::T;
     __shared__ __attribute__((aligned(16))) unsigned char lds[kPhiloxLds + 16];
     __shared__ uint32_t st[6][256];
-    for (uint64_t s0 = (uint64_t)blockIdx.x * rpw; s0 < count; s0 += (uint64_t)gridDim.x * rpw) {
-        const uint32_t rows = count - s0 < rpw ? (uint32_t)(count - s0) : rpw;
+    if (!MANY) rows_wg = rpw;
+    const uint64_t wg = MANY ? xcd_chunk(gridDim.x).first : blockIdx.x;
+    for (uint64_t s0 = wg * rows_wg; s0 < count; s0 += (uint64_t)gridDim.x * rows_wg) {
+        const uint32_t all = count - s0 < rows_wg ? (uint32_t)(count - s0) : rows_wg;
         // this thread's row starts within a block, or has another key than the
         // first row (sets are made under one key, but any states can be set)
         int within = 0, odd_key = 0;
-        if (threadIdx.x < rows) {
+        if (threadIdx.x < all) {
             uint32_t w[6];
             load_state(planes, plane_stride, first + s0 + threadIdx.x, w);
 #pragma unroll
@@ -137,7 +142,7 @@ philox_rows_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
             within = w[0] & 3u;
         }
         const bool lined = !__syncthreads_or(within) && quads;
-        if (threadIdx.x < rows)
+        if (threadIdx.x < all)
             odd_key = st[4][threadIdx.x] != st[4][0] || st[5][threadIdx.x] != st[5][0];
         const bool one_key = !__syncthreads_or(odd_key);
         // the round keys stay in scalar registers
@@ -145,7 +150,7 @@ philox_rows_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
         const uint32_t key1 = __builtin_amdgcn_readfirstlane(st[5][0]);
         unsigned char *base = out + s0 * n * sizeof(T);
         if (lined && one_key) {
-            for (uint32_t i = threadIdx.x; i < rows * mb; i += 256) {
+            for (uint32_t i = threadIdx.x; i < all * mb; i += 256) {
                 const uint32_t r = mb == 1 ? i : __umulhi(i, magic), b = i - r * mb;
                 const uint32_t w[6] = {st[0][r], st[1][r], st[2][r], st[3][r], key0, key1};
                 uint32_t v[4];
@@ -155,47 +160,52 @@ philox_rows_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_
             __syncthreads();  // st is free again
             continue;
         }
-        const uint32_t o = (uint32_t)((uintptr_t)base & 15u);
         // a row of whole units that starts within a block touches one block more
         const uint32_t nb = mb + (quads ? 1u : 0u);
-        for (uint32_t i = threadIdx.x; i < rows * nb; i += 256) {
-            const uint32_t r = quads ? i / nb : mb == 1 ? i : __umulhi(i, magic), b = i - r * nb;
-            uint32_t w[6] = {st[0][r], st[1][r], st[2][r], st[3][r], key0, key1};
-            const uint64_t pos = position(w);
-            uint32_t v[4];
-            if (one_key) {
-                philox_block(w, (pos >> 2) + b, v);
-            } else {
-                w[4] = st[4][r];
-                w[5] = st[5][r];
-                philox_block(w, (pos >> 2) + b, v);
-            }
-            const uint32_t k0 = 4 * b - ((uint32_t)pos & 3u);  // wraps below 0 for b = 0
-            const uint32_t at = o + (r * n + k0) * (uint32_t)sizeof(T);
-            if (k0 < n && k0 + 4 <= n && at % 16 == 0) {
-                store_unit<DT>((T *)(lds + at), v);
-                continue;
-            }
+        for (uint32_t q = 0; q < all; q += rpw, base += rpw * n * sizeof(T)) {
+            const uint32_t rows = !MANY ? all : all - q < rpw ? all - q : rpw;
+            const uint32_t o = (uint32_t)((uintptr_t)base & 15u);
+            for (uint32_t i = threadIdx.x; i < rows * nb; i += 256) {
+                const uint32_t r = quads ? i / nb : mb == 1 ? i : __umulhi(i, magic), b = i - r * nb;
+                const uint32_t t = q + r;
+                uint32_t w[6] = {st[0][t], st[1][t], st[2][t], st[3][t], key0, key1};
+                const uint64_t pos = position(w);
+                uint32_t v[4];
+                if (one_key) {
+                    philox_block(w, (pos >> 2) + b, v);
+                } else {
+                    w[4] = st[4][t];
+                    w[5] = st[5][t];
+                    philox_block(w, (pos >> 2) + b, v);
+                }
+                const uint32_t k0 = 4 * b - ((uint32_t)pos & 3u);  // wraps below 0 for b = 0
+                const uint32_t at = o + (r * n + k0) * (uint32_t)sizeof(T);
+                if (k0 < n && k0 + 4 <= n && at % 16 == 0) {
+                    store_unit<DT>((T *)(lds + at), v);
+                    continue;
+                }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t k = k0 + j;
-                if (k < n) ((T *)(lds + o))[r * n + k] = PhiloxOut<DT>::conv(v[j]);
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t k = k0 + j;
+                    if (k < n) ((T *)(lds + o))[r * n + k] = PhiloxOut<DT>::conv(v[j]);
+                }
             }
-        }
-        __syncthreads();
-        // bytes [o, end) of lds belong at base - o
-        const uint32_t end = o + rows * n * (uint32_t)sizeof(T);
-        unsigned char *dst = base - o;
-        for (uint32_t i = threadIdx.x * 16; i < end; i += 256 * 16) {
-            if (i >= o && i + 16 <= end) {
-                *(uint4 *)(dst + i) = *(const uint4 *)(lds + i);
-            } else {
+            __syncthreads();
+            // bytes [o, end) of lds belong at base - o
+            const uint32_t end = o + rows * n * (uint32_t)sizeof(T);
+            unsigned char *dst = base - o;
+            for (uint32_t i = threadIdx.x * 16; i < end; i += 256 * 16) {
+                if (i >= o && i + 16 <= end) {
+                    *(uint4 *)(dst + i) = *(const uint4 *)(lds + i);
+                } else {
 #pragma unroll
-                for (uint32_t d = i; d < i + 16; d += 4)
-                    if (d >= o && d < end) *(uint32_t *)(dst + d) = *(const uint32_t *)(lds + d);
+                    for (uint32_t d = i; d < i + 16; d += 4)
+                        if (d >= o && d < end) *(uint32_t *)(dst + d) = *(const uint32_t *)(lds + d);
+                }
             }
+            __syncthreads();  // lds, and after the last rows st, are free again
+            if (!MANY) break;
         }
-        __syncthreads();  // lds and st are free again
     }
 }
 
@@ -381,17 +391,31 @@ static hipError_t launch_philox_fill_t(uint32_t *planes, uint64_t plane_stride, 
     // bytes or blocks are faster in runs: 65536 x 600 42 against 39 us)
     const int quads = n % 4 == 0 && (uintptr_t)out % 16 == 0;
     if (n * ES < (quads || ES == 8 ? 4096 : 2048)) {
-        // as many rows as fit (four blocks per thread), fewer while that
-        // leaves under four workgroups per CU
+        // pieces of as many rows as fit (four blocks per thread), fewer while
+        // that leaves under four workgroups per CU; fills of 512 MiB and more two
+        // pieces to a workgroup, of a GiB in binary64 four, in the chunked order
+        // (2^20 x 384 uint32 403 us in single pieces, 298 in pairs, at position 1
+        // 407 and 359; 2^20 x 384 binary64 690, in pairs 650, in fours 601; below
+        // 512 MiB pairs lose: 262144 x 128 uint32 25.2 us in single pieces and 28)
         const uint32_t mb = quads ? (uint32_t)n / 4 : (uint32_t)(n + 6) / 4;
         uint64_t rpw = kPhiloxLds / (n * ES) < 1024 / mb ? kPhiloxLds / (n * ES) : 1024 / mb;
         if (rpw > 256) rpw = 256;
         const uint64_t spread = count / ((uint64_t)cus * 4);
         if (rpw > spread) rpw = spread < 1 ? 1 : spread;
-        const uint64_t wgs = (count + rpw - 1) / rpw;
+        const uint64_t bytes = count * n * ES;
+        const bool many = bytes >= (uint64_t)512 << 20;
+        const uint64_t pieces = !many ? 1 : ES == 8 && bytes >= (uint64_t)1 << 30 ? 4 : 2;
+        const uint64_t rows_wg = rpw * pieces <= 256 ? rpw * pieces : 256 / rpw * rpw;
+        const uint64_t wgs = (count + rows_wg - 1) / rows_wg;
         const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + mb - 1) / mb);  // mb = 1: not used
-        hipLaunchKernelGGL((philox_rows_kernel<DT>), dim3((unsigned)(wgs < cap ? wgs : cap)), dim3(256), 0, st, planes,
-                           plane_stride, first, count, (uint32_t)n, (uint32_t)rpw, mb, magic, quads, o);
+        const dim3 grid((unsigned)(wgs < cap ? wgs : cap)), block(256);
+#define MRG_ROWS(MANY)                                                                          \
+    hipLaunchKernelGGL((philox_rows_kernel<DT, MANY>), grid, block, 0, st, planes, plane_stride,  \
+                       first, count, (uint32_t)n, (uint32_t)rows_wg, (uint32_t)rpw, mb, magic,    \
+                       quads, o)
+        if (many) MRG_ROWS(true);
+        else MRG_ROWS(false);
+#undef MRG_ROWS
         return hipGetLastError();
     }
     // runs of up to 16 KiB (16 steps of 64 units, 8 of binary64: 131072 x 4096

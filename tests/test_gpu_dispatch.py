@@ -251,6 +251,13 @@ PHILOX += [(65539, 2049, 0, 0, 0, 1), (65541, 4096, 0, 0, 0, 0), (33333, 4096, 1
            (16411, 4097, 0, 0, 3, 2)]
 
 
+# several pieces of rows to a workgroup, from 512 MiB (binary64 a GiB) on: whole
+# and partial last pieces, 256 rows, on and off 16 bytes and blocks, and below
+PHILOX += [(300007, 4, 0, 0, 0, 0), (100003, 128, 1, 0, 0, 2), (70001, 508, 2, 0, 0, 0),
+           (700001, 192, 0, 0, 0, 0), (700001, 192, 1, 0, 0, 3), (130001, 1031, 0, 0, 1, 1),
+           (400001, 171, 2, 0, 0, 0), (400001, 340, 2, 0, 0, 0), (400001, 340, 2, 0, 0, 1), (400001, 337, 2, 0, 1, 0)]
+
+
 @pytest.mark.parametrize("count,n,dtype,layout,off,pos", PHILOX)
 def test_philox(mg, count, n, dtype, layout, off, pos):
     import torch
