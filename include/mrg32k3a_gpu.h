@@ -367,7 +367,8 @@ typedef struct {
 
 typedef struct {
     uint64_t requests;        /* non-empty requests */
-    uint64_t items;           /* work items of the plan under config */
+    uint64_t items;           /* work items of the plan under config (mrg_batch_running_plan:
+                                 of the one that runs) */
     uint64_t samples;         /* outputs per run */
     uint64_t bytes;           /* output bytes per run */
     uint64_t scratch_states;  /* end states that plan stages before copy-back */
@@ -390,9 +391,10 @@ typedef struct mrg_batch_s *mrg_batch;
  * then the copy-back of end states).  A batch of under 16 GiB of output whose
  * segment_bytes and wave_min_bytes are left to their defaults runs the same
  * requests as one group of finer items of every dtype (the plan that
- * mrg_batch_info and mrg_batch_plan_groups state is the one under cfg).  Every non-empty request's d_out must be device
- * memory of the set's device holding its output inside one allocation (else
- * MRG_EINVAL / MRG_ERANGE naming the request).  reqs is copied; cfg may be
+ * mrg_batch_info and mrg_batch_plan_groups state is the one under cfg,
+ * mrg_batch_running_plan states the one that runs).  Every non-empty request's
+ * d_out must be device memory of the set's device holding its output inside
+ * one allocation (else MRG_EINVAL / MRG_ERANGE naming the request).  reqs is copied; cfg may be
  * NULL.  The plan refers to ss and to the output buffers, which must outlive
  * it.  Free with mrg_batch_destroy. */
 mrg_status mrg_batch_create(mrg_batch *out, mrg_streamset ss, const mrg_request *reqs,
@@ -412,6 +414,27 @@ mrg_status mrg_batch_run_per_request(mrg_batch b, void *stream);
 
 mrg_status mrg_batch_info(mrg_batch b, mrg_batch_info_t *info);
 
+/* The plan that a batch runs. */
+typedef struct {
+    uint64_t items;           /* work items */
+    uint64_t scratch_states;  /* end states staged before copy-back */
+    uint64_t segment_bytes;   /* the sizes its items are cut by */
+    uint64_t wave_min_bytes;
+    uint32_t groups;          /* persistent launches */
+    uint32_t streams_per_item; /* most whole streams a wave item holds; 0: a segment's worth */
+    uint32_t grid;            /* most persistent workgroups a launch has */
+    uint32_t pad;
+} mrg_batch_plan_t;
+
+/* The plan that b's runs execute. */
+mrg_status mrg_batch_running_plan(mrg_batch b, mrg_batch_plan_t *plan);
+
+/* The same for a batch of these requests under cfg (NULL: defaults) on a
+ * device of cus compute units, computed on the host alone; the requests are
+ * taken as by mrg_batch_plan_groups. */
+mrg_status mrg_batch_plan(const mrg_request *reqs, uint64_t n_reqs, const mrg_batch_config *cfg,
+                          int cus, mrg_batch_plan_t *plan);
+
 /* One launch group of a batch plan (mrg_batch_plan_groups). */
 typedef struct {
     int32_t dtype;         /* dtype of the group's wave items */
@@ -423,9 +446,10 @@ typedef struct {
 } mrg_plan_group;
 
 /* The launch groups of these requests under cfg (NULL: defaults; what a batch
- * of 16 GiB or more, or one with sizes in cfg, captures), computed on the host alone: no stream set,
- * device or output memory is touched, d_out is not read, and the requests
- * are not validated against a stream set (dtype and flags are checked).
+ * of 16 GiB or more, or one with sizes in cfg, captures), computed on the host
+ * alone: no stream set, device or output memory is touched, d_out is not read,
+ * and the requests are not validated against a stream set (dtype and flags are
+ * checked).
  * groups receives up to 3 groups in launch order (*n_groups of them); when
  * pos is not NULL, pos[i] is input request i's index in the grouped order
  * (items are claimed in that order; UINT64_MAX for empty requests), and
@@ -459,10 +483,10 @@ mrg_status mrg_batch_destroy(mrg_batch b);
 
 /* For callers that cannot allocate device memory (serving loops and
  * harnesses that forbid hipMalloc, code that must not grow the device heap):
- * plan and run one batch -- the same validation, work items, kernels and
- * results as mrg_batch_create(ss, reqs, n_reqs, cfg) followed by
- * mrg_batch_run and mrg_batch_destroy -- without any device or pinned
- * allocation.  The request descriptors, item prefixes, claim counters and the
+ * plan and run one batch -- the same validation and results as
+ * mrg_batch_create(ss, reqs, n_reqs, cfg) followed by mrg_batch_run and
+ * mrg_batch_destroy, always in the work items and launch groups that
+ * mrg_batch_plan_groups states -- without any device or pinned allocation.  The request descriptors, item prefixes, claim counters and the
  * staged end states of multi-segment streams go into one fixed device array
  * of MRG_NOALLOC_SCRATCH_BYTES bytes; a batch needing more (about 80 bytes per
  * request plus 24 bytes per stream of more than one segment) returns

@@ -292,16 +292,27 @@ def batch_config(segment_bytes=0, wave_min_bytes=0, waves_per_cu=0, schedule=0):
 
 
 def batch_plan_groups(requests, config=None):
-    """The launch groups a Batch of these request rows would run, planned on
-    the host alone (no device, d_out not read): (groups in launch order,
-    each request's index in the grouped order, each request's work items)."""
+    """The launch groups of these request rows under config, planned on the
+    host alone (no device, d_out not read): (groups in launch order, each
+    request's index in the grouped order, each request's work items).  A Batch
+    of 16 GiB or more, or with item sizes of its own, runs these; batch_plan
+    states what any other runs."""
     rows = list(requests)
     return _abi.mrg_batch_plan_groups(_abi.make_requests(rows), len(rows), config)
 
 
+def batch_plan(requests, config=None, cus: int = 256) -> dict:
+    """The plan that a Batch of these request rows runs on a device of cus
+    compute units (Batch.running_plan), on the host alone."""
+    rows = list(requests)
+    return _abi.mrg_batch_plan(_abi.make_requests(rows), len(rows), config, cus)
+
+
 class Batch:
-    """Many fill requests over one StreamSet run as one hipGraph of
-    persistent launches (batch_plan_groups shows the grouping).
+    """Many fill requests over one StreamSet run as one hipGraph of persistent
+    launches: the groups that batch_plan_groups shows, or for under 16 GiB of
+    output in items of the library's sizes one launch of finer items
+    (running_plan, batch_plan).
 
     ``requests`` rows are (first, count, n_per_stream, substream0, d_out,
     dtype, flags); d_out is a device pointer (int) to a [count, n] array.
@@ -331,7 +342,12 @@ class Batch:
         _abi.mrg_batch_run_per_request(self._h, _stream_handle(stream))
 
     def info(self) -> dict:
+        """The plan under the configuration (running_plan: the one that runs)."""
         return _abi.mrg_batch_info(self._h)
+
+    def running_plan(self) -> dict:
+        """Items, launches and item sizes of the plan that run executes."""
+        return _abi.mrg_batch_running_plan(self._h)
 
     def autotune(self, configs, reps: int = 1, stream=None):
         return _abi.mrg_batch_autotune(self._h, configs, reps, _stream_handle(stream))
@@ -354,5 +370,5 @@ class Batch:
         self.close()
 
 
-__all__ += ["Batch", "batch_config", "batch_plan_groups", "REQ_SUBSTREAMS", "SCHEDULE_DYNAMIC",
-            "SCHEDULE_STATIC"]
+__all__ += ["Batch", "batch_config", "batch_plan", "batch_plan_groups", "REQ_SUBSTREAMS",
+            "SCHEDULE_DYNAMIC", "SCHEDULE_STATIC"]

@@ -100,6 +100,13 @@ class mrg_batch_info_t(ctypes.Structure):
                 ("pad", ctypes.c_uint32), ("config", mrg_batch_config)]
 
 
+class mrg_batch_plan_t(ctypes.Structure):
+    _fields_ = [("items", ctypes.c_uint64), ("scratch_states", ctypes.c_uint64),
+                ("segment_bytes", ctypes.c_uint64), ("wave_min_bytes", ctypes.c_uint64),
+                ("groups", ctypes.c_uint32), ("streams_per_item", ctypes.c_uint32),
+                ("grid", ctypes.c_uint32), ("pad", ctypes.c_uint32)]
+
+
 class mrg_plan_group(ctypes.Structure):
     _fields_ = [("dtype", ctypes.c_int32), ("rows", ctypes.c_int32), ("requests", ctypes.c_uint64),
                 ("items", ctypes.c_uint64), ("row_items", ctypes.c_uint64),
@@ -116,6 +123,9 @@ _SIGS.update({
     "mrg_batch_run_direct": [_P, _P],
     "mrg_batch_run_per_request": [_P, _P],
     "mrg_batch_info": [_P, ctypes.POINTER(mrg_batch_info_t)],
+    "mrg_batch_running_plan": [_P, ctypes.POINTER(mrg_batch_plan_t)],
+    "mrg_batch_plan": [ctypes.POINTER(mrg_request), _U64, ctypes.POINTER(mrg_batch_config), _I32,
+                       ctypes.POINTER(mrg_batch_plan_t)],
     "mrg_batch_request_times": [_P, _P, ctypes.POINTER(ctypes.c_double)],
     "mrg_batch_autotune": [_P, ctypes.POINTER(mrg_batch_config), ctypes.c_uint32, ctypes.c_uint32,
                            _P, ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(ctypes.c_float)],
@@ -436,6 +446,24 @@ def mrg_batch_info(b: int) -> dict:
             "bytes": info.bytes, "scratch_states": info.scratch_states, "grid": info.grid,
             "segment_bytes": c.segment_bytes, "wave_min_bytes": c.wave_min_bytes,
             "waves_per_cu": c.waves_per_cu, "schedule": c.schedule}
+
+
+def _plan_dict(p) -> dict:
+    return {name: getattr(p, name) for name, _ in p._fields_ if name != "pad"}
+
+
+def mrg_batch_running_plan(b: int) -> dict:
+    p = mrg_batch_plan_t()
+    _call("mrg_batch_running_plan", b, ctypes.byref(p))
+    return _plan_dict(p)
+
+
+def mrg_batch_plan(reqs, n_reqs: int, cfg=None, cus: int = 256) -> dict:
+    """Host-only: the plan a batch of these requests runs on cus compute units."""
+    p = mrg_batch_plan_t()
+    _call("mrg_batch_plan", reqs, n_reqs, ctypes.byref(cfg) if cfg is not None else None, cus,
+          ctypes.byref(p))
+    return _plan_dict(p)
 
 
 def mrg_batch_plan_groups(reqs, n_reqs: int, cfg=None):

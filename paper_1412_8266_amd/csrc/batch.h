@@ -26,8 +26,8 @@ constexpr int kBatchLaneBytes = 1024;
 // row items are too few and too uneven to fill the chip on their own (a
 // stream of up to 16 KiB per lane), and the wave items that follow them fill
 // the slots their tail leaves idle.
-// kKindMixed: the items of every dtype and form in one launch (batches too
-// small to fill the chip group by group).
+// kKindMixed: the items of every dtype and form in one launch (batches of under
+// 16 GiB whose item sizes are the library's).
 constexpr int kKindWave = 0;
 constexpr int kKindRows = 1;
 constexpr int kKindMixed = 2;
@@ -137,6 +137,16 @@ struct HostPlan {
 // one group.
 void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, HostPlan *out,
                 uint32_t pack = 0);
+// The plan that a batch runs on a device of `cus` CUs: that of cfg, or finer
+// items of one group (batch_host.cpp).
+struct RunPlan {
+    HostPlan host;
+    uint64_t cfg_items, cfg_scratch;  // items and staged states of the plan under cfg
+    mrg_batch_config cfg;             // the sizes `host` is cut by
+    uint32_t pack;                    // as for plan_batch
+};
+void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool sizes_given,
+              int cus, RunPlan *out);
 // cfg with defaults filled in (cfg may be NULL).
 mrg_batch_config batch_config(const mrg_batch_config *cfg);
 // The checks of mrg_batch_create: dtypes, flags, outputs (device memory of

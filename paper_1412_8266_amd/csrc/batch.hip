@@ -12,8 +12,8 @@
 //     rows_fill_carry_w or rows_fill.
 // One launch per group (batch.h): wave items of one dtype, or the row items
 // of every dtype, largest first, followed by the wave items of one dtype; a
-// batch too small to fill the chip that way is one launch of finer items of
-// every dtype.
+// batch of under 16 GiB whose item sizes are the library's is one launch of
+// finer items of every dtype.
 // Persistent workgroups (one wave each) claim items from a global counter or
 // take them round robin; item i belongs to the request r with
 // prefix[r] <= i < prefix[r+1].  A request in substream mode draws its streams

@@ -156,6 +156,33 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
     else group_requests(P.in, &P.plan);
 }
 
+// A batch of under 16 GiB whose item sizes were left to the library runs
+// as one launch of finer items: under the sizes for batches that fill the
+// chip many times over, its three launches each ended in a few long items
+// (64 streams of 16 KiB drawn in series, 16 short streams in one wave).
+// With fewer streams than two waves of lanes per SIMD, rows from 2 KiB on
+// go to whole waves too (300 requests, 0.97 GB: 866 -> 317 us, with rows
+// under 16 KiB in lanes 434; 1000 requests of 490,000 streams, 5.6 GB:
+// 1956 against 1426 us the other way round).
+void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool sizes_given,
+              int cus, RunPlan *out)
+{
+    HostPlan &P = out->host;
+    plan_batch(reqs, n, cfg, &P);
+    out->cfg = cfg;
+    out->pack = 0;
+    out->cfg_items = P.plan.total_items;
+    out->cfg_scratch = P.scratch_slots;
+    if (sizes_given || P.bytes >= (uint64_t)16 << 30) return;
+    uint64_t streams = 0;
+    for (const BatchReq &R : P.in) streams += R.k;
+    const bool many = streams >= (uint64_t)cus * 512;
+    out->cfg.segment_bytes = many ? 262144 : 131072;
+    out->cfg.wave_min_bytes = many ? 16384 : 2048;
+    out->pack = many ? 4 : 2;
+    plan_batch(reqs, n, out->cfg, &P, out->pack);
+}
+
 hipError_t launch_grouped(const Grouped &g, const BatchReq *d_reqs, const uint64_t *d_prefix,
                           unsigned long long *d_counters, const BatchArgs &base,
                           uint64_t grid_cap, int engine, hipStream_t st)
@@ -202,6 +229,8 @@ struct mrg_batch_s {
     // mrg_batch_plan_groups state it (a small batch runs in finer items)
     uint64_t cfg_items = 0, cfg_scratch = 0;
     bool sizes_given = false;        // segment_bytes or wave_min_bytes asked for
+    mrg_batch_config run_cfg = {};   // the sizes the plan is cut by
+    uint32_t pack = 0;
     mrg::BatchReq *d_reqs = nullptr;
     uint64_t *d_prefix = nullptr;
     uint64_t *d_solo = nullptr;      // [nreq][2]: {0, items of request r}
@@ -263,27 +292,13 @@ mrg_status upload(T **dst, const std::vector<T> &src, const char *what)
 mrg_status build_plan(mrg_batch b)
 {
     free_plan(b);
-    mrg::HostPlan hp;
-    mrg::plan_batch(b->reqs.data(), b->reqs.size(), b->cfg, &hp);
-    b->cfg_items = hp.plan.total_items;
-    b->cfg_scratch = hp.scratch_slots;
-    // A batch of under 16 GiB whose item sizes were left to the library runs
-    // as one launch of finer items: under the sizes for batches that fill the
-    // chip many times over, its three launches each ended in a few long items
-    // (64 streams of 16 KiB drawn in series, 16 short streams in one wave).
-    // With fewer streams than two waves of lanes per SIMD, rows from 2 KiB on
-    // go to whole waves too (300 requests, 0.97 GB: 866 -> 317 us, with rows
-    // under 16 KiB in lanes 434; 1000 requests of 490,000 streams, 5.6 GB:
-    // 1956 against 1426 us the other way round).
-    if (!b->sizes_given && hp.bytes < (uint64_t)16 << 30) {
-        uint64_t streams = 0;
-        for (const mrg::BatchReq &R : hp.in) streams += R.k;
-        const bool many = streams >= (uint64_t)b->tabs.cus * 512;
-        mrg_batch_config c = b->cfg;
-        c.segment_bytes = many ? 262144 : 131072;
-        c.wave_min_bytes = many ? 16384 : 2048;
-        mrg::plan_batch(b->reqs.data(), b->reqs.size(), c, &hp, many ? 4 : 2);
-    }
+    mrg::RunPlan run;
+    mrg::plan_run(b->reqs.data(), b->reqs.size(), b->cfg, b->sizes_given, b->tabs.cus, &run);
+    mrg::HostPlan &hp = run.host;
+    b->cfg_items = run.cfg_items;
+    b->cfg_scratch = run.cfg_scratch;
+    b->run_cfg = run.cfg;
+    b->pack = run.pack;
     b->plan = std::move(hp.plan);
     b->req_of = std::move(hp.req_of);
     b->cb_prefix = std::move(hp.cb_prefix);
@@ -370,6 +385,35 @@ mrg_status capture(mrg_batch b)
     e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
     if (e != hipSuccess) return hip_error(e, "hipGraphInstantiate");
     return MRG_OK;
+}
+
+// The checks of a request that need no stream set.
+mrg_status check_kinds(const mrg_request *reqs, uint64_t n)
+{
+    for (uint64_t i = 0; i < n; ++i) {
+        const mrg_request &q = reqs[i];
+        if (q.dtype != MRG_U32 && q.dtype != MRG_F32 && q.dtype != MRG_F64)
+            return set_error(MRG_EINVAL, "request %llu: unknown dtype %d", (unsigned long long)i,
+                             (int)q.dtype);
+        if (q.flags & ~(uint32_t)MRG_REQ_SUBSTREAMS)
+            return set_error(MRG_EINVAL, "request %llu: unknown flags", (unsigned long long)i);
+    }
+    return MRG_OK;
+}
+
+void fill_plan(const mrg::Grouped &g, uint64_t scratch, const mrg_batch_config &cfg, uint32_t pack,
+               uint64_t grid_cap, mrg_batch_plan_t *out)
+{
+    uint64_t most = 0;
+    for (const mrg::Grouped::Group &G : g.groups) most = std::max(most, G.items);
+    *out = {};
+    out->items = g.total_items;
+    out->scratch_states = scratch;
+    out->segment_bytes = cfg.segment_bytes;
+    out->wave_min_bytes = cfg.wave_min_bytes;
+    out->groups = (uint32_t)g.groups.size();
+    out->streams_per_item = pack;
+    out->grid = (uint32_t)std::min(grid_cap, most);
 }
 
 mrg_status validate(mrg_streamset ss, const mrg_request *reqs, uint64_t n)
@@ -574,19 +618,33 @@ mrg_status mrg_batch_info(mrg_batch b, mrg_batch_info_t *info)
     return MRG_OK;
 }
 
+mrg_status mrg_batch_running_plan(mrg_batch b, mrg_batch_plan_t *plan)
+{
+    if (!b || !plan) return set_error(MRG_EINVAL, "null argument");
+    fill_plan(b->plan, b->scratch_slots, b->run_cfg, b->pack, b->grid_cap, plan);
+    return MRG_OK;
+}
+
+mrg_status mrg_batch_plan(const mrg_request *reqs, uint64_t n_reqs, const mrg_batch_config *cfg,
+                          int cus, mrg_batch_plan_t *plan)
+{
+    if ((!reqs && n_reqs) || !plan) return set_error(MRG_EINVAL, "null argument");
+    if (cus < 1) return set_error(MRG_EINVAL, "no compute units");
+    if (mrg_status st = check_kinds(reqs, n_reqs)) return st;
+    const mrg_batch_config c = effective(cfg);
+    mrg::RunPlan run;
+    mrg::plan_run(reqs, n_reqs, c, sizes_given(cfg), cus, &run);
+    fill_plan(run.host.plan, run.host.scratch_slots, run.cfg, run.pack,
+              (uint64_t)cus * c.waves_per_cu, plan);
+    return MRG_OK;
+}
+
 mrg_status mrg_batch_plan_groups(const mrg_request *reqs, uint64_t n_reqs,
                                  const mrg_batch_config *cfg, mrg_plan_group *groups,
                                  uint32_t *n_groups, uint64_t *pos, uint64_t *items)
 {
     if ((!reqs && n_reqs) || !groups || !n_groups) return set_error(MRG_EINVAL, "null argument");
-    for (uint64_t i = 0; i < n_reqs; ++i) {
-        const mrg_request &q = reqs[i];
-        if (q.dtype != MRG_U32 && q.dtype != MRG_F32 && q.dtype != MRG_F64)
-            return set_error(MRG_EINVAL, "request %llu: unknown dtype %d", (unsigned long long)i,
-                             (int)q.dtype);
-        if (q.flags & ~(uint32_t)MRG_REQ_SUBSTREAMS)
-            return set_error(MRG_EINVAL, "request %llu: unknown flags", (unsigned long long)i);
-    }
+    if (mrg_status st = check_kinds(reqs, n_reqs)) return st;
     mrg::HostPlan P;
     mrg::plan_batch(reqs, n_reqs, mrg::batch_config(cfg), &P);
     const mrg::Grouped &g = P.plan;

@@ -1,6 +1,6 @@
-// Batched generation that allocates nothing: the same plan and persistent
-// kernels as mrg_batch_create + mrg_batch_run, with every device buffer the
-// run needs (request descriptors, item prefixes, the copy-back table, the
+// Batched generation that allocates nothing: the plan that mrg_batch_plan_groups
+// states and the persistent kernels of mrg_batch_run (which runs batches of
+// under 16 GiB in finer items), with every device buffer the run needs (request descriptors, item prefixes, the copy-back table, the
 // claim counters and the staged end states of multi-segment streams) carved
 // out of one fixed device array, for callers that cannot call hipMalloc.
 //

@@ -103,3 +103,50 @@ def test_plan_rejects_bad_dtype_and_flags():
         mg.batch_plan_groups([(0, 1, 1, 0, 0, 0, 8)])
     groups, pos, items = mg.batch_plan_groups([])
     assert groups == [] and pos == [] and items == []
+
+
+def test_small_batches_state_the_plan_that_runs():
+    """Under 16 GiB with the library's sizes: one launch of every dtype's items."""
+    rows = [(0, 100, 50, 0, 0, mg.U32, 0), (100, 10, 5000, 0, 0, mg.F64, 0),
+            (110, 1, 1 << 20, 0, 0, mg.F32, 0)]
+    p = mg.batch_plan(rows)
+    assert p["groups"] == 1 and p["streams_per_item"] >= 1
+    k, n, dt = ([r[i] for r in rows] for i in (1, 2, 5))
+    items = 0
+    for kk, nn, d in zip(k, n, dt):
+        e = es(d)
+        if nn * e < p["wave_min_bytes"] or nn * e > p["segment_bytes"]:
+            items += expected_items(kk, nn, d, p["segment_bytes"], p["wave_min_bytes"])
+        else:
+            items += -(-kk // min(p["streams_per_item"], p["segment_bytes"] // (nn * e)))
+    assert p["items"] == items
+    assert p["grid"] == min(items, 256 * 16)
+    assert p["scratch_states"] == 1  # the one stream of several segments
+
+
+@pytest.mark.parametrize("cfg", [dict(segment_bytes=32 << 10), dict(wave_min_bytes=4096)], ids=str)
+def test_given_sizes_run_the_grouped_plan(cfg):
+    rows = [(0, 100, 50, 0, 0, mg.U32, 0), (100, 10, 5000, 0, 0, mg.F64, 0),
+            (110, 3, 1 << 18, 0, 0, mg.F32, 0)]
+    groups, _, items = mg.batch_plan_groups(rows, mg.batch_config(**cfg))
+    p = mg.batch_plan(rows, mg.batch_config(**cfg))
+    assert p["items"] == sum(items) and p["groups"] == len(groups)
+    assert p["streams_per_item"] == 0
+    assert all(p[key] == v for key, v in cfg.items())
+
+
+def test_large_batches_run_the_grouped_plan():
+    n = 1 << 20
+    rows = [(0, 4096, n, 0, 0, mg.U32, 0)]  # 16 GiB
+    p = mg.batch_plan(rows)
+    assert p["items"] == sum(mg.batch_plan_groups(rows)[2]) and p["streams_per_item"] == 0
+    assert mg.batch_plan([(0, 4095, n, 0, 0, mg.U32, 0)])["streams_per_item"] > 0
+
+
+def test_plan_refuses_what_groups_refuse():
+    for row in ((0, 1, 1, 0, 0, 7, 0), (0, 1, 1, 0, 0, 0, 8)):
+        with pytest.raises(mg.MRGError):
+            mg.batch_plan([row])
+    with pytest.raises(mg.MRGError):
+        mg.batch_plan([], cus=0)
+    assert mg.batch_plan([])["items"] == 0 and mg.batch_plan([])["groups"] == 0

@@ -450,3 +450,28 @@ def test_small_batch_in_one_launch(mg, requests, streams, length):
             times = b.request_times()
             assert (times > 0).all()
     ss.close()
+
+
+@pytest.mark.parametrize("cfg", [{}, dict(segment_bytes=32 << 10), dict(waves_per_cu=4)], ids=str)
+def test_running_plan_is_what_runs(mg, cfg):
+    """running_plan states the captured launches: those of batch_plan on this
+    device, and of batch_plan_groups where the sizes were given."""
+    import torch
+    say("running plan", cfg)
+    rng = np.random.default_rng(SEED + 77)
+    rows, outs, specs, nstreams = make_plain(mg, rng, 30, 100, 40000, 2_000_000)
+    ss = mg.StreamSet(nstreams, seed=[1, 2, 3, 4, 5, 6])
+    conf = mg.batch_config(**cfg)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    with mg.Batch(ss, rows, conf) as b:
+        plan = b.running_plan()
+        assert plan == mg.batch_plan(rows, conf, cus)
+        groups, _, items = mg.batch_plan_groups(rows, conf)
+        if "segment_bytes" in cfg:
+            assert plan["items"] == sum(items) and plan["groups"] == len(groups)
+        else:
+            assert plan["groups"] == 1
+        assert plan["grid"] <= cus * b.info()["waves_per_cu"]
+        b.run()
+        torch.cuda.synchronize()
+    ss.close()
