@@ -389,14 +389,14 @@ typedef struct mrg_batch_s *mrg_batch;
  * short streams' items of every dtype, largest first, and capture one
  * hipGraph (one reset of stamps and counters, a persistent kernel per group,
  * then the copy-back of end states).  A batch of under 16 GiB of output whose
- * segment_bytes and wave_min_bytes are left to their defaults runs the same
+ * segment_bytes and wave_min_bytes are the defaults runs the same
  * requests as one group of finer items of every dtype (the plan that
  * mrg_batch_info and mrg_batch_plan_groups state is the one under cfg,
  * mrg_batch_running_plan states the one that runs).  Every non-empty request's
  * d_out must be device memory of the set's device holding its output inside
- * one allocation (else MRG_EINVAL / MRG_ERANGE naming the request).  reqs is copied; cfg may be
- * NULL.  The plan refers to ss and to the output buffers, which must outlive
- * it.  Free with mrg_batch_destroy. */
+ * one allocation (else MRG_EINVAL / MRG_ERANGE naming the request).  reqs is
+ * copied; cfg may be NULL.  The plan refers to ss and to the output buffers,
+ * which must outlive it.  Free with mrg_batch_destroy. */
 mrg_status mrg_batch_create(mrg_batch *out, mrg_streamset ss, const mrg_request *reqs,
                             uint64_t n_reqs, const mrg_batch_config *cfg);
 

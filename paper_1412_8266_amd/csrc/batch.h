@@ -145,7 +145,7 @@ struct RunPlan {
     mrg_batch_config cfg;             // the sizes `host` is cut by
     uint32_t pack;                    // as for plan_batch
 };
-void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool sizes_given,
+void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool own_sizes,
               int cus, RunPlan *out);
 // cfg with defaults filled in (cfg may be NULL).
 mrg_batch_config batch_config(const mrg_batch_config *cfg);

@@ -164,7 +164,7 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
 // go to whole waves too (300 requests, 0.97 GB: 866 -> 317 us, with rows
 // under 16 KiB in lanes 434; 1000 requests of 490,000 streams, 5.6 GB:
 // 1956 against 1426 us the other way round).
-void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool sizes_given,
+void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool own_sizes,
               int cus, RunPlan *out)
 {
     HostPlan &P = out->host;
@@ -173,7 +173,7 @@ void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, 
     out->pack = 0;
     out->cfg_items = P.plan.total_items;
     out->cfg_scratch = P.scratch_slots;
-    if (sizes_given || P.bytes >= (uint64_t)16 << 30) return;
+    if (own_sizes || P.bytes >= (uint64_t)16 << 30) return;
     uint64_t streams = 0;
     for (const BatchReq &R : P.in) streams += R.k;
     const bool many = streams >= (uint64_t)cus * 512;
@@ -228,7 +228,6 @@ struct mrg_batch_s {
     // items and staged states of the plan under cfg, as mrg_batch_info and
     // mrg_batch_plan_groups state it (a small batch runs in finer items)
     uint64_t cfg_items = 0, cfg_scratch = 0;
-    bool sizes_given = false;        // segment_bytes or wave_min_bytes asked for
     mrg_batch_config run_cfg = {};   // the sizes the plan is cut by
     uint32_t pack = 0;
     mrg::BatchReq *d_reqs = nullptr;
@@ -262,18 +261,26 @@ void free_plan(mrg_batch b)
     b->d_scratch = nullptr;
 }
 
+constexpr uint64_t kSegmentBytes = 256 * 1024, kWaveMinBytes = 16 * 1024;
+
 mrg_batch_config effective(const mrg_batch_config *c)
 {
     mrg_batch_config e = {};
     if (c) e = *c;
-    if (!e.segment_bytes) e.segment_bytes = 256 * 1024;
+    if (!e.segment_bytes) e.segment_bytes = kSegmentBytes;
     if (!e.waves_per_cu) e.waves_per_cu = 16;
-    if (!e.wave_min_bytes) e.wave_min_bytes = 16 * 1024;
+    if (!e.wave_min_bytes) e.wave_min_bytes = kWaveMinBytes;
     if (e.schedule != MRG_SCHEDULE_STATIC) e.schedule = MRG_SCHEDULE_DYNAMIC;
     return e;
 }
 
-bool sizes_given(const mrg_batch_config *c) { return c && (c->segment_bytes || c->wave_min_bytes); }
+// Whether cfg asks for item sizes of its own.  The defaults by value are the
+// defaults: an effective configuration taken from mrg_batch_info plans the batch
+// it came from.
+bool own_sizes(const mrg_batch_config &cfg)
+{
+    return cfg.segment_bytes != kSegmentBytes || cfg.wave_min_bytes != kWaveMinBytes;
+}
 
 template <class T>
 mrg_status upload(T **dst, const std::vector<T> &src, const char *what)
@@ -293,7 +300,7 @@ mrg_status build_plan(mrg_batch b)
 {
     free_plan(b);
     mrg::RunPlan run;
-    mrg::plan_run(b->reqs.data(), b->reqs.size(), b->cfg, b->sizes_given, b->tabs.cus, &run);
+    mrg::plan_run(b->reqs.data(), b->reqs.size(), b->cfg, own_sizes(b->cfg), b->tabs.cus, &run);
     mrg::HostPlan &hp = run.host;
     b->cfg_items = run.cfg_items;
     b->cfg_scratch = run.cfg_scratch;
@@ -504,7 +511,6 @@ mrg_status mrg_batch_create(mrg_batch *out, mrg_streamset ss, const mrg_request 
     b->device = ss->device;
     b->reqs.assign(reqs, reqs + n_reqs);
     b->cfg = effective(cfg);
-    b->sizes_given = sizes_given(cfg);
     b->engine = mrg::current_tuning().engine;
     if ((st = mrg::device_tables(ss->device, &b->tabs))) {
         delete b;
@@ -633,7 +639,7 @@ mrg_status mrg_batch_plan(const mrg_request *reqs, uint64_t n_reqs, const mrg_ba
     if (mrg_status st = check_kinds(reqs, n_reqs)) return st;
     const mrg_batch_config c = effective(cfg);
     mrg::RunPlan run;
-    mrg::plan_run(reqs, n_reqs, c, sizes_given(cfg), cus, &run);
+    mrg::plan_run(reqs, n_reqs, c, own_sizes(c), cus, &run);
     fill_plan(run.host.plan, run.host.scratch_slots, run.cfg, run.pack,
               (uint64_t)cus * c.waves_per_cu, plan);
     return MRG_OK;
@@ -695,11 +701,9 @@ mrg_status mrg_batch_autotune(mrg_batch b, const mrg_batch_config *cands, uint32
     uint32_t best = 0;
     float best_ms = 0;
     const mrg_batch_config keep = b->cfg;
-    const bool keep_given = b->sizes_given;
     for (uint32_t i = 0; i < n_cands && status == MRG_OK; ++i) {
         (void)hipStreamSynchronize(st);
         b->cfg = effective(&cands[i]);
-        b->sizes_given = sizes_given(&cands[i]);
         if ((status = build_plan(b)) || (status = capture(b))) break;
         if ((status = mrg_batch_run(b, stream))) break;  // warm-up
         (void)hipEventRecord(t0, st);
@@ -726,12 +730,10 @@ mrg_status mrg_batch_autotune(mrg_batch b, const mrg_batch_config *cands, uint32
     if (e != hipSuccess && status == MRG_OK) status = hip_error(e, "state restore");
     if (status == MRG_OK) {
         b->cfg = effective(&cands[best]);
-        b->sizes_given = sizes_given(&cands[best]);
         status = build_plan(b);
         if (status == MRG_OK) status = capture(b);
     } else {
         b->cfg = keep;
-        b->sizes_given = keep_given;
         if (build_plan(b) == MRG_OK) (void)capture(b);
     }
     (void)hipStreamSynchronize(st);

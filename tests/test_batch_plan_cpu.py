@@ -150,3 +150,11 @@ def test_plan_refuses_what_groups_refuse():
     with pytest.raises(mg.MRGError):
         mg.batch_plan([], cus=0)
     assert mg.batch_plan([])["items"] == 0 and mg.batch_plan([])["groups"] == 0
+
+
+def test_default_sizes_by_value_are_the_defaults():
+    """A configuration read back (info) plans as the one it was made from."""
+    rows = [(0, 100, 50, 0, 0, mg.U32, 0), (100, 10, 5000, 0, 0, mg.F64, 0)]
+    for cfg in (dict(segment_bytes=256 << 10, wave_min_bytes=16 << 10),
+                dict(segment_bytes=256 << 10), dict(wave_min_bytes=16 << 10)):
+        assert mg.batch_plan(rows, mg.batch_config(**cfg)) == mg.batch_plan(rows)

@@ -471,7 +471,12 @@ def test_running_plan_is_what_runs(mg, cfg):
             assert plan["items"] == sum(items) and plan["groups"] == len(groups)
         else:
             assert plan["groups"] == 1
-        assert plan["grid"] <= cus * b.info()["waves_per_cu"]
+        info = b.info()
+        assert plan["grid"] <= cus * info["waves_per_cu"]
+        again = mg.batch_config(**{name: info[name] for name in
+                                   ("segment_bytes", "wave_min_bytes", "waves_per_cu", "schedule")})
+        b.autotune([again], 1)
+        assert b.running_plan() == plan
         b.run()
         torch.cuda.synchronize()
     ss.close()
