@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <iterator>
@@ -16,6 +17,9 @@ using mrg::hip_error;
 using mrg::set_error;
 
 namespace mrg {
+
+// the default sizes of mrg_batch_config
+constexpr uint64_t kSegmentBytes = 256 * 1024, kWaveMinBytes = 16 * 1024;
 
 void group_requests(const std::vector<BatchReq> &in, Grouped *out)
 {
@@ -156,14 +160,63 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
     else group_requests(P.in, &P.plan);
 }
 
+// Shortest rows, in bytes, that go to whole waves in a small batch, and the most
+// of their streams that a wave item holds.  In lanes a batch lasts as long as its
+// longest row takes one lane (60 to 95 ns a value, more where every SIMD has
+// several such waves); in waves each stream costs its wave a start of 14 us and
+// 0.2 ns a byte, 8 waves a CU.  Of 2 to 16 KiB the least estimate of both is
+// taken, the shorter part counted 0.6 beside the longer one; 2 KiB where that
+// makes at most a wave to every other CU (22 rows 20 us in waves, 26 in lanes).
+// 300 requests of 0.97 GB 866 us grouped, 434 with rows of under 16 KiB in lanes,
+// 317 in waves from 2 KiB on; but 122000 rows of 520 uint32 162 us in lanes and
+// 830 in waves, 20000 of 1000 146 and 218.  Over 312 mixes of up to 6 GB the
+// choice takes 1.02 of the best of the four and 0.54 of the grouped plan's time
+// on average, at worst 1.18 of the one and 1.16 of the other (62 us: 72).
+struct SmallSizes { uint64_t wave_min; uint32_t pack; };
+SmallSizes small_sizes(const std::vector<BatchReq> &in, uint64_t streams, const mrg_batch_config &cfg,
+                       int cus)
+{
+    static const double kLane[3] = {0.060, 0.065, 0.095};  // us per value: u32, f32, f64
+    const double par = (double)cus * std::min<uint32_t>(cfg.waves_per_cu, 8);
+    SmallSizes best = {kWaveMinBytes, 1};
+    double best_us = 0;
+    for (uint64_t w = 2048; w <= kWaveMinBytes; w *= 2) {
+        double chain = 0, wave = 0;
+        uint64_t lanes = 0, nw = 0;
+        for (const BatchReq &R : in) {
+            const uint64_t bytes = R.n * (R.dtype == 2 ? 8 : 4);
+            if (bytes < w) {
+                lanes += R.k;
+                chain = std::max(chain, (double)R.n * kLane[R.dtype]);
+            } else {
+                nw += R.k;
+                wave += (double)R.k * ((bytes < 131072 ? 14.0 : 0.0) + 0.0002 * (double)bytes);
+            }
+        }
+        chain *= 1.0 + (double)lanes / ((double)cus * 512);
+        const uint32_t pack = nw <= 1024 ? 1 : streams < (uint64_t)cus * 512 ? 2 : 4;
+        const double few = nw <= 1024 ? 1 : 2;  // streams in series in the last wave
+        if (nw)
+            wave = std::max(wave / par, std::min(std::ceil((double)nw / (par * few)), 2.0) * few * 15) + 10;
+        if (w == 2048 && nw <= (uint64_t)cus / 2) return {w, 1};
+        double us = std::max(chain, wave) + 0.6 * std::min(chain, wave);
+        if (w < kWaveMinBytes) us *= 1.2;  // the estimate's own error
+        if (w == 2048 || us <= best_us) {
+            best = {w, pack};
+            best_us = us;
+        }
+    }
+    return best;
+}
+
 // A batch of under 16 GiB whose item sizes were left to the library runs
 // as one launch of finer items: under the sizes for batches that fill the
 // chip many times over, its three launches each ended in a few long items
-// (64 streams of 16 KiB drawn in series, 16 short streams in one wave).
-// With fewer streams than two waves of lanes per SIMD, rows from 2 KiB on
-// go to whole waves too (300 requests, 0.97 GB: 866 -> 317 us, with rows
-// under 16 KiB in lanes 434; 1000 requests of 490,000 streams, 5.6 GB:
-// 1956 against 1426 us the other way round).
+// (64 streams of 16 KiB drawn in series, 16 short streams in one wave).  One
+// launch against groups, in parts of the time: 6 GB 0.73-0.86, 12-14 GB
+// 0.87-0.94, 20 GB 0.90-0.96, 40 GB 0.93-0.99, 70 GB 0.89-1.01.  With more
+// streams than two waves of lanes per SIMD the long rows' items stay at 256 KiB
+// (1000 requests of 490,000 streams, 5.6 GB: 1426 us, in 128 KiB 1956).
 void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, bool own_sizes,
               int cus, RunPlan *out)
 {
@@ -176,10 +229,10 @@ void plan_run(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg, 
     if (own_sizes || P.bytes >= (uint64_t)16 << 30) return;
     uint64_t streams = 0;
     for (const BatchReq &R : P.in) streams += R.k;
-    const bool many = streams >= (uint64_t)cus * 512;
-    out->cfg.segment_bytes = many ? 262144 : 131072;
-    out->cfg.wave_min_bytes = many ? 16384 : 2048;
-    out->pack = many ? 4 : 2;
+    const SmallSizes sizes = small_sizes(P.in, streams, cfg, cus);
+    out->cfg.segment_bytes = streams >= (uint64_t)cus * 512 ? kSegmentBytes : kSegmentBytes / 2;
+    out->cfg.wave_min_bytes = sizes.wave_min;
+    out->pack = sizes.pack;
     plan_batch(reqs, n, out->cfg, &P, out->pack);
 }
 
@@ -261,15 +314,13 @@ void free_plan(mrg_batch b)
     b->d_scratch = nullptr;
 }
 
-constexpr uint64_t kSegmentBytes = 256 * 1024, kWaveMinBytes = 16 * 1024;
-
 mrg_batch_config effective(const mrg_batch_config *c)
 {
     mrg_batch_config e = {};
     if (c) e = *c;
-    if (!e.segment_bytes) e.segment_bytes = kSegmentBytes;
+    if (!e.segment_bytes) e.segment_bytes = mrg::kSegmentBytes;
     if (!e.waves_per_cu) e.waves_per_cu = 16;
-    if (!e.wave_min_bytes) e.wave_min_bytes = kWaveMinBytes;
+    if (!e.wave_min_bytes) e.wave_min_bytes = mrg::kWaveMinBytes;
     if (e.schedule != MRG_SCHEDULE_STATIC) e.schedule = MRG_SCHEDULE_DYNAMIC;
     return e;
 }
@@ -279,7 +330,7 @@ mrg_batch_config effective(const mrg_batch_config *c)
 // it came from.
 bool own_sizes(const mrg_batch_config &cfg)
 {
-    return cfg.segment_bytes != kSegmentBytes || cfg.wave_min_bytes != kWaveMinBytes;
+    return cfg.segment_bytes != mrg::kSegmentBytes || cfg.wave_min_bytes != mrg::kWaveMinBytes;
 }
 
 template <class T>

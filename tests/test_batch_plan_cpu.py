@@ -158,3 +158,26 @@ def test_default_sizes_by_value_are_the_defaults():
     for cfg in (dict(segment_bytes=256 << 10, wave_min_bytes=16 << 10),
                 dict(segment_bytes=256 << 10), dict(wave_min_bytes=16 << 10)):
         assert mg.batch_plan(rows, mg.batch_config(**cfg)) == mg.batch_plan(rows)
+
+
+@pytest.mark.parametrize("k, n, dt, wave_min, pack", [
+    (20, 520, mg.U32, 2 << 10, 1),       # a few rows: a wave each
+    (128, 1000, mg.F32, 2 << 10, 1),     # the most of them
+    (7000, 520, mg.U32, 16 << 10, 1),    # many short rows: lanes (162 us, in waves 830 at 122000)
+    (122000, 520, mg.U32, 16 << 10, 1),
+    (20000, 1000, mg.F64, 16 << 10, 1),
+    (500, 4000, mg.U32, 8 << 10, 1),     # few long rows: waves
+    (3000, 4095, mg.U32, 8 << 10, 2),    # whose waves take two
+], ids=str)
+def test_small_batches_weigh_lanes_against_waves(k, n, dt, wave_min, pack):
+    p = mg.batch_plan([(0, k, n, 0, 0, dt, 0)])
+    assert (p["wave_min_bytes"], p["streams_per_item"]) == (wave_min, pack)
+    # the requests' cut does not depend on how the rows are listed
+    half = [(0, k // 2, n, 0, 0, dt, 0), (k // 2, k - k // 2, n, 0, 0, dt, 0)]
+    assert mg.batch_plan(half)["wave_min_bytes"] == wave_min
+
+
+def test_many_streams_keep_long_segments():
+    rows = [(0, 131072, 100, 0, 0, mg.U32, 0), (131072, 8, 1 << 20, 0, 0, mg.U32, 0)]
+    assert mg.batch_plan(rows)["segment_bytes"] == 256 << 10
+    assert mg.batch_plan(rows[1:])["segment_bytes"] == 128 << 10
