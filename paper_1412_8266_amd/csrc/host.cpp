@@ -523,8 +523,11 @@ mrg::FillLaunch plan_fill(const mrg::FillTuning &tune, int cus, uint64_t set_n, 
                 fl = mrg::FillLaunch();
         }
         // lane per stream, rows of whole 4 KiB on lines: two lanes per stream
-        // (fill_sm_kernel's HALVES; other row lengths lose by it: 131072 x 1536
-        // float32 171 -> 189 us, x 512 59 -> 62)
+        // (fill_sm_kernel's HALVES: float32 rows of 4 KiB 65536 80 -> 59 us, 262144
+        // 306 -> 226; of 12 KiB, from 65536 on in lanes, 240 -> 171 and 730 -> 682,
+        // at 131072 367 and 365, binary64 187 -> 157 and 637 -> 615; rows of 8 KiB
+        // are whole chunks of the wave writer.  Other row lengths lose by it:
+        // 131072 x 1536 float32 171 -> 189 us, x 512 59 -> 62)
         if (tune.strategy == 0 && fl.kernel == 0 && tune.tile_bytes == 0 &&
             out % 128 == 0 && n_per_stream * es % 4096 == 0) {
             fl.kernel = 4;

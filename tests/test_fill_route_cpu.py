@@ -148,3 +148,18 @@ LANE_RULE = [(1, 380, U32, 0, False), (1, 384, U32, 4, True), (1, 384, U32, 0, F
 def test_shortest_row_of_several_lanes(count, row, dtype, off, several):
     r = rows(count, row // (8 if dtype == F64 else 4), dtype, off)
     assert (r.kernel == WAVE) == several
+
+
+@pytest.mark.parametrize("dtype,es", [(U32, 4), (F32, 4), (F64, 8)])
+def test_rows_of_whole_4_kib_take_two_lanes(dtype, es):
+    """On lines, in the lane writer: 4 KiB at any number of streams it takes,
+    12 KiB from a wave of lanes per SIMD on."""
+    n = 4096 // es
+    for count in (40000, 65536, 262144):
+        assert rows(count, n, dtype).kernel == HALVES
+        assert rows(count, n, dtype, 4).kernel != HALVES
+        assert rows(count, n + 1, dtype).kernel != HALVES
+        assert rows(count, n + 128 // es, dtype).kernel != HALVES
+        assert rows(count, 2 * n, dtype).kernel == WAVE
+    assert rows(65535, 3 * n, dtype).kernel == WAVE
+    assert rows(65536, 3 * n, dtype).kernel == HALVES

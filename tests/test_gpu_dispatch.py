@@ -57,6 +57,8 @@ ROWS += [(8192, 96, 2, 0), (8192, 80, 2, 0), (16384, 352, 0, 0), (16384, 384, 0,
 
 # two lanes per stream (rows of 4 KiB on lines): whole and partial last waves
 ROWS += [(65536, 1024, 0, 0), (65553, 1024, 1, 0), (65569, 512, 2, 0), (65600, 1024, 0, 32)]
+# and rows of 12 KiB, from 65536 on
+ROWS += [(65536, 3072, 0, 0), (65553, 1536, 2, 0)]
 
 
 @pytest.mark.parametrize("count,n,dtype,off", ROWS)
