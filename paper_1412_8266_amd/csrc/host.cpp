@@ -571,8 +571,9 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     // each player's cards in a row: items of KB = min(K, 64) card columns
     // x T players (R = 64 / KB lanes per column, Ts = T / R players
     // each), T chosen for about 4 items per resident wave, with at least 64
-    // players per lane, 32 where that leaves under four waves per CU (65536 x
-    // 52: with 256 18.4 us, with 32 10.6, with 16 14.0).  While the items at 64
+    // players per lane, 32 where that leaves four waves per CU or fewer (65536 x
+    // 52: with 256 18.4 us, with 64, a wave on each SIMD, 11.5, with 32 10.3, with
+    // 16 14.0; 70400 x 52 has more, 32 loses 2 %).  While the items at 64
     // players do not fill the chip, up to 16 waves to a workgroup, which count
     // themselves in together, and the stream moved in the kernel; then a wave
     // to a workgroup, since the waves of one share a CU and write far apart, and
@@ -591,7 +592,7 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     const uint64_t ts_max = (players + A.R - 1) / A.R;
     const uint64_t at64 = nkb * ((ts_max + 63) / 64);
     const bool few = at64 < (uint64_t)cus * 15;
-    const uint64_t ts_min = at64 < (uint64_t)cus * 4 ? 32 : 64;
+    const uint64_t ts_min = at64 <= (uint64_t)cus * 4 ? 32 : 64;
     uint64_t Ts = ts_max;
     if (nkb < target) {
         const uint64_t segs = (target + nkb - 1) / nkb;

@@ -9,15 +9,16 @@ namespace mrg {
 
 constexpr int kTableWords = 2 * kTableWindows * kTableWindowWords;
 
-// A set's device memory: the six state planes, then in sets of up to 2^20
-// streams one ticket word per stream (arrive() in gen_device.hpp), 0 between launches and set by the kernels that
-// create the streams and by mrg_set_states: fills of one stream that a caller
-// failed to order can leave its ticket in between, and every later fill would
-// then move the stream before all its parts have read the state.  Arrivals at one 128-byte line queue up, 20 ns each over
-// the eight XCDs, so sets of up to 4096 streams give each ticket its own line.
-// Larger sets than 2^20 streams have no tickets: few of their fills are cut
-// into parts, a launch moves those, and every set would pay a sixth more memory
-// and time to create (2^24 streams: 64 of 448 MiB).
+// A set's device memory: the six state planes, then in sets of up to 2^20 streams
+// one ticket word per stream (arrive() in gen_device.hpp), 0 between launches and
+// set by the kernels that create the streams and by mrg_set_states: fills of one
+// stream that a caller failed to order can leave its ticket in between, and every
+// later fill would then move the stream before all its parts have read the state.
+// Arrivals at one 128-byte line queue up, 20 ns each over the eight XCDs, so sets
+// of up to 4096 streams give each ticket its own line. Larger sets than 2^20
+// streams have no tickets: few of their fills are cut into parts, a launch moves
+// those, and every set would pay a sixth more memory and time to create (2^24
+// streams: 64 of 448 MiB).
 __host__ __device__ constexpr uint64_t ticket_pitch(uint64_t n)
 {
     return n <= 4096 ? 32 : n <= ((uint64_t)1 << 20) ? 1 : 0;
@@ -27,13 +28,13 @@ __host__ __device__ constexpr uint64_t ticket_of(uint64_t n, uint64_t i)
     return 6 * n + i * ticket_pitch(n);
 }
 // Whether the parts of a fill of `count` streams of a set of n count themselves
-// in, and the last one moves its stream (a single part does so without a
-// ticket); else a launch follows (1.5-4 us).  The
-// arrivals at one line must not take longer.  One per wave: 256 a line (5 us in
-// a row).  One per lane, up to 32 of them in a step of a wave: 256 a ticket, and
-// 2048 a line, 4096 where the fill is long enough to hide them (segments of 16 x
-// 16384 uint32 of a set with packed tickets 15.8 us at 4096 a line, 9.7 with a
-// launch; 32 x 4096 7.9 at 2048 and 7.9-8.4; 1024 x 16384 20.3 at 4096 and 21.4).
+// in, and the last one moves its stream (a single part does so without a ticket);
+// else a launch follows (1.5-4 us).  The arrivals at one line must not take
+// longer.  One per wave: 256 a line (5 us in a row).  One per lane, up to 32 of
+// them in a step of a wave: 256 a ticket, and 2048 a line, 4096 where the fill is
+// long enough to hide them (segments of 16 x 16384 uint32 of a set with packed
+// tickets 15.8 us at 4096 a line, 9.7 with a launch; 32 x 4096 7.9 at 2048 and
+// 7.9-8.4; 1024 x 16384 20.3 at 4096 and 21.4).
 constexpr bool parts_move(uint64_t n, uint64_t count, uint64_t parts, bool per_lane)
 {
     const uint64_t line = ticket_pitch(n) > 1 || count == 1 ? 1 : count < 32 ? count : 32;
