@@ -162,16 +162,18 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
 
 // Shortest rows, in bytes, that go to whole waves in a small batch, and the most
 // of their streams that a wave item holds.  In lanes a batch lasts as long as its
-// longest row takes one lane (60 to 95 ns a value, more where every SIMD has
-// several such waves); in waves each stream costs its wave a start of 14 us and
-// 0.2 ns a byte, 8 waves a CU.  Of 2 to 16 KiB the least estimate of both is
-// taken, the shorter part counted 0.6 beside the longer one; 2 KiB where that
-// makes at most a wave to every other CU (22 rows 20 us in waves, 26 in lanes).
-// 300 requests of 0.97 GB 866 us grouped, 434 with rows of under 16 KiB in lanes,
-// 317 in waves from 2 KiB on; but 122000 rows of 520 uint32 162 us in lanes and
-// 830 in waves, 20000 of 1000 146 and 218.  Over 312 mixes of up to 6 GB the
-// choice takes 1.02 of the best of the four and 0.54 of the grouped plan's time
-// on average, at worst 1.18 of the one and 1.16 of the other (62 us: 72).
+// longest row takes one lane (60 to 95 ns a value) and all of them the lanes of a
+// wave per SIMD; in waves each stream costs its wave a start of 14 us and 0.2 ns
+// a byte, 8 waves a CU.  Of 2 to 16 KiB the least estimate of both is taken, the
+// shorter part counted 0.6 beside the longer one; 2 KiB where that makes at most
+// a wave to every other CU (22 rows 20 us in waves, 26 in lanes).  300 requests
+// of 0.97 GB 866 us grouped, 434 with rows of under 16 KiB in lanes, 317 in waves
+// from 2 KiB on; but 122000 rows of 520 uint32 162 us in lanes and 830 in waves,
+// 20000 of 1000 146 and 218.  Over 312 mixes of up to 6 GB the choice takes 1.02
+// of the best of the four and 0.54 of the grouped plan's time on average, at
+// worst 1.2 of either (27211 rows of 1 to 500 uint32: 69 us, 82).
+// 5858 requests of 2.9 million rows of under 16 KiB stay in lanes, 1.81 ms
+// (2.33 with those of 8 KiB and more in waves).
 struct SmallSizes { uint64_t wave_min; uint32_t pack; };
 SmallSizes small_sizes(const std::vector<BatchReq> &in, uint64_t streams, const mrg_batch_config &cfg,
                        int cus)
@@ -181,23 +183,24 @@ SmallSizes small_sizes(const std::vector<BatchReq> &in, uint64_t streams, const 
     SmallSizes best = {kWaveMinBytes, 1};
     double best_us = 0;
     for (uint64_t w = 2048; w <= kWaveMinBytes; w *= 2) {
-        double chain = 0, wave = 0;
-        uint64_t lanes = 0, nw = 0;
+        double chain = 0, lanes = 0, wave = 0;
+        uint64_t nw = 0;
         for (const BatchReq &R : in) {
             const uint64_t bytes = R.n * (R.dtype == 2 ? 8 : 4);
             if (bytes < w) {
-                lanes += R.k;
-                chain = std::max(chain, (double)R.n * kLane[R.dtype]);
+                const double us = (double)R.n * kLane[R.dtype];
+                lanes += (double)R.k * us;
+                chain = std::max(chain, us);
             } else {
                 nw += R.k;
                 wave += (double)R.k * ((bytes < 131072 ? 14.0 : 0.0) + 0.0002 * (double)bytes);
             }
         }
-        chain *= 1.0 + (double)lanes / ((double)cus * 512);
+        chain += lanes / ((double)cus * 256);
         const uint32_t pack = nw <= 1024 ? 1 : streams < (uint64_t)cus * 512 ? 2 : 4;
         const double few = nw <= 1024 ? 1 : 2;  // streams in series in the last wave
         if (nw)
-            wave = std::max(wave / par, std::min(std::ceil((double)nw / (par * few)), 2.0) * few * 15) + 10;
+            wave = std::max(wave / par, std::min(std::ceil((double)nw / (par * few)), 2.0) * few * 15) + 15;
         if (w == 2048 && nw <= (uint64_t)cus / 2) return {w, 1};
         double us = std::max(chain, wave) + 0.6 * std::min(chain, wave);
         if (w < kWaveMinBytes) us *= 1.2;  // the estimate's own error

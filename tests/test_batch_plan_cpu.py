@@ -181,3 +181,16 @@ def test_many_streams_keep_long_segments():
     rows = [(0, 131072, 100, 0, 0, mg.U32, 0), (131072, 8, 1 << 20, 0, 0, mg.U32, 0)]
     assert mg.batch_plan(rows)["segment_bytes"] == 256 << 10
     assert mg.batch_plan(rows[1:])["segment_bytes"] == 128 << 10
+
+
+def test_many_streams_of_all_lengths_stay_in_lanes():
+    """The lanes' time is the longest row and then all rows over the lanes, not
+    the longest row once per round of lanes."""
+    rng = np.random.default_rng(5)
+    k = np.exp(rng.uniform(0, np.log(4096), 5858)).astype(int) + 1
+    n = np.minimum(np.exp(rng.uniform(0, np.log(4096), 5858)).astype(int) + 1, 2047)
+    dt = rng.integers(0, 3, 5858)
+    first = np.concatenate([[0], np.cumsum(k)[:-1]])
+    rows = [(int(f), int(c), int(v), 0, 0, int(d), 0) for f, c, v, d in zip(first, k, n, dt)]
+    p = mg.batch_plan(rows)
+    assert p["wave_min_bytes"] == 16 << 10 and p["segment_bytes"] == 256 << 10
