@@ -171,7 +171,7 @@ void plan_batch(const mrg_request *reqs, uint64_t n, const mrg_batch_config &cfg
 // from 2 KiB on; but 122000 rows of 520 uint32 162 us in lanes and 830 in waves,
 // 20000 of 1000 146 and 218.  Over 312 mixes of up to 6 GB the choice takes 1.02
 // of the best of the four and 0.54 of the grouped plan's time on average, at
-// worst 1.2 of either (27211 rows of 1 to 500 uint32: 69 us, 82).
+// worst 1.2 of either (27211 rows of 1 to 385 uint32: 69 us, 82).
 // 5858 requests of 2.9 million rows of under 16 KiB stay in lanes, 1.81 ms
 // (2.33 with those of 8 KiB and more in waves).
 struct SmallSizes { uint64_t wave_min; uint32_t pack; };
