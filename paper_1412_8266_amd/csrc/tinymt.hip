@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gen_device.hpp"   // rows_fill, rows_fill_carry, rows_fill_short, put1
 #include "kernels.h"
 #include "tinymt_device.h"
@@ -101,7 +103,7 @@ tmt_jump_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t f
     r.store(planes, plane_stride, first + s);
 }
 
-// The stream as the row writers draw from it.
+// The stream as the row writers and the interleaved floats draw from it.
 struct RowStream : TinyMTStream {
     __device__ __forceinline__ uint32_t next_u32()
     {
@@ -154,7 +156,9 @@ tmt_sm_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fir
     if (active) g.store(planes, plane_stride, first + s0 + lane);
 }
 
-// Interleaved output out[k * count + s].
+// Interleaved output out[k * count + s].  A value's conversion is work beside the
+// chain of steps, as rows are, so floats draw by step_rows (13334 x 2000 float32
+// 97.6 us, with step 101.2; float64 106.0 and 108.4; uint32 104.0 and 92.8).
 template <int DT>
 __global__ void __launch_bounds__(256)
 tmt_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
@@ -164,7 +168,7 @@ tmt_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fir
     constexpr int ES = Elem<DT>::size;
     const uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= count) return;
-    TinyMTStream g;
+    std::conditional_t<DT == 0, TinyMTStream, RowStream> g;
     g.load(planes, plane_stride, first + s, records, q0);
     unsigned char *p = out + s * ES;
     const uint64_t step = count * ES;
