@@ -20,8 +20,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
 #include "gen_device.hpp"   // rows_fill, rows_fill_carry, rows_fill_short, put1
 #include "kernels.h"
 #include "tinymt_device.h"
@@ -156,10 +154,12 @@ tmt_sm_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fir
     if (active) g.store(planes, plane_stride, first + s0 + lane);
 }
 
-// Interleaved output out[k * count + s].  A value's conversion is work beside the
-// chain of steps, as rows are, so floats draw by step_rows (13334 x 2000 float32
-// 97.6 us, with step 101.2; float64 106.0 and 108.4; uint32 104.0 and 92.8).
-template <int DT>
+// Interleaved output out[k * count + s] of stream objects G: RowStream for floats
+// (a value's conversion is work beside the chain of steps, as rows are: 13334 x
+// 2000 float32 97.6 us, with step 101.2; float64 106.0 and 108.4) and for uint32
+// of up to one workgroup, else TinyMTStream (x 2000: 1 to 64 streams 81-91 us,
+// with step 87-100; 200 87 and 88; 512 89.7 and 88.6; 13334 104.0 and 92.8).
+template <int DT, class G>
 __global__ void __launch_bounds__(256)
 tmt_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t first,
               uint64_t count, uint64_t n, unsigned char *__restrict__ out,
@@ -168,7 +168,7 @@ tmt_il_kernel(uint32_t *__restrict__ planes, uint64_t plane_stride, uint64_t fir
     constexpr int ES = Elem<DT>::size;
     const uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= count) return;
-    std::conditional_t<DT == 0, TinyMTStream, RowStream> g;
+    G g;
     g.load(planes, plane_stride, first + s, records, q0);
     unsigned char *p = out + s * ES;
     const uint64_t step = count * ES;
@@ -196,8 +196,13 @@ hipError_t launch_tmt_fill_t(uint32_t *planes, uint64_t plane_stride, uint64_t f
 {
     unsigned char *o = (unsigned char *)out;
     if (layout == 1) {
-        hipLaunchKernelGGL((tmt_il_kernel<DT>), dim3(blocks_of(count, 256)), dim3(256), 0, st,
-                           planes, plane_stride, first, count, n, o, records, q0);
+        const dim3 grid(blocks_of(count, 256)), block(256);
+        if (DT == 0 && count > 256)
+            hipLaunchKernelGGL((tmt_il_kernel<DT, TinyMTStream>), grid, block, 0, st, planes,
+                               plane_stride, first, count, n, o, records, q0);
+        else
+            hipLaunchKernelGGL((tmt_il_kernel<DT, RowStream>), grid, block, 0, st, planes,
+                               plane_stride, first, count, n, o, records, q0);
     } else {
         constexpr int ES = Elem<DT>::size;
         const int tb = tile_bytes ? tile_bytes : (n * ES < 1024 ? 128 : 256);

@@ -281,3 +281,19 @@ def test_full_workload_sampled(mg):
         want, st3 = oracle.tmt_fill(st2, n, oracle.U32, 0, P)
         assert np.array_equal(got, want)
         assert np.array_equal(states_of(ss)[rows], st3)
+
+
+@pytest.mark.parametrize("count", [255, 256, 257])
+@pytest.mark.parametrize("n", [1, 4, 131])
+def test_interleaved_at_one_workgroup(mg, count, n):
+    """uint32 of up to one workgroup and of more are drawn by two forms of the
+    step; both continue one stream."""
+    say("tinymt steps", count, n)
+    P, _ = oracle.tmt_search(MASTER, (count + 2) // 64 + 1)
+    with mg.StreamSet(count + 3, master_seed=MASTER, generator="tinymt", per_param=64) as ss:
+        st = states_of(ss)
+        for _ in range(2):
+            out = host(ss.fill(n, mg.U32, 1, first=2, count=count))
+            want, st[2:2 + count] = oracle.tmt_fill(st[2:2 + count], n, mg.U32, 1, P)
+            assert np.array_equal(out, want)
+        assert np.array_equal(states_of(ss), st)
