@@ -432,16 +432,19 @@ void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, ui
 // the segments have to pay for it.  uint32, up to half a wave of streams per
 // SIMD they do (32768 x 4096 184 -> 100 us on lines, 168 -> 155 off them); up
 // to 40960 on lines and from 192 steps on (36000 x 1000 46 -> 34; off lines
-// x 4096 171 -> 197, x 128 9.2 -> 9.9); beyond, only near a wave per SIMD, on
-// lines and for long fills (65536 x 1000 53 -> 51, off lines 72 -> 76; 52000 x
-// 4096 1.04 times).  binary64: up to 18432 always (18001 x 4096 off lines 0.92
+// x 4096 171 -> 197, x 128 9.2 -> 9.9), off lines up to 38912 for 192 to 800
+// steps (38900 x 800 0.92 times, x 1000 1.10) and up to 43008 for 192 to 600
+// (42788 x 512 28.1 -> 21.2, 45000 x 512 0.99 times); beyond, only near a wave
+// per SIMD, on lines and for long fills (65536 x 1000 53 -> 51, off lines 72 ->
+// 76; 52000 x 4096 1.04 times).  binary64: up to 18432 always (18001 x 4096 off lines 0.92
 // times, 20001 1.02, 24000 x 1000 47 -> 52), up to 28672 on lines (28000 x 4096
 // 0.97 times, 30000 1.04), up to 32768 for short fills (x 512 0.90 times).
 bool steps_cut(int cus, uint64_t count, uint64_t n, uint64_t es, bool lined)
 {
     const uint64_t c = (uint64_t)cus;
     if (es == 4)
-        return count <= c * 128 || (lined && n >= 192 && count <= c * 160) ||
+        return count <= c * 128 || (n >= 192 && n <= 600 && count <= c * 168) ||
+               (n >= 192 && (lined ? count <= c * 160 : n <= 800 && count <= c * 152)) ||
                (lined && n >= 1000 && count >= c * 224);
     return count <= c * 72 || (count <= c * 128 && (n <= 512 || (lined && (n < 1000 || count <= c * 112))));
 }

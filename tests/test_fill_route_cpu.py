@@ -84,7 +84,9 @@ STEP_RULE = [
     (18432, 4096, F64, 24, True), (18433, 4096, F64, 24, False), (18448, 4096, F64, 0, True),
     (28672, 4096, F64, 0, True), (28688, 4096, F64, 0, False), (32768, 999, F64, 0, True),
     (32768, 1000, F64, 0, False), (32768, 512, F64, 8, True), (32768, 513, F64, 8, False),
-    (32784, 512, F64, 0, False)]
+    (32784, 512, F64, 0, False), (38912, 800, U32, 4, True), (38912, 801, F32, 4, False),
+    (38913, 800, U32, 0, False), (43008, 600, F32, 20, True), (43008, 601, U32, 20, False),
+    (43009, 600, U32, 0, False), (43008, 192, U32, 4, True), (43008, 191, U32, 4, False)]
 
 
 @pytest.mark.parametrize("count,n,dtype,off,cut", STEP_RULE)

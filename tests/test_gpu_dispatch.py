@@ -101,7 +101,7 @@ STEPS = [(2, 40000, 0, 1), (70, 20000, 2, 0), (1, 64, 0, 0), (1, 70001, 1, 3), (
 
 
 # both sides of the lines where many streams stop being cut
-STEPS += [(32800, 192, 0, 0), (32800, 192, 0, 5), (57344, 1000, 1, 0), (65536, 1001, 0, 0),
+STEPS += [(38912, 799, 0, 1), (43007, 577, 1, 5), (32800, 192, 0, 0), (32800, 192, 0, 5), (57344, 1000, 1, 0), (65536, 1001, 0, 0),
           (18432, 700, 2, 1), (28672, 1000, 2, 0), (28688, 1000, 2, 0), (32768, 520, 2, 0)]
 
 
