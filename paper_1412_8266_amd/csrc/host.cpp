@@ -577,14 +577,15 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     // players per lane, 32 where that leaves four waves per CU or fewer (65536 x
     // 52: with 256 18.4 us, with 64, a wave on each SIMD, 11.5, with 32 10.3, with
     // 16 14.0; 70400 x 52 has more, 32 loses 2 %).  While the items at 64
-    // players do not fill the chip, up to 16 waves to a workgroup, which count
-    // themselves in together, and the stream moved in the kernel; then a wave
-    // to a workgroup, since the waves of one share a CU and write far apart, and
-    // a launch for the stream (65536 x 8000 uint32 439 us, in groups of 16 475;
-    // 8192 x 6000 43.4 and 45.8; 4096 x 2048 16.9 and 15.4).  Over 109 deals of
-    // 1 MB to 2 GB these rules took 1.03 times the best of 32 to 256 players per
-    // lane in groups of 1, 4 and 16 waves, 32 players and 16 waves for all 1.05,
-    // 256 players and one wave 1.40.
+    // players do not fill the chip, and for up to 4096 cards, up to 16 waves to a
+    // workgroup, which count themselves in together, and the stream moved in the
+    // kernel (4096 x 4096 float64 31.7 us against 39.9 with a wave to a workgroup
+    // and a launch; 8192 x 2048 26.6 and 32.3; 65536 x 1024 52.6 and 55.3); beyond,
+    // a wave to a workgroup, since the waves of one share a CU and write far
+    // apart, and a launch for the stream (65536 x 8000 uint32 439 us, in groups of
+    // 16 475; 8192 x 6000 43.4 and 45.8).  Over 218 deals of 1 MB to 2 GB these
+    // rules take 1.03 times the best of 32 to 256 players per lane in groups of
+    // 1, 4 and 16 waves, 32 players and 16 waves for all 1.04.
     const uint64_t slots = (uint64_t)cus * 16;  // resident waves
     A.P = players;
     A.K = per_player;
@@ -594,7 +595,7 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     const uint64_t target = 4 * slots;
     const uint64_t ts_max = (players + A.R - 1) / A.R;
     const uint64_t at64 = nkb * ((ts_max + 63) / 64);
-    const bool few = at64 < (uint64_t)cus * 15;
+    const bool grouped = at64 < (uint64_t)cus * 15 || per_player <= 4096;
     const uint64_t ts_min = at64 <= (uint64_t)cus * 4 ? 32 : 64;
     uint64_t Ts = ts_max;
     if (nkb < target) {
@@ -620,8 +621,8 @@ bool plan_leap(int cus, uint64_t set_n, uint64_t players, uint64_t per_player, u
     A.end = jump_matrices(en);  // the stream moves past the N outputs dealt
     // up to 16 waves a workgroup, for at most 256 arrivals at the ticket
     A.waves = (unsigned)(A.items < slots ? A.items : slots);
-    A.per_group = !few || A.waves <= 256 ? 1 : A.waves >= 4096 ? 16 : (A.waves + 255) / 256;
-    A.move = few && mrg::ticket_pitch(set_n);
+    A.per_group = !grouped || A.waves <= 256 ? 1 : A.waves >= 4096 ? 16 : (A.waves + 255) / 256;
+    A.move = grouped && mrg::ticket_pitch(set_n);
     return false;
 }
 

@@ -116,9 +116,11 @@ def test_blocks_of_a_stream_in_order(mib, dtype, block, chunk):
 
 
 # (players, cards, waves, waves to a workgroup, players a lane, moved in the
-# kernel): both sides of 4 and of 15 waves per CU at 64 players a lane
+# kernel): both sides of 4 and of 15 waves per CU at 64 players a lane, and of
+# 4096 cards
 DEAL_RULE = [(2, 5, 1, 1, 1, 1), (1000, 1000, 512, 2, 32, 1), (65536, 52, 2048, 8, 32, 1),
-             (65537, 52, 1025, 5, 64, 1), (245696, 52, 3839, 15, 64, 1), (245697, 52, 3840, 1, 64, 0),
+             (65537, 52, 1025, 5, 64, 1), (245696, 52, 3839, 15, 64, 1), (245697, 52, 3840, 15, 64, 1),
+             (4096, 4096, 4096, 16, 64, 1), (4096, 4097, 4096, 1, 64, 0),
              (60, 64 * 3839, 3839, 15, 60, 1), (60, 64 * 3840, 3840, 1, 60, 0),
              (65536, 8000, 4096, 1, 497, 0), (65536, 65536, 4096, 1, 4096, 0)]
 
