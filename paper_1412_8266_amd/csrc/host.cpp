@@ -392,22 +392,32 @@ mrg::JumpMatrices jump_matrices(const uint64_t e[3])
 //   up to 192 MiB  32 KiB, two chunks (72 MB 22.9 us, 16 KiB 23.6, 64 KiB, just
 //                  over one to a SIMD, 28.9; 128 MiB 29.4, 32.5 and 28.2);
 //                  binary64 up to 320 MiB (260 MB 44.8 us, 64 KiB 45.2)
-//   up to 320 MiB  64 KiB, in chunks of 64 KiB: 256 uint32 per lane and start
-//                  state (260 MB 47.4 us, 32 KiB 52.9)
-//   beyond         the same with two pieces staged per flush, half the waves
-//                  and longer runs of lines (1.1 GB 204 us, with one piece 214);
-//                  128 KiB from 2 GiB on (4 GiB 763, 64 KiB 786, 2 MiB 2 % more)
+//   up to 320 MiB  48 KiB, three chunks (270 MB 62.5 us, 32 KiB 63.9, 64 KiB 67.3,
+//                  in one chunk 68.7; 220 MB 54.3, 48.6, 54.9 and 57.9), or where
+//                  the busiest SIMD then has less to draw 64 KiB in one chunk: 256
+//                  uint32 per lane and start state (64 rows of 4 MiB 59.5 us, 48
+//                  KiB 60.7)
+//   beyond         64 KiB in one chunk, with two pieces staged per flush, half
+//                  the waves and longer runs of lines (1.1 GB 204 us, with one
+//                  piece 214); 128 KiB from 2 GiB on (4 GiB 763, 64 KiB 786, 2
+//                  MiB 2 % more)
 void split_rows(mrg::FillLaunch *fl, int cus, uint64_t set_n, uint64_t count, uint64_t n, uint64_t es)
 {
     const uint64_t row = n * es, want = row / 16 * count / (uint64_t)cus;  // 16 per CU
-    const bool large = want >= (es == 8 ? 81920u : 49152u);
-    const uint64_t unit = want < 3072 ? 8192 : large ? 65536 : 16384;  // a chunk of 64 lanes
-    uint64_t bb = want < 3072 ? 8192 : want < 12288 ? 16384 : !large ? 32768 : want < 524288 ? 65536 : 131072;
+    // bytes of the SIMD that draws most
+    auto most = [&](uint64_t b) {
+        const uint64_t simds = (uint64_t)cus * 4, blocks = count * ((row + b - 1) / b);
+        return (blocks + simds - 1) / simds * b;
+    };
+    const bool large = want >= 81920;
+    const uint64_t mid = es == 8 || want < 49152 ? 32768 : most(49152) < most(65536) ? 49152 : 65536;
+    uint64_t bb = want < 3072 ? 8192 : want < 12288 ? 16384 : !large ? mid : want < 524288 ? 65536 : 131072;
+    const uint64_t unit = want < 3072 ? 8192 : bb >= 65536 ? 65536 : 16384;  // a chunk of 64 lanes
     // fewer blocks than 2^32 per row, and than 2^31 workgroups in all
     while (row / bb >= ((uint64_t)1 << 31) / count) bb *= 2;
     fl->kernel = 2;
     fl->L = (int)(unit / 64 / es);
-    fl->pieces = want >= 81920 ? 2 : 1;
+    fl->pieces = large ? 2 : 1;
     fl->B = bb / es;
     // a remainder under an eighth of a block goes to the last block
     fl->nblk = (uint32_t)(n / fl->B + (n % fl->B > fl->B / 8 || n < fl->B));

@@ -100,7 +100,8 @@ def test_interleaved_streams_are_cut_where_it_pays(count, n, dtype, off, cut):
 # (MiB of one stream in order, dtype, block bytes, chunk bytes): both sides of
 # the block sizes' lines
 ORDER_RULE = [(1, U32, 8, 8), (11, U32, 8, 8), (12, U32, 16, 16), (47, F32, 16, 16), (48, U32, 32, 16),
-              (191, F32, 32, 16), (192, U32, 64, 64), (319, F64, 32, 16), (320, F64, 64, 64),
+              (191, F32, 32, 16), (192, U32, 64, 64), (193, U32, 48, 16), (256, U32, 64, 64),
+              (257, F32, 48, 16), (319, F32, 64, 64), (319, F64, 32, 16), (320, F64, 64, 64),
               (320, U32, 64, 64), (2047, U32, 64, 64), (2048, F64, 128, 64)]
 
 
