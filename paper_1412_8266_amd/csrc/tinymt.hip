@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gen_device.hpp"   // rows_fill, rows_fill_carry, rows_fill_short, put1
 #include "kernels.h"
 #include "tinymt_device.h"
@@ -196,13 +198,15 @@ hipError_t launch_tmt_fill_t(uint32_t *planes, uint64_t plane_stride, uint64_t f
 {
     unsigned char *o = (unsigned char *)out;
     if (layout == 1) {
+        using Few = RowStream;
+        using Many = std::conditional_t<DT == 0, TinyMTStream, RowStream>;
         const dim3 grid(blocks_of(count, 256)), block(256);
-        if (DT == 0 && count > 256)
-            hipLaunchKernelGGL((tmt_il_kernel<DT, TinyMTStream>), grid, block, 0, st, planes,
-                               plane_stride, first, count, n, o, records, q0);
+        if (count > 256)
+            hipLaunchKernelGGL((tmt_il_kernel<DT, Many>), grid, block, 0, st, planes, plane_stride,
+                               first, count, n, o, records, q0);
         else
-            hipLaunchKernelGGL((tmt_il_kernel<DT, RowStream>), grid, block, 0, st, planes,
-                               plane_stride, first, count, n, o, records, q0);
+            hipLaunchKernelGGL((tmt_il_kernel<DT, Few>), grid, block, 0, st, planes, plane_stride,
+                               first, count, n, o, records, q0);
     } else {
         constexpr int ES = Elem<DT>::size;
         const int tb = tile_bytes ? tile_bytes : (n * ES < 1024 ? 128 : 256);
